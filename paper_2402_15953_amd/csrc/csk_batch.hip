@@ -284,20 +284,17 @@ __device__ __forceinline__ void seg16_quads(const BItem &I, uint64_t begin_, uin
         uint32_t j[K], neg[K];
         if constexpr (E1) {
             CoefE1<NC> C;
-            C.load(cf);
-            uint32_t flag = 0;
+            C.load(cf, m);
+            HashFlag flag;
 #pragma unroll
-            for (int g = 0; g < K; ++g) {
-                uint32_t f;
-                C.bin_neg_fast(Q.x[g], j[g], neg[g], f);
-                flag = max(flag, f);
+            for (int g = 0; g < K; ++g) C.bin_neg_fast(Q.x[g], j[g], neg[g], flag);
+            if (C.bin_near(flag, 0xFFFFFFFFu)) {
+#pragma unroll
+                for (int g = 0; g < K; ++g) j[g] = C.bin(Q.x[g]);
             }
-            if (flag >= 0xFFFFFFFFu) {  // a hash may need the full reduction
+            if (C.sign_near(flag, 0xFFFFFFFFu)) {
 #pragma unroll
-                for (int g = 0; g < K; ++g) {
-                    j[g] = C.bin(Q.x[g]);
-                    neg[g] = C.neg(Q.x[g]);
-                }
+                for (int g = 0; g < K; ++g) neg[g] = C.neg(Q.x[g]);
             }
         } else {
 #pragma unroll

@@ -201,17 +201,21 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg(const uint32_t *__rest
     for (int t = t0; t <= t1; ++t) {
         const uint64_t *cf = coef + (size_t)t * cpr;
         CoefE1<NC> K;
-        if constexpr (E1) K.load(cf);
+        if constexpr (E1) K.load(cf, m);
         const uint32_t row = (uint32_t)((uint64_t)t * m - cell0);  // may wrap; used mod 2^32
         for (uint64_t i = begin + threadIdx.x; i < end; i += kSegBlock) {
             uint32_t x[NC];
             load_keys<NC>(keys, i, vec2, x);
             uint32_t j, neg;
             if constexpr (E1) {  // power-of-two m only
-                j = K.bin(x) & (m - 1);
+                HashFlag flag;
+                j = K.bin_fast(x, flag);
+                if (K.bin_near(flag, 0xFFFFFFFFu)) j = K.bin(x);
+                j &= m - 1;
                 const uint32_t loc = row + j;
                 if (!whole && loc >= span) continue;  // bucket outside this segment
-                neg = K.neg(x);
+                neg = K.neg_fast(x, flag);
+                if (K.sign_near(flag, 0xFFFFFFFFu)) neg = K.neg(x);
             } else if (whole) {
                 hash_rep<NC>(cf, plan, x, j, neg);
             } else {
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg_compact(const uint32_t
     for (uint32_t e = threadIdx.x; e < R; e += kSegBlock) s_c[e] = 0;
     __syncthreads();
     CoefE1<NC> K;
-    K.load(coef + (size_t)t * cpr);
+    K.load(coef + (size_t)t * cpr, m);
     const uint64_t begin = (uint64_t)wg.chunk * chunk;
     const uint64_t end = begin + chunk < n ? begin + chunk : n;
     uint32_t head = 0, count = 0;  // wave-uniform queue state
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
     for (int t = t0; t <= t1; ++t) {
         const uint64_t *cf = coef + (size_t)t * cpr;
         CoefE1<NC> K;
-        if constexpr (E1) K.load(cf);
+        if constexpr (E1) K.load(cf, m);
         const uint32_t row = (uint32_t)((uint64_t)t * m - cell0);
         unsigned long long *srow = sketch + (uint64_t)t * m;
         // Tuples go in groups of kSeg16Group: all are hashed in one straight-line block
@@ -373,19 +377,9 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
                         spill16(pend[g].w, shift16(pend[g].inc), srow + pend[g].j);
             }
         };
-        auto hash1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, uint32_t &flag) {
-            if constexpr (E1) {
-                K.bin_neg_fast(x, j, neg, flag);
-            } else {
-                hash_rep<NC>(cf, plan, x, j, neg);
-                flag = 0;
-            }
-        };
-        auto exact1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg) {
-            if constexpr (E1) {
-                j = K.bin(x);
-                neg = K.neg(x);
-            }
+        auto hash1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, HashFlag &flag) {
+            if constexpr (E1) K.bin_neg_fast(x, j, neg, flag);
+            else hash_rep<NC>(cf, plan, x, j, neg);
         };
         auto add1 = [&](uint32_t j, uint32_t neg, int64_t wt) -> Pend {
             if constexpr (E1) j &= m - 1;
@@ -420,19 +414,18 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
 #pragma unroll
             for (int g = 0; g < G; ++g)
                 if (i + (G + g) * B < end) load(i + (G + g) * B, xn[g], wn[g]);
-            uint32_t j[G], neg[G], flag = 0;
+            uint32_t j[G], neg[G];
+            HashFlag flag;
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                uint32_t f;
-                hash1(x[g], j[g], neg[g], f);
-                flag = max(flag, f);
-            }
-            if (flag >= canon_thresh) {  // a hash may need the full reduction
+            for (int g = 0; g < G; ++g) hash1(x[g], j[g], neg[g], flag);
+            if constexpr (E1) {
+                if (K.bin_near(flag, canon_thresh)) {
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    uint32_t jj, nn, f;
-                    hash1(x[g], jj, nn, f);
-                    if (f >= canon_thresh) exact1(x[g], j[g], neg[g]);
+                    for (int g = 0; g < G; ++g) j[g] = K.bin(x[g]);
+                }
+                if (K.sign_near(flag, canon_thresh)) {
+#pragma unroll
+                    for (int g = 0; g < G; ++g) neg[g] = K.neg(x[g]);
                 }
             }
             Pend now[G];
@@ -446,9 +439,13 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
 #pragma unroll
         for (int g = 0; g < G - 1; ++g) {
             if (i + g * B < end) {
-                uint32_t jj, nn, f;
+                uint32_t jj, nn;
+                HashFlag f;
                 hash1(xn[g], jj, nn, f);
-                if (f >= canon_thresh) exact1(xn[g], jj, nn);
+                if constexpr (E1) {
+                    if (K.bin_near(f, canon_thresh)) jj = K.bin(xn[g]);
+                    if (K.sign_near(f, canon_thresh)) nn = K.neg(xn[g]);
+                }
                 const Pend now = add1(jj, nn, wn[g]);
                 check();
                 pend[0] = now;
@@ -500,7 +497,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
     const uint64_t nq = len >> 2;
     const uint64_t *cf = coef + (size_t)t * cpr;
     CoefE1<NC> K;
-    if constexpr (E1) K.load(cf);
+    if constexpr (E1) K.load(cf, m);
     unsigned long long *srow = sketch + (uint64_t)t * m;
 
     struct Quad {
@@ -552,19 +549,9 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
             for (int g = 0; g < 4; ++g) Q.w[g] = 1;
         }
     };
-    auto hash1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, uint32_t &flag) {
-        if constexpr (E1) {
-            K.bin_neg_fast(x, j, neg, flag);
-        } else {
-            hash_rep<NC>(cf, plan, x, j, neg);
-            flag = 0;
-        }
-    };
-    auto exact1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg) {
-        if constexpr (E1) {
-            j = K.bin(x);
-            neg = K.neg(x);
-        }
+    auto hash1 = [&](const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, HashFlag &flag) {
+        if constexpr (E1) K.bin_neg_fast(x, j, neg, flag);
+        else hash_rep<NC>(cf, plan, x, j, neg);
     };
     // j is the bucket before the mask (E1) or reduced (otherwise); the word's byte offset
     // masks and scales in two instructions, and the half's shift uses only bit 0 of j
@@ -592,19 +579,18 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
         }
     };
     auto process = [&](const Quad &Q, Pend (&P)[4]) {
-        uint32_t j[4], neg[4], flag = 0;
+        uint32_t j[4], neg[4];
+        HashFlag flag;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            uint32_t f;
-            hash1(Q.x[g], j[g], neg[g], f);
-            flag = max(flag, f);
-        }
-        if (flag >= canon_thresh) {  // a hash may need the full reduction
+        for (int g = 0; g < 4; ++g) hash1(Q.x[g], j[g], neg[g], flag);
+        if constexpr (E1) {
+            if (K.bin_near(flag, canon_thresh)) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                uint32_t jj, nn, f;
-                hash1(Q.x[g], jj, nn, f);
-                if (f >= canon_thresh) exact1(Q.x[g], j[g], neg[g]);
+                for (int g = 0; g < 4; ++g) j[g] = K.bin(Q.x[g]);
+            }
+            if (K.sign_near(flag, canon_thresh)) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) neg[g] = K.neg(Q.x[g]);
             }
         }
 #pragma unroll
@@ -636,9 +622,13 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
 #pragma unroll
         for (int c = 0; c < NC; ++c) x[c] = keys[i * NC + c];
         const int64_t wt = HW ? weights[i] : 1;
-        uint32_t j, neg, f;
+        uint32_t j, neg;
+        HashFlag f;
         hash1(x, j, neg, f);
-        if (f >= canon_thresh) exact1(x, j, neg);
+        if constexpr (E1) {
+            if (K.bin_near(f, canon_thresh)) j = K.bin(x);
+            if (K.sign_near(f, canon_thresh)) neg = K.neg(x);
+        }
         Pend one[4];
         one[0] = add1(j, neg, wt);
 #pragma unroll
@@ -681,32 +671,10 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
     for (uint32_t e = threadIdx.x; e < kSeg16Words; e += kSegBlock) s_w[e] = (kBias16 << 16) | kBias16;
     __syncthreads();
     CoefE1<NC> K;
-    K.load(coef + (size_t)t * cpr);
+    K.load(coef + (size_t)t * cpr, m);
     unsigned long long *srow = sketch + (uint64_t)t * m + off;
     const uint64_t begin = (uint64_t)wg.chunk * chunk;
     const uint64_t end = begin + chunk < n ? begin + chunk : n;
-    // bin and sign without the canonical reduction (CoefE1::bin_neg_fast split in two)
-    auto bin_fast = [&](const uint32_t (&x)[NC], uint32_t &flag) {
-        uint32_t j = 0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const HPair rb = hstep_p(hpair(K.b1[c]), x[c], K.b0[c]);
-            j += rb.lo + (rb.hi >> 29);
-            flag = max(flag, rb.hi | 0xE0000000u);
-        }
-        return j;
-    };
-    auto neg_fast = [&](const uint32_t (&x)[NC], uint32_t &flag) {
-        uint32_t neg = 0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const HPair rs = hstep_p(hstep_p(hstep_p(hpair(K.a[c][3]), x[c], K.a[c][2]), x[c], K.a[c][1]), x[c],
-                                     K.a[c][0]);
-            neg ^= rs.lo ^ (rs.hi >> 29);
-            flag = max(flag, rs.hi | 0xE0000000u);
-        }
-        return neg & 1u;
-    };
     uint32_t head = 0, count = 0;  // wave-uniform queue state
     auto drain = [&](uint32_t k) {  // lanes < k take one queued tuple each
         if ((uint32_t)lane < k) {
@@ -715,9 +683,9 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
 #pragma unroll
             for (int c = 0; c < NC; ++c) x[c] = s_qx[wave][c][slot];
             const uint32_t l = s_ql[wave][slot];
-            uint32_t flag = 0;
-            uint32_t neg = neg_fast(x, flag);
-            if (flag >= canon_thresh) neg = K.neg(x);
+            HashFlag flag;
+            uint32_t neg = K.neg_fast(x, flag);
+            if (K.sign_near(flag, canon_thresh)) neg = K.neg(x);
             neg ^= l >> 31;
             const uint32_t j = l & (kRange - 1);
             const uint32_t inc = inc16(neg, (j & 1u) << 4);
@@ -734,9 +702,9 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
         uint32_t x[NC], loc = 0;
         if (i < end) {
             load_keys<NC>(keys, i, vec2, x);
-            uint32_t flag = 0;
-            uint32_t j = bin_fast(x, flag);
-            if (flag >= canon_thresh) j = K.bin(x);
+            HashFlag flag;
+            uint32_t j = K.bin_fast(x, flag);
+            if (K.bin_near(flag, canon_thresh)) j = K.bin(x);
             j = (j & (m - 1)) - off;
             if (j < kRange) {
                 in = true;
@@ -1007,22 +975,27 @@ struct PartHasher {
     __device__ __forceinline__ void load(const uint64_t *coef_t)
     {
         cf = coef_t;
-        if constexpr (FAST) K.load(coef_t);
+        if constexpr (FAST) K.load(coef_t, mmask + 1);
     }
-    __device__ __forceinline__ void hash(const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, uint32_t &flag) const
+    __device__ __forceinline__ void hash(const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg, HashFlag &flag) const
+    {
+        if constexpr (FAST) K.bin_neg_fast(x, j, neg, flag);
+        else hash_rep<NC>(cf, plan, x, j, neg);
+    }
+    // The tuples' bins (signs) again exactly, where the group's flag asks for it.
+    template <int G>
+    __device__ __forceinline__ void settle(const uint32_t (*x)[NC], uint32_t (&j)[G], uint32_t (&neg)[G],
+                                           const HashFlag &flag, uint32_t canon) const
     {
         if constexpr (FAST) {
-            K.bin_neg_fast(x, j, neg, flag);
-        } else {
-            hash_rep<NC>(cf, plan, x, j, neg);
-            flag = 0;
-        }
-    }
-    __device__ __forceinline__ void exact(const uint32_t (&x)[NC], uint32_t &j, uint32_t &neg) const
-    {
-        if constexpr (FAST) {
-            j = K.bin(x);
-            neg = K.neg(x);
+            if (K.bin_near(flag, canon)) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) j[g] = K.bin(x[g]);
+            }
+            if (K.sign_near(flag, canon)) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) neg[g] = K.neg(x[g]);
+            }
         }
     }
     __device__ __forceinline__ uint32_t bucket(uint32_t j) const { return FAST ? (j & mmask) : j; }
@@ -1334,21 +1307,11 @@ __global__ __launch_bounds__(kPB, 4) void k_part_hash(const uint32_t *__restrict
                 for (int g = 0; g < G; ++g) P[G * q + g] = kPartSink;
                 continue;
             }
-            uint32_t j[G], ng[G], flag = 0;
+            uint32_t j[G], ng[G];
+            HashFlag flag;
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                uint32_t f;
-                hs.hash(x[G * q + g], j[g], ng[g], f);
-                flag = max(flag, f);
-            }
-            if (flag >= canon_thresh) {  // a hash may need the full reduction
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    uint32_t jj, nn, f;
-                    hs.hash(x[G * q + g], jj, nn, f);
-                    if (f >= canon_thresh) hs.exact(x[G * q + g], j[g], ng[g]);
-                }
-            }
+            for (int g = 0; g < G; ++g) hs.hash(x[G * q + g], j[g], ng[g], flag);
+            hs.settle(x + G * q, j, ng, flag, canon_thresh);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int s = G * q + g;
@@ -1555,11 +1518,12 @@ __global__ __launch_bounds__(kPAB) void k_part_accum(const uint16_t *__restrict_
             uint32_t x[NC];
             x[0] = h.key[k][0];
             if constexpr (NC == 2) x[1] = h.key[k][1];
-            uint32_t j, ng, f;
-            hs.hash(x, j, ng, f);
-            if (f >= canon_thresh) hs.exact(x, j, ng);
-            const uint32_t b = hs.bucket(j);
-            if ((int)(b >> kPartLog2R) == r) atomicAdd(&my_cnt[b & (kPartR - 1)], ng ? -h.sum[k] : h.sum[k]);
+            uint32_t j[1], ng[1];
+            HashFlag f;
+            hs.hash(x, j[0], ng[0], f);
+            hs.settle(&x, j, ng, f, canon_thresh);
+            const uint32_t b = hs.bucket(j[0]);
+            if ((int)(b >> kPartLog2R) == r) atomicAdd(&my_cnt[b & (kPartR - 1)], ng[0] ? -h.sum[k] : h.sum[k]);
         }
     }
     __syncthreads();
