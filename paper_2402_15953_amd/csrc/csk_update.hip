@@ -203,9 +203,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg(const uint32_t *__rest
         CoefE1<NC> K;
         if constexpr (E1) K.load(cf, m);
         const uint32_t row = (uint32_t)((uint64_t)t * m - cell0);  // may wrap; used mod 2^32
-        for (uint64_t i = begin + threadIdx.x; i < end; i += kSegBlock) {
-            uint32_t x[NC];
-            load_keys<NC>(keys, i, vec2, x);
+        auto add = [&](const uint32_t (&x)[NC], int64_t delta) {
             uint32_t j, neg;
             if constexpr (E1) {  // power-of-two m only
                 HashFlag flag;
@@ -213,7 +211,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg(const uint32_t *__rest
                 if (K.bin_near(flag, 0xFFFFFFFFu)) j = K.bin(x);
                 j &= m - 1;
                 const uint32_t loc = row + j;
-                if (!whole && loc >= span) continue;  // bucket outside this segment
+                if (!whole && loc >= span) return;  // bucket outside this segment
                 neg = K.neg_fast(x, flag);
                 if (K.sign_near(flag, 0xFFFFFFFFu)) neg = K.neg(x);
             } else if (whole) {
@@ -221,11 +219,10 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg(const uint32_t *__rest
             } else {
                 // bins first; signs only for buckets inside this segment
                 j = hash_bin<NC>(cf, plan, x);
-                if (row + j >= span) continue;
+                if (row + j >= span) return;
                 neg = hash_neg<NC>(cf, plan, x);
             }
             const uint32_t loc = row + j;
-            const int64_t delta = weights ? weights[i] : 1;
             if constexpr (sizeof(CT) == 4) {
                 const int32_t v32 = (int32_t)delta;  // +1, or +-1 with unit weights
                 atomicAdd(&s_c[loc], neg ? -v32 : v32);
@@ -233,6 +230,35 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg(const uint32_t *__rest
                 const uint64_t val = neg ? (uint64_t)0 - (uint64_t)delta : (uint64_t)delta;
                 atomicAdd(reinterpret_cast<unsigned long long *>(&s_c[loc]), (unsigned long long)val);
             }
+        };
+        // G tuples of a thread, a block's stride apart, are loaded together (at an index
+        // clamped into the chunk) while the previous G are hashed: the loads' latency, not
+        // the hash, bounded a loop of one tuple at a time
+        constexpr int G = NC <= 2 ? 4 : 2;
+        uint32_t xn[G][NC];
+        int64_t wn[G];
+        auto load = [&](uint64_t i) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const uint64_t ic = min(i + (uint64_t)g * kSegBlock, end - 1);
+                load_keys<NC>(keys, ic, vec2, xn[g]);
+                wn[g] = weights ? weights[ic] : 1;
+            }
+        };
+        if (begin < end) load(begin + threadIdx.x);
+        for (uint64_t i = begin + threadIdx.x; i < end; i += (uint64_t)G * kSegBlock) {
+            uint32_t x[G][NC];
+            int64_t w[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) x[g][c] = xn[g][c];
+                w[g] = wn[g];
+            }
+            load(i + (uint64_t)G * kSegBlock);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                if (i + (uint64_t)g * kSegBlock < end) add(x[g], w[g]);
         }
     }
     __syncthreads();
@@ -839,15 +865,29 @@ __global__ void k_seg_reduce16(const uint32_t *__restrict__ partial, int32_t C, 
     }
 }
 
-// sketch[cell] += sum over chunks of partial[chunk][cell] (int64, wrapping)
+// sketch[cell] += sum over chunks of partial[chunk][cell] (int64, wrapping).  A workgroup
+// takes 64 cells, its four wavefronts a quarter of the chunks each: a small sketch has few
+// cells, and one thread's chain of loads over all chunks took most of its update (4.8 us of
+// 60 us at 5120 cells and 4 chunks; 51 chunks would have taken 15).
 template <typename CT>
-__global__ void k_seg_reduce(const CT *__restrict__ partial, int32_t C, uint64_t cells, uint64_t *sketch)
+__global__ __launch_bounds__(kBlock) void k_seg_reduce(const CT *__restrict__ partial, int32_t C, uint64_t cells,
+                                                       uint64_t *sketch)
 {
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < cells;
-         e += (uint64_t)gridDim.x * blockDim.x) {
+    __shared__ uint64_t s_sum[kBlock / 64][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (uint64_t e0 = (uint64_t)blockIdx.x * 64; e0 < cells; e0 += (uint64_t)gridDim.x * 64) {
+        const uint64_t e = min(e0 + lane, cells - 1);
         uint64_t s = 0;
-        for (int c = 0; c < C; ++c) s += (uint64_t)(int64_t)partial[(size_t)c * cells + e];
-        sketch[e] += s;
+#pragma unroll 8
+        for (int c = wave; c < C; c += kBlock / 64) s += (uint64_t)(int64_t)partial[(size_t)c * cells + e];
+        s_sum[wave][lane] = s;
+        __syncthreads();
+        if (wave == 0 && e0 + lane < cells) {
+#pragma unroll
+            for (int w = 1; w < kBlock / 64; ++w) s += s_sum[w][lane];
+            sketch[e] += s;
+        }
+        __syncthreads();
     }
 }
 
@@ -1536,7 +1576,6 @@ __global__ __launch_bounds__(kPAB) void k_part_accum(const uint16_t *__restrict_
 }
 
 }  // namespace
-int32_t chunks_for_n(int32_t C, uint64_t n);
 namespace {
 
 template <int NC>
@@ -1750,24 +1789,24 @@ cs_status launch_nc(const UpdateArgs &a, int strategy, int grid_blocks, hipStrea
                                a.coef, a.plan.coef_per_rep, a.m, log2m, a.d, sg.R, chunk, vec2, part);
             CSK_HIP(hipGetLastError());
             CSK_MARK(a.ev_stop, s);
-            hipLaunchKernelGGL(k_seg_reduce<int32_t>, dim3((unsigned)std::min<uint64_t>((cells + 255) / 256, 8192)),
-                               dim3(256), 0, s, reinterpret_cast<const int32_t *>(a.scratch), sg.chunks, cells,
+            hipLaunchKernelGGL(k_seg_reduce<int32_t>, dim3((unsigned)std::min<uint64_t>((cells + 63) / 64, 8192)),
+                               dim3(kBlock), 0, s, reinterpret_cast<const int32_t *>(a.scratch), sg.chunks, cells,
                                a.sketch);
         } else if (narrow) {
             if (!fits(sg.chunks, 4)) return fail(CS_EINVAL, "update scratch buffer too small for d * m int32 partial sums");
             int32_t *part = reinterpret_cast<int32_t *>(a.scratch);
             st = e1 ? launch(&k_update_seg<NC, int32_t, true>, part) : launch(&k_update_seg<NC, int32_t, false>, part);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_seg_reduce<int32_t>, dim3((unsigned)std::min<uint64_t>((cells + 255) / 256, 8192)),
-                               dim3(256), 0, s, reinterpret_cast<const int32_t *>(a.scratch), sg.chunks, cells,
+            hipLaunchKernelGGL(k_seg_reduce<int32_t>, dim3((unsigned)std::min<uint64_t>((cells + 63) / 64, 8192)),
+                               dim3(kBlock), 0, s, reinterpret_cast<const int32_t *>(a.scratch), sg.chunks, cells,
                                a.sketch);
         } else {
             if (!fits(sg.chunks, 8)) return fail(CS_EINVAL, "update scratch buffer too small for d * m int64 partial sums");
             int64_t *part = reinterpret_cast<int64_t *>(a.scratch);
             st = e1 ? launch(&k_update_seg<NC, int64_t, true>, part) : launch(&k_update_seg<NC, int64_t, false>, part);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_seg_reduce<int64_t>, dim3((unsigned)std::min<uint64_t>((cells + 255) / 256, 8192)),
-                               dim3(256), 0, s, reinterpret_cast<const int64_t *>(a.scratch), sg.chunks, cells,
+            hipLaunchKernelGGL(k_seg_reduce<int64_t>, dim3((unsigned)std::min<uint64_t>((cells + 63) / 64, 8192)),
+                               dim3(kBlock), 0, s, reinterpret_cast<const int64_t *>(a.scratch), sg.chunks, cells,
                                a.sketch);
         }
         CSK_HIP(hipGetLastError());
@@ -1861,50 +1900,59 @@ cs_status launch_nc(const UpdateArgs &a, int strategy, int grid_blocks, hipStrea
 
 }  // namespace
 
-// At least this many tuples per chunk: a small update runs on fewer workgroups rather
-// than paying each one's counter initialisation and partial-sum traffic.
-constexpr uint64_t kSegTuplesPerChunk = 32768;
-
-int32_t chunks_for_n(int32_t C, uint64_t n)
+// Repetitions per segment and tuple chunks of a segmented update of n tuples: the pair
+// with the smallest modelled time.  Every workgroup pays a fixed part (launch, clearing and
+// storing its counters) and hashes its chunk once per repetition it holds; the reduction
+// reads every chunk's partial sums.  Splitting further shortens the hashing and lengthens
+// the rest, so the best split moves with n: a fixed 32768 tuples per chunk left 10^5
+// tuples into 5 x 1024 counters on 4 of 256 CUs (55 us; 9 us balanced) and 20001 tuples
+// into 9 x 2^16 counters on 9 of them.
+static SegGeom balanced_geometry(uint32_t m, int32_t d, uint32_t max_r, int elem, size_t scratch_bytes, uint64_t n)
 {
-    const uint64_t by_n = n / kSegTuplesPerChunk + (n % kSegTuplesPerChunk != 0);  // no wrap at n = 2^64 - 1
-    return (int32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)C, by_n));
+    const uint64_t cells = (uint64_t)d * m;
+    const uint64_t cap = std::min<uint64_t>(256, std::max<uint64_t>(1, scratch_bytes / (cells * elem)));
+    const int32_t q_max = m <= max_r ? (int32_t)std::min<uint64_t>(d, max_r / m) : 1;
+    SegGeom best{};
+    double best_us = 0.0;
+    int32_t last_segments = 0;
+    for (int32_t q = q_max; q >= 1; q = q > 1 ? (q + 1) / 2 : 0) {
+        SegGeom g{};
+        g.R = m <= max_r ? (uint32_t)q * m : max_r;
+        g.segments = (int32_t)((cells + g.R - 1) / g.R);
+        if (g.segments == last_segments) continue;
+        last_segments = g.segments;
+        const double lds = (double)g.R * elem / 131072.0;       // share of 128 KB
+        const double fixed = 1.5 + 1.5 * lds;                    // us
+        const int per_round = lds <= 0.6 ? 512 : 256;            // two workgroups per CU when two fit
+        for (int32_t c = 1; c <= (int32_t)cap; c += c < 8 ? 1 : c / 8) {
+            // whole rounds: also the largest count that fits the rounds c needs
+            for (int32_t C : {c, (int32_t)std::min<uint64_t>(cap, 256 * ((g.segments * (uint64_t)c + 255) / 256) / g.segments)}) {
+                const uint64_t wgs = (uint64_t)g.segments * C;
+                const double iters = (double)((n / C >> 10) + 1);  // of 1024 tuples
+                const double us = fixed * ((wgs + per_round - 1) / per_round) +
+                                  0.3 * iters * q * ((wgs + 255) / 256) + (double)C * cells * elem * 2 / 4e6 +
+                                  0.03 * C;
+                if (best.chunks == 0 || us < best_us) {
+                    best = g;
+                    best.chunks = C;
+                    best_us = us;
+                }
+            }
+        }
+    }
+    return best;
 }
 
 SegGeom seg_geometry(uint32_t m, int32_t d, bool narrow, size_t scratch_bytes, uint64_t n)
 {
-    SegGeom g{};
-    // LDS per block: 128 KB of counters (one 1024-thread block per CU)
-    g.R = narrow ? (1u << 15) : (1u << 14);
-    const uint64_t cells = (uint64_t)d * m;
-    if (m <= g.R) g.R = (g.R / m) * m;  // whole repetitions per segment
-    g.segments = (int32_t)((cells + g.R - 1) / g.R);
-    // one 128 KB workgroup per CU: a whole number of rounds over the 256 CUs (two
-    // rounds when there are few segments), bounded by the scratch buffer
-    int32_t C = 512 / g.segments;
-    if (C < 1) C = 1;
-    const uint64_t cap = std::max<uint64_t>(1, scratch_bytes / (cells * (narrow ? 4 : 8)));
-    if ((uint64_t)C > cap) C = (int32_t)cap;
-    if (C > 64) C = 64;
-    g.chunks = chunks_for_n(C, n);
-    return g;
+    // LDS per block: at most 128 KB of counters (one 1024-thread block per CU)
+    return balanced_geometry(m, d, narrow ? (1u << 15) : (1u << 14), narrow ? 4 : 8, scratch_bytes, n);
 }
 
 SegGeom seg16_geometry(uint32_t m, int32_t d, size_t scratch_bytes, uint64_t n)
 {
-    SegGeom g{};
-    g.R = 1u << 16;  // 16-bit counters in 128 KB of LDS
-    const uint64_t cells = (uint64_t)d * m;
-    if (m <= g.R) g.R = (g.R / m) * m;
-    g.segments = (int32_t)((cells + g.R - 1) / g.R);
-    // one round of 128 KB workgroups over the 256 CUs: fewer partial sums to reduce
-    int32_t C = 256 / g.segments;
-    if (C < 1) C = 1;
-    const uint64_t cap = std::max<uint64_t>(1, scratch_bytes / (cells * 2));
-    if ((uint64_t)C > cap) C = (int32_t)cap;
-    if (C > 64) C = 64;
-    g.chunks = chunks_for_n(C, n);
-    return g;
+    // 16-bit counters in 128 KB of LDS
+    return balanced_geometry(m, d, 1u << 16, 2, scratch_bytes, n);
 }
 
 // Records (2 bytes per tuple and repetition, runs padded), run starts (2 bytes per range
