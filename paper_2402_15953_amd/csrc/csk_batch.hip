@@ -193,13 +193,13 @@ __device__ void run_segment(const BItem &I, uint32_t seg, uint64_t begin, uint64
 // 128 KB, whole repetitions when m <= 2^16.  Keys of the next tuple are loaded while
 // this one is hashed, and each LDS add's returned value is checked one add later.
 // At the end, each non-zero counter is added into the sketch with one global atomic.
-// Whole repetitions in the segment, one or two key columns: a thread takes quads of four
-// consecutive tuples (loaded at an index clamped into the range, so no bounds branches),
-// and per repetition hashes the quad in one straight-line block, issues its four LDS adds
-// and checks the returned words right away (the other wavefronts cover the LDS latency).
-// E1 (every column in exactly one join, m a power of two): coefficients in registers and
-// the canonical reduction skipped unless a hash's flag asks for it.  The range's last
-// (end - begin) mod 4 tuples go one per thread.
+// Whole repetitions in the segment: a thread takes groups of consecutive tuples (four of one
+// or two key columns, two of three to five; loaded at an index clamped into the range, so
+// no bounds branches), and per repetition hashes the group in one straight-line block,
+// issues its LDS adds and checks the returned words right away (the other wavefronts cover
+// the LDS latency).  E1 (every column in exactly one join, m a power of two): the
+// leading-bits hash, one column's coefficients in scalar registers at a time, exact where
+// its flags ask for it.  The range's last tuples, fewer than a group, go one per thread.
 // Values the whole workgroup shares, moved into scalar registers (the compiler cannot
 // tell that fields read from the task table are uniform).
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -233,9 +233,10 @@ __device__ __forceinline__ void seg16_quads(const BItem &I, uint64_t begin_, uin
     const int t0 = (int)uni((uint32_t)t0_), t1 = (int)uni((uint32_t)t1_);
     unsigned long long *sk = uni(sk_);
     const DevPlan plan = I.plan;
-    const uint64_t len = end - begin, nq = len >> 2;
+    constexpr int G = NC <= 2 ? 4 : 2;
+    const uint64_t len = end - begin, nq = len / G;
     struct Quad {
-        uint32_t x[4][NC];
+        uint32_t x[G][NC];
         uint32_t wneg;  // bit g: tuple g's Delta is -1 (16-bit segments take Deltas +-1 only)
     };
     struct Pend {
@@ -254,10 +255,10 @@ __device__ __forceinline__ void seg16_quads(const BItem &I, uint64_t begin_, uin
         for (int c = 0; c < NC; ++c) x[c] = keys[i * NC + c];
     };
     auto load_quad = [&](uint64_t q, Quad &Q) {
-        const uint64_t i0 = begin + 4 * q;
+        const uint64_t i0 = begin + G * q;
         Q.wneg = 0;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < G; ++g) {
             load1(i0 + g, Q.x[g]);
             if (weights) Q.wneg |= (uint32_t)((uint64_t)weights[i0 + g] >> 63) << g;
         }
@@ -283,18 +284,23 @@ __device__ __forceinline__ void seg16_quads(const BItem &I, uint64_t begin_, uin
         const uint32_t row = (uint32_t)((uint64_t)t * m - cell0);
         uint32_t j[K], neg[K];
         if constexpr (E1) {
-            CoefE1<NC> C;
-            C.load(cf, m);
             HashFlag flag;
 #pragma unroll
-            for (int g = 0; g < K; ++g) C.bin_neg_fast(Q.x[g], j[g], neg[g], flag);
-            if (C.bin_near(flag, 0xFFFFFFFFu)) {
+            for (int c = 0; c < NC; ++c) {
+                CoefE1<1> C;
+                C.load(cf + 6 * c, m);
 #pragma unroll
-                for (int g = 0; g < K; ++g) j[g] = C.bin(Q.x[g]);
+                for (int g = 0; g < K; ++g) {
+                    const uint32_t xc[1] = {Q.x[g][c]};
+                    uint32_t jc, nc;
+                    C.bin_neg_fast(xc, jc, nc, flag);
+                    j[g] = c ? j[g] + jc : jc;
+                    neg[g] = c ? neg[g] ^ nc : nc;
+                }
             }
-            if (C.sign_near(flag, 0xFFFFFFFFu)) {
+            if (CoefE1<1>::bin_near(flag, m, 0xFFFFFFFFu) || CoefE1<1>::sign_near(flag, 0xFFFFFFFFu)) {
 #pragma unroll
-                for (int g = 0; g < K; ++g) neg[g] = C.neg(Q.x[g]);
+                for (int g = 0; g < K; ++g) hash_rep<NC>((const uint64_t *)cf, plan, Q.x[g], j[g], neg[g]);
             }
         } else {
 #pragma unroll
@@ -312,16 +318,16 @@ __device__ __forceinline__ void seg16_quads(const BItem &I, uint64_t begin_, uin
         load_quad(q < last ? q : last, A);
         while (q < nq) {
             load_quad(q + kBBlock < last ? q + kBBlock : last, B);
-            for (int t = t0; t <= t1; ++t) run(A, std::integral_constant<int, 4>{}, t);
+            for (int t = t0; t <= t1; ++t) run(A, std::integral_constant<int, G>{}, t);
             q += kBBlock;
             if (q >= nq) break;
             load_quad(q + kBBlock < last ? q + kBBlock : last, A);
-            for (int t = t0; t <= t1; ++t) run(B, std::integral_constant<int, 4>{}, t);
+            for (int t = t0; t <= t1; ++t) run(B, std::integral_constant<int, G>{}, t);
             q += kBBlock;
         }
     }
-    if ((uint64_t)threadIdx.x < (len & 3)) {
-        const uint64_t i = begin + 4 * nq + threadIdx.x;
+    if ((uint64_t)threadIdx.x < len % G) {
+        const uint64_t i = begin + G * nq + threadIdx.x;
         Quad Q;
         load1(i, Q.x[0]);
         Q.wneg = weights ? (uint32_t)((uint64_t)weights[i] >> 63) : 0u;
@@ -346,7 +352,7 @@ __device__ void run_segment16(const BItem &I, uint32_t seg, uint64_t begin, uint
     uint32_t p_old = kBias16 * 0x10001u, p_inc = 0;  // before the first add: in range
     uint64_t p_g = 0;
     uint32_t *p_w = s_w;
-    if constexpr (NC <= 2) {
+    if constexpr (NC <= 5) {
         if (whole) {
             if (I.e1) seg16_quads<NC, true>(I, begin, end, cell0, t0, t1, s_w, sk);
             else seg16_quads<NC, false>(I, begin, end, cell0, t0, t1, s_w, sk);
@@ -527,31 +533,57 @@ cs_status make_item(const cs_update_item &it, BItem &I, ItemInfo &info)
 
 // The fixed rule: global atomics where aggregation cannot pay (a few microseconds of
 // them at most; a segment task's fixed cost is zeroing and flushing its LDS counters),
-// else LDS segments over tuple chunks of at most 2^18 (chunk_log2 -1: balanced chunks).
+// else LDS segments (chunk_log2 -1: balanced by add_tasks).
 void rule_choice(const BItem &I, int *kind, int *chunk_log2)
 {
     const uint64_t cells = (uint64_t)I.d * I.m;
     const uint64_t tuple_reps = I.n * I.d;
     if (tuple_reps < 65536 || tuple_reps < cells / 4) {
         *kind = 0;
-        *chunk_log2 = 16;
     } else {
         *kind = 1;
-        *chunk_log2 = -1;
     }
+    *chunk_log2 = -1;
 }
 
-// Tasks of item idx with the given kind and tuple chunk (2^chunk_log2, or for -1 the
-// balanced chunks of at most 2^18).
-void add_tasks(int idx, const ItemInfo &info, int kind, int chunk_log2, std::vector<BTask> &bt,
+// Modelled work of an item: Horner steps over its tuples and repetitions, three more per
+// tuple and repetition for the add.
+double item_cost(const ItemInfo &info) { return (double)info.I.n * info.I.d * (info.steps + 3); }
+
+// A segment task should not exceed its share of the batch: a workgroup's quarter of the
+// total, so that largest-first order ends level.  One task of 2^18 tuples and every
+// repetition of a small sketch is 2.5 ms of one CU, 20 times the rest of a batch of 60
+// queries.  At least about 5 us of work, the fixed cost of clearing and flushing.
+double task_share(double total, int n_cu) { return std::max(total / (4.0 * n_cu), 1.2e5); }
+
+// Tasks of item idx with the given kind and tuple chunk (2^chunk_log2; -1: segments of as
+// many repetitions, over as few chunks of at most 2^18 tuples, as `share` allows.
+// Repetitions are split first: that costs only reads of the keys, where every further
+// chunk flushes the segment's counters once more).
+void add_tasks(int idx, ItemInfo &info, int kind, int chunk_log2, double share, std::vector<BTask> &bt,
                std::vector<double> &cost, uint64_t &n_atomic, uint64_t &n_segment, uint64_t &n_sort)
 {
-    const BItem &I = info.I;
+    BItem &I = info.I;
     const uint64_t n = I.n;
     const uint64_t cells = (uint64_t)I.d * I.m;
     uint64_t chunk;
     if (chunk_log2 < 0) {
-        const uint64_t C = (n + (1u << 18) - 1) >> 18;
+        uint64_t C = (n + (1u << 18) - 1) >> 18;
+        if (kind == 1) {
+            const double per_rep = (double)n * (info.steps + 3);
+            double task = per_rep;
+            if (I.R >= I.m) {
+                const int q_max = std::min<int>(I.d, (int)(I.R / I.m));
+                const int q = (int)std::max(1.0, std::min((double)q_max, share / per_rep));
+                const int segs = (I.d + q - 1) / q;
+                I.R = (uint32_t)((I.d + segs - 1) / segs) * I.m;
+                task = per_rep * ((I.d + segs - 1) / segs);
+            }
+            C = std::max<uint64_t>(C, (uint64_t)std::min((double)((n + 4095) / 4096), task / share + 0.5));
+        } else {
+            const double task = (double)n * I.d * (info.steps + 40);
+            C = std::max<uint64_t>(C, (uint64_t)std::min((double)((n + 1023) / 1024), task / share + 0.5));
+        }
         chunk = (n + C - 1) / C;
     } else {
         const uint64_t C = (n + (1ull << chunk_log2) - 1) >> chunk_log2;
@@ -619,10 +651,12 @@ cs_status upload_tables(BatchState &B, const std::vector<BItem> &bi, const std::
 
 cs_status plan_batch(BatchState &B, const cs_update_item *items, int32_t n_items, hipStream_t s)
 {
+    std::vector<ItemInfo> infos;
     std::vector<BItem> bi;
     std::vector<BTask> bt;
     std::vector<double> cost;
     B.tasks_atomic = B.tasks_segment = B.tasks_sort = 0;
+    double total = 0.0;
     for (int32_t i = 0; i < n_items; ++i) {
         const cs_update_item &it = items[i];
         if (!it.sketch) return fail(CS_EINVAL, "batch item without handle");
@@ -636,12 +670,20 @@ cs_status plan_batch(BatchState &B, const cs_update_item *items, int32_t n_items
         ItemInfo info;
         cs_status st = make_item(it, I, info);
         if (st != CS_OK) return st;
+        infos.push_back(info);
+        total += item_cost(info);
+    }
+    int n_cu = 256;
+    if (!infos.empty()) CSK_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, B.device));
+    const double share = task_share(total, n_cu);
+    for (ItemInfo &info : infos) {
+        const BItem &I = info.I;
         int kind, chunk_log2;
-        if (!tune_lookup_batch(h.device, h.m, (int)h.d, I.n_cols, info.e1, info.unit, it.n, &kind, &chunk_log2))
+        if (!tune_lookup_batch(B.device, I.m, I.d, I.n_cols, info.e1, info.unit, I.n, &kind, &chunk_log2))
             rule_choice(I, &kind, &chunk_log2);
-        const int idx = (int)bi.size();
-        bi.push_back(I);
-        add_tasks(idx, info, kind, chunk_log2, bt, cost, B.tasks_atomic, B.tasks_segment, B.tasks_sort);
+        add_tasks((int)bi.size(), info, kind, chunk_log2, share, bt, cost, B.tasks_atomic, B.tasks_segment,
+                  B.tasks_sort);
+        bi.push_back(info.I);
     }
     return upload_tables(B, bi, bt, cost, s);
 }
@@ -844,6 +886,11 @@ cs_status cs_tune_batch_update(cs_batch *b, const cs_update_item *items, int32_t
     const int cands[][2] = {{0, 16}, {-1, -1}, {2, 16}, {1, 14}, {1, 16}, {1, 18}, {1, 20}};
     const int n_cand = (int)(sizeof(cands) / sizeof(cands[0]));
     cs_status st = CS_OK;
+    int n_cu = 256;
+    if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        cleanup();
+        return fail(CS_EDEVICE, "batch tuning device");
+    }
     for (auto &kv : classes) {
         const std::vector<int> &members = kv.second;
         size_t cells = 0;
@@ -863,15 +910,17 @@ cs_status cs_tune_batch_update(cs_batch *b, const cs_update_item *items, int32_t
                 std::vector<BTask> bt;
                 std::vector<double> cost;
                 uint64_t na = 0, ns = 0, nr = 0;
+                double total = 0.0;
+                for (int i : members) total += item_cost(info[i]) * copies;
+                const double share = task_share(total, n_cu);
                 for (int c = 0; c < copies; ++c)
                     for (size_t j = 0; j < members.size(); ++j) {
                         ItemInfo ii = info[members[j]];
                         ii.I.sketch = dst + (size_t)c * cells + off[j];
                         int kind = cands[ci][0], chunk = cands[ci][1];
                         if (kind < 0) rule_choice(ii.I, &kind, &chunk);
-                        const int idx = (int)bi.size();
+                        add_tasks((int)bi.size(), ii, kind, chunk, share, bt, cost, na, ns, nr);
                         bi.push_back(ii.I);
-                        add_tasks(idx, ii, kind, chunk, bt, cost, na, ns, nr);
                     }
                 return upload_tables(T, bi, bt, cost, s);
             };

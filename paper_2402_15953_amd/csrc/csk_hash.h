@@ -303,11 +303,12 @@ struct CoefE1 {
     }
     // Whether a bin (a sign) of the group has to be taken again with bin() (neg()); `canon`
     // (0xFFFFFFFF outside tests) lowers the limits.
-    __device__ __forceinline__ bool bin_near(const HashFlag &f, uint32_t canon) const
+    __device__ __forceinline__ bool bin_near(const HashFlag &f, uint32_t canon) const { return bin_near(f, m, canon); }
+    static __device__ __forceinline__ bool bin_near(const HashFlag &f, uint32_t m, uint32_t canon)
     {
         return f.bin >= min(canon, 0u - 2u * m - 2u);
     }
-    __device__ __forceinline__ bool sign_near(const HashFlag &f, uint32_t canon) const
+    static __device__ __forceinline__ bool sign_near(const HashFlag &f, uint32_t canon)
     {
         return f.sign >= min(canon, 0u - 16u * 24u);
     }
