@@ -36,7 +36,6 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kSegBlock = 1024;
 constexpr uint32_t kSeg16Words = 1u << 15;  // 128 KB: 2^16 16-bit counters
-constexpr int kSeg16Group = 4;              // tuples hashed together by one thread
 
 template <int NC>
 __global__ __launch_bounds__(kBlock) void k_update_global(const uint32_t *__restrict__ keys,
@@ -348,6 +347,24 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg_compact(const uint32_t
     for (uint32_t e = threadIdx.x; e < R; e += kSegBlock) out[e] = s_c[e];
 }
 
+// The 16-bit counters' start value and their partial sums, four words at a time where the
+// word count and the destination allow it.
+__device__ __forceinline__ void fill16(uint32_t *s_w, uint32_t words)
+{
+    constexpr uint32_t b = (kBias16 << 16) | kBias16;
+    for (uint32_t e = threadIdx.x; e < words / 4; e += kSegBlock) reinterpret_cast<uint4 *>(s_w)[e] = make_uint4(b, b, b, b);
+    if (threadIdx.x < (words & 3)) s_w[(words & ~3u) + threadIdx.x] = b;
+}
+__device__ __forceinline__ void store16(uint32_t *out, const uint32_t *s_w, uint32_t words)
+{
+    if ((words & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+        for (uint32_t e = threadIdx.x; e < words / 4; e += kSegBlock)
+            reinterpret_cast<uint4 *>(out)[e] = reinterpret_cast<const uint4 *>(s_w)[e];
+    } else {
+        for (uint32_t e = threadIdx.x; e < words; e += kSegBlock) out[e] = s_w[e];
+    }
+}
+
 template <int NC, bool E1, bool HW>
 __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__restrict__ keys,
                                                             const int64_t *__restrict__ weights, uint64_t n,
@@ -359,7 +376,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
 {
     // [R / 2] words, two counters each (R <= 2^16); a fixed array, so that its LDS
     // address is a constant the compiler folds into the address arithmetic
-    __shared__ uint32_t s_w[kSeg16Words];
+    __shared__ __align__(16) uint32_t s_w[kSeg16Words];
     const uint64_t cells = (uint64_t)d * m;
     const SegTile wg = seg_tile();
     const uint64_t cell0 = (uint64_t)wg.seg * R;
@@ -367,7 +384,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
     const uint32_t span = (uint32_t)(cell1 - cell0);  // even: R is even (so is cells)
     const int t0 = (int)(cell0 / m);
     const int t1 = (int)((cell1 - 1) / m);
-    for (uint32_t e = threadIdx.x; e < span / 2; e += kSegBlock) s_w[e] = (kBias16 << 16) | kBias16;
+    fill16(s_w, span / 2);
     __syncthreads();
     const uint64_t begin = (uint64_t)wg.chunk * chunk;
     const uint64_t end = begin + chunk < n ? begin + chunk : n;
@@ -377,14 +394,15 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
         if constexpr (E1) K.load(cf, m);
         const uint32_t row = (uint32_t)((uint64_t)t * m - cell0);
         unsigned long long *srow = sketch + (uint64_t)t * m;
-        // Tuples go in groups of kSeg16Group: all are hashed in one straight-line block
+        // Tuples go in groups of G: all are hashed in one straight-line block
         // (independent chains for the scheduler, one test of the rare full-reduction
         // flag), their LDS adds are issued, and only then are the words the previous
         // group's adds returned checked; the next group's keys are in flight meanwhile.
         // Neither the LDS latency nor the loads stall the wavefront.  A thread has at most
-        // 2 * kSeg16Group adds whose result it has not checked: with 1024 threads a half
-        // stays within 2^15 +- (2^14 + 8 * 1024).
-        constexpr int G = kSeg16Group;
+        // 2 G adds whose result it has not checked: with 1024 threads a half stays within
+        // 2^15 +- (2^14 + 4 * 1024).  Groups of four spilled 75 registers at four columns
+        // (1.5 * 10^6 tuples, m = 2^16, d = 5: 70 us; 45 us with groups of two).
+        constexpr int G = NC <= 5 ? 2 : 1;  // more tuples of three and more columns spill registers
         struct Pend {
             uint32_t old, inc, j;  // word before the add, the increment, the bucket
             uint32_t *w;
@@ -484,7 +502,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16(const uint32_t *__re
     __syncthreads();
     // partial sums leave as the biased 16-bit pairs: [chunk][cells / 2] words
     uint32_t *out = partial + (size_t)wg.chunk * (cells >> 1) + (cell0 >> 1);
-    for (uint32_t e = threadIdx.x; e < span / 2; e += kSegBlock) out[e] = s_w[e];
+    store16(out, s_w, span / 2);
 }
 
 // The same 16-bit update for relations of one or two key columns when one repetition
@@ -511,11 +529,11 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
         chunk = ((n + gridDim.x - 1) / gridDim.x + 3) & ~(uint64_t)3;
     }
     static_assert(NC == 1 || NC == 2, "quads of one- and two-column tuples");
-    __shared__ uint32_t s_w[kSeg16Words];
+    __shared__ __align__(16) uint32_t s_w[kSeg16Words];
     const uint64_t cells = (uint64_t)gridDim.y * m;  // one segment per repetition
     const SegTile wg = seg_tile();
     const int t = (int)wg.seg;
-    for (uint32_t e = threadIdx.x; e < m / 2; e += kSegBlock) s_w[e] = (kBias16 << 16) | kBias16;
+    fill16(s_w, m / 2);
     __syncthreads();
     const uint64_t begin = (uint64_t)wg.chunk * chunk;  // chunk is a multiple of 4
     const uint64_t end = begin + chunk < n ? begin + chunk : n;
@@ -663,7 +681,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16q(const uint32_t *__r
     }
     __syncthreads();
     uint32_t *out = partial + (size_t)wg.chunk * (cells >> 1) + (((uint64_t)t * m) >> 1);
-    for (uint32_t e = threadIdx.x; e < m / 2; e += kSegBlock) out[e] = s_w[e];
+    store16(out, s_w, m / 2);
 }
 
 // 16-bit counters beyond 2^16 buckets (m a power of two, one or two key columns, each in
@@ -685,7 +703,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
     static_assert(NC == 1 || NC == 2, "one- and two-column relations");
     constexpr uint32_t kRange = 1u << 16;
     constexpr int kWavesPB = kSegBlock / 64;
-    __shared__ uint32_t s_w[kSeg16Words];
+    __shared__ __align__(16) uint32_t s_w[kSeg16Words];
     __shared__ uint32_t s_qx[kWavesPB][NC][kQCap];
     __shared__ uint32_t s_ql[kWavesPB][kQCap];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -694,7 +712,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
     const uint64_t cell0 = (uint64_t)wg.seg * kRange;
     const int t = (int)(cell0 / m);
     const uint32_t off = (uint32_t)(cell0 - (uint64_t)t * m);  // first bucket of the range
-    for (uint32_t e = threadIdx.x; e < kSeg16Words; e += kSegBlock) s_w[e] = (kBias16 << 16) | kBias16;
+    fill16(s_w, kSeg16Words);
     __syncthreads();
     CoefE1<NC> K;
     K.load(coef + (size_t)t * cpr, m);
@@ -757,7 +775,7 @@ __global__ __launch_bounds__(kSegBlock) void k_update_seg16c(const uint32_t *__r
     if (count > 0) drain(count);
     __syncthreads();
     uint32_t *out = partial + (size_t)wg.chunk * (cells >> 1) + (cell0 >> 1);
-    for (uint32_t e = threadIdx.x; e < kSeg16Words; e += kSegBlock) out[e] = s_w[e];
+    store16(out, s_w, kSeg16Words);
 }
 
 // Compaction pass of a filtered update with 16-bit counters: the keys (and Deltas) of the
