@@ -227,10 +227,10 @@ struct RepDesc {
     int32_t S;             // row length 2^S of the two-pass transforms of this length
     uint32_t m;            // buckets (log2m is exact only for powers of two)
     uint32_t conj;         // SPECTRAL: relations taken conjugated
-    int32_t vec_base;      // SPECTRAL: first packed vector of query q in its group's buffer
     int32_t nb;            // blocks of this repetition's reductions
-    int32_t sk_base;       // first sketch (k * d + t order) of query q in the SkDesc table
-    int32_t mod_vec_base;  // modular pass: first vector of query q in its group's buffer
+    // SPECTRAL, relation k's sketch of this repetition: packed fp64 vector times 2 plus the
+    // half it is, and vector of the modular pass, in its group's buffers
+    int32_t zv[kMaxRel], mv[kMaxRel];
     int64_t spec_off;      // fp64 spectral partials, (2 + r) doubles per block
     int64_t dot_off;       // DOT partials, 4 words per block (int128 sum, fp64 sum, fp64 sum of |terms|)
     int64_t mod_off;       // modular partials (per prime plane)
@@ -239,10 +239,13 @@ struct RepDesc {
 struct QDesc {
     int32_t plan, r, d, log2m, rep_base, nb;
     uint32_t m;
-    // where this query's partials start (its first sketch's norm pair, its first
-    // repetition's spectral sums and residues): the finalize reads them without going
+    // where this query's partials start (its first repetition's spectral sums and
+    // residues, each relation's first norm pair): the finalize reads them without going
     // through the repetition and sketch descriptors first
-    int64_t norm_off0, spec_off0, mod_off0;
+    int64_t spec_off0, mod_off0;
+    int64_t norm_off[kMaxRel];
+    // odd d: norm pair of the sketch packed with relation k's last one (-1: none)
+    int64_t pair_off[kMaxRel];
 };
 
 // ---------------------------------------------------------------- kernels
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(kThreads) void k_dot(const RepDesc *__restrict__ re
 }
 
 // fp64 spectral product-reduce for repetitions idx[blockIdx.y] of one m-group.
-// Sketch s = k * d + t of a query is half (s & 1) of packed vector vec_base + s / 2.
+// Relation k's sketch of the repetition is half zv & 1 of packed vector zv / 2.
 // partials: sum Re(term), sum |Re|+|Im| of terms, max |C_k| per relation.
 __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict__ Z,
                                                        const RepDesc *__restrict__ reps,
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
 {
     __shared__ double sh[kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
-    const RepDesc D = reps[idx[item]];
+    const RepDesc &D = reps[idx[item]];
     const int blk = (int)(blockIdx.x - prefix[item]);
     const int log2m = D.log2m, S = D.S;
     const uint32_t m = 1u << log2m;
@@ -350,8 +353,8 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
 #pragma unroll
         for (int k = 0; k < kMaxRel; ++k) {
             if (k < r) {
-                const int sidx = k * D.d + D.t;
-                const double2 *zv = Z + (size_t)(D.vec_base + (sidx >> 1)) * m;
+                const int sidx = D.zv[k];
+                const double2 *zv = Z + (size_t)(sidx >> 1) * m;
                 const double2 a = zv[pos], b = zv[npos];
                 double cr, ci;
                 if ((sidx & 1) == 0) {
@@ -383,8 +386,8 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
     }
 }
 
-// Modular spectral product-reduce.  Buffer [K][vpp][m]; query q's sketch k * d + t is
-// vector mod_vec_base + k * d + t.  partials [K][plane] at mod_off.
+// Modular spectral product-reduce.  Buffer [K][vpp][m]; relation k's sketch of the
+// repetition is vector mv[k].  partials [K][plane] at mod_off.
 __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restrict__ N, int vpp,
                                                        const RepDesc *__restrict__ reps,
                                                        const int32_t *__restrict__ idx,
@@ -395,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restric
     __shared__ uint32_t sh[kThreads];
     const int item = find_item(prefix, n_items, blockIdx.x);
     if (kp && (int)blockIdx.y >= kp[idx[item]]) return;  // prime not needed by this repetition
-    const RepDesc D = reps[idx[item]];
+    const RepDesc &D = reps[idx[item]];
     const int blk = (int)(blockIdx.x - prefix[item]);
     const int pi = blockIdx.y;
     const PrimeDev P = primes[pi];
@@ -419,7 +422,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restric
             prod[u] = P.one;
         }
         for (int k = 0; k < D.r; ++k) {
-            const uint32_t *v = base + (size_t)(D.mod_vec_base + k * D.d + D.t) * m;
+            const uint32_t *v = base + (size_t)D.mv[k] * m;
             const bool cj = (D.conj >> k) & 1u;
             uint32_t val[U];
 #pragma unroll
@@ -572,6 +575,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
     // stage 1: per-block partials of this query reduced once, one wavefront per
     // sketch (norms) or repetition (spectral sums), in a fixed order
     __shared__ double s_q2[kMaxRel * kMaxD], s_l1[kMaxRel * kMaxD];
+    __shared__ double s_p2[kMaxRel];  // odd d: squared norm of the last sketch's packed partner
     __shared__ double s_sum[kMaxD], s_sabs[kMaxD], s_mx[kMaxD * kMaxRel];
     __shared__ double s_stage[kStage];  // scratch of the bound computation
     __shared__ uint32_t s_res[kMaxD * kMaxPrimes], s_dig[kMaxD * kMaxPrimes];
@@ -588,11 +592,11 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
         // a shuffle tree of depth 6 adds them, in a fixed order.
         const int nb = Q.nb;
         const int n_sk = Q.r * Q.d;
-        const double *nrm = a.norms + Q.norm_off0 * 2;
         for (int o = wv; o < n_sk; o += kWaves) {
             double q2 = 0.0, l1 = 0.0;
             if (lane < nb) {
-                const double *p = nrm + ((int64_t)o * nb + lane) * 2;
+                const int k = o / Q.d;
+                const double *p = a.norms + (a.qs[blockIdx.x].norm_off[k] + (int64_t)(o - k * Q.d) * nb + lane) * 2;
                 q2 = p[0];
                 l1 = p[1];
             }
@@ -601,6 +605,13 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             if (lane == 0) {
                 s_q2[o] = q2;
                 s_l1[o] = l1;
+            }
+        }
+        if (plan == CS_PLAN_SPECTRAL && (Q.d & 1)) {
+            for (int k = wv; k < Q.r; k += kWaves) {
+                const int64_t po = a.qs[blockIdx.x].pair_off[k];
+                const double q2 = warp_sum(po >= 0 && lane < nb ? a.norms[(po + lane) * 2] : 0.0);
+                if (lane == 0) s_p2[k] = q2;
             }
         }
         if (plan == CS_PLAN_SPECTRAL) {
@@ -703,13 +714,9 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                     double *e = s_stage + t * 3 * kMaxRel;
                     double *N = e + kMaxRel;
                     double *M = N + kMaxRel;
-                    const int n_sk = Q.r * Q.d;
                     for (int k = 0; k < Q.r; ++k) {
-                        // packed partner: sketch index s ^ 1 within the query
-                        const int sidx = k * Q.d + t;
-                        double z2 = s2(k);
-                        const int ps = sidx ^ 1;
-                        if (ps < n_sk) z2 += s_q2[ps] * up;
+                        // packed partner: repetition t ^ 1 of the relation, or the last one's
+                        const double z2 = s2(k) + ((t ^ 1) < Q.d ? s_q2[k * Q.d + (t ^ 1)] : s_p2[k]) * up;
                         e[k] = kappa * sm * sqrt(z2) * (1.0 + 4.0 * u);
                         N[k] = sm * sqrt(s2(k)) * (1.0 + 4.0 * u) + e[k];
                         M[k] = mx[k] * (1.0 + 4.0 * u) + e[k];
@@ -1224,7 +1231,7 @@ struct Carve {
 }  // namespace
 
 cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t *outs, const cs_reps_t *reps_out,
-                         EstimateWork &ws, cs_estimate_t *async_out)
+                         EstimateWork &ws, cs_estimate_t *async_out, bool shared)
 {
     if (nq <= 0) return CS_OK;
     const int device = hs[0]->device;
@@ -1254,10 +1261,24 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         std::vector<int> queries;
         std::vector<int32_t> rep_idx;
         std::vector<const int64_t *> re, im;
-        std::vector<const int64_t *> mod_ptrs;  // every sketch, (query, relation, repetition) order
-        std::vector<int32_t> rep_of;            // repetition of each of those sketches
+        std::vector<const int64_t *> mod_ptrs;  // every sketch once
         size_t z_off = 0;
     };
+    // The d sketches of one relation, normed and transformed once however many queries of
+    // the call read them (with `shared`: the sub-queries of one base query do, 30 relation
+    // sketches of a 5-chain's ten sub-chains being 11 distinct ones).  Repetitions 2i and
+    // 2i + 1 are packed into one complex vector; the last ones of an odd d pair up over the
+    // relations of the query that brought them.
+    struct RelBlock {
+        const int64_t *base;
+        const Group *group;          // its transforms' group (null: norms only)
+        int64_t norm_off;
+        int32_t vec0 = 0, mod0 = 0;  // first packed vector, first vector of the modular pass
+        int32_t last = 0;            // odd d: zv of the last sketch
+        int64_t pair_off = -1;       // odd d: norm pair of its partner
+    };
+    std::vector<RelBlock> blocks;
+    std::vector<int> q_blocks;  // the current query's blocks
     std::map<int, Group> groups;
     std::vector<int> general_q;
     int64_t norm_off = 0, spec_off = 0, dot_off = 0, mod_off = 0;
@@ -1273,16 +1294,38 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         Q.m = h.m;
         Q.rep_base = (int32_t)rd.size();
         Q.nb = nb;
-        Q.norm_off0 = norm_off;
         Q.spec_off0 = spec_off;
         Q.mod_off0 = mod_off;
-        const int sk_base = (int)sd.size();
         const size_t m = h.m;
+        Group *G = nullptr;
+        if (Q.plan == CS_PLAN_SPECTRAL) {
+            G = &groups[L];
+            G->log2m = L;
+            G->S = split_of(L);
+            G->queries.push_back(q);
+        }
+        q_blocks.clear();
         if (Q.plan != CS_PLAN_DOT) {
-            for (int k = 0; k < r; ++k)
+            int open = -1;  // block whose last sketch waits for a partner
+            for (int k = 0; k < r; ++k) {
+                const int64_t *base = rel_counters(h, k);
+                int b = -1;
+                for (size_t i = 0; shared && i < blocks.size() && b < 0; ++i)
+                    if (blocks[i].base == base && (!G || blocks[i].group == G)) b = (int)i;
+                if (b >= 0) {
+                    q_blocks.push_back(b);
+                    continue;
+                }
+                b = (int)blocks.size();
+                q_blocks.push_back(b);
+                RelBlock B{};
+                B.base = base;
+                B.group = G;
+                B.pair_off = -1;
+                B.norm_off = norm_off;
                 for (int t = 0; t < d; ++t) {
                     SkDesc S;
-                    S.p = rel_counters(h, k) + (size_t)t * m;
+                    S.p = base + (size_t)t * m;
                     S.log2m = L;
                     S.m = h.m;
                     S.nb = nb;
@@ -1290,26 +1333,36 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                     norm_off += nb;
                     sd.push_back(S);
                 }
+                if (G) {
+                    B.mod0 = (int32_t)G->mod_ptrs.size();
+                    B.vec0 = (int32_t)G->re.size();
+                    for (int t = 0; t < d; ++t) G->mod_ptrs.push_back(base + (size_t)t * m);
+                    for (int t = 0; t + 1 < d; t += 2) {
+                        G->re.push_back(base + (size_t)t * m);
+                        G->im.push_back(base + (size_t)(t + 1) * m);
+                    }
+                    if (d & 1) {
+                        if (open < 0) {
+                            B.last = 2 * (int32_t)G->re.size();
+                            G->re.push_back(base + (size_t)(d - 1) * m);
+                            G->im.push_back(nullptr);
+                            open = b;
+                        } else {
+                            RelBlock &O = blocks[open];
+                            B.last = O.last + 1;
+                            G->im[O.last >> 1] = base + (size_t)(d - 1) * m;
+                            B.pair_off = O.norm_off + (int64_t)(d - 1) * nb;
+                            O.pair_off = B.norm_off + (int64_t)(d - 1) * nb;
+                            open = -1;
+                        }
+                    }
+                }
+                blocks.push_back(B);
+            }
         }
-        int vec_base = 0, mod_base = 0;
-        Group *G = nullptr;
-        if (Q.plan == CS_PLAN_SPECTRAL) {
-            G = &groups[L];
-            G->log2m = L;
-            G->S = split_of(L);
-            G->queries.push_back(q);
-            vec_base = (int)G->re.size();
-            const int n_sk = r * d;
-            for (int v = 0; v < (n_sk + 1) / 2; ++v) {
-                const int s0 = 2 * v, s1 = 2 * v + 1;
-                G->re.push_back(sd[sk_base + s0].p);
-                G->im.push_back(s1 < n_sk ? sd[sk_base + s1].p : nullptr);
-            }
-            mod_base = (int)G->mod_ptrs.size();
-            for (int j = 0; j < n_sk; ++j) {
-                G->mod_ptrs.push_back(sd[sk_base + j].p);
-                G->rep_of.push_back(Q.rep_base + j % d);
-            }
+        for (size_t k = 0; k < q_blocks.size(); ++k) {
+            Q.norm_off[k] = blocks[q_blocks[k]].norm_off;
+            Q.pair_off[k] = blocks[q_blocks[k]].pair_off;
         }
         if (Q.plan == CS_PLAN_GENERAL) general_q.push_back(q);
         for (int t = 0; t < d; ++t) {
@@ -1324,10 +1377,12 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             D.r = r;
             D.d = d;
             D.conj = h.g.conj_mask;
-            D.vec_base = vec_base;
             D.nb = nb;
-            D.sk_base = sk_base;
-            D.mod_vec_base = mod_base;
+            for (size_t k = 0; G && k < q_blocks.size(); ++k) {
+                const RelBlock &B = blocks[q_blocks[k]];
+                D.zv[k] = (t ^ 1) < d ? 2 * B.vec0 + t : B.last;
+                D.mv[k] = B.mod0 + t;
+            }
             D.spec_off = spec_off;
             D.dot_off = dot_off;
             D.mod_off = mod_off;
@@ -1360,7 +1415,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     for (size_t i = 0; i < dot_idx.size(); ++i) dot_pre[i + 1] = dot_pre[i] + rd[dot_idx[i]].nb;
     const size_t o_skpre = c.take(sk_pre.size() * sizeof(int64_t));
     const size_t o_dotpre = c.take(dot_pre.size() * sizeof(int64_t));
-    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_grepof;
+    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr;
     std::vector<std::vector<int64_t>> g_pre;
     size_t z_total = 0;
     for (auto &kv : groups) {
@@ -1373,7 +1428,6 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         o_gre.push_back(c.take(G.re.size() * sizeof(void *)));
         o_gim.push_back(c.take(G.im.size() * sizeof(void *)));
         o_gptr.push_back(c.take(G.mod_ptrs.size() * sizeof(void *)));
-        o_grepof.push_back(c.take(G.rep_of.size() * sizeof(int32_t)));
         G.z_off = z_total;
         z_total += align_up(G.re.size() * ((size_t)1 << G.log2m) * sizeof(double2));
     }
@@ -1403,7 +1457,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const size_t h_img = hc.take(host_tables);
     const size_t h_rs = hc.take((size_t)n_rep * sizeof(RepDev));  // same relative layout as the device's
     const size_t h_outs = hc.take((size_t)nq * sizeof(OutDev));
-    const size_t h_mod = hc.take(align_up(sd.size() * sizeof(void *)) + align_up((size_t)n_rep * sizeof(int32_t)) +
+    size_t n_sk = 0;  // every query's sketches, shared ones counted each time
+    for (const QDesc &Q : qd) n_sk += Q.plan == CS_PLAN_DOT ? 0 : (size_t)Q.r * Q.d;
+    const size_t h_mod = hc.take(align_up(n_sk * sizeof(void *)) + align_up((size_t)n_rep * sizeof(int32_t)) +
                                  (size_t)(n_rep + 1 + (int)groups.size()) * sizeof(int64_t) +
                                  3 * 256 * (groups.size() + 1));
     // an asynchronous estimate may still be uploading from the staging area
@@ -1446,7 +1502,6 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             std::memcpy(img.data() + o_gre[gi], G.re.data(), G.re.size() * sizeof(void *));
             std::memcpy(img.data() + o_gim[gi], G.im.data(), G.im.size() * sizeof(void *));
             std::memcpy(img.data() + o_gptr[gi], G.mod_ptrs.data(), G.mod_ptrs.size() * sizeof(void *));
-            std::memcpy(img.data() + o_grepof[gi], G.rep_of.data(), G.rep_of.size() * sizeof(int32_t));
             ++gi;
         }
     }
@@ -1680,7 +1735,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 for (int k = 0; k < qd[q].r; ++k)
                     for (int t = 0; t < qd[q].d; ++t) ptrs.push_back(rel_counters(*hs[q], k) + (size_t)t * hs[q]->m);
                 for (int t = 0; t < qd[q].d; ++t) {
-                    rd[qd[q].rep_base + t].mod_vec_base = base;
+                    RepDesc &D = rd[qd[q].rep_base + t];
+                    for (int k = 0; k < D.r; ++k) D.mv[k] = base + k * D.d + t;
                     idx.push_back(qd[q].rep_base + t);
                 }
             }
@@ -1698,7 +1754,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             std::memcpy(mimg + align_up(ptrs.size() * sizeof(void *)), idx.data(), idx.size() * sizeof(int32_t));
             std::memcpy(mimg + o_mpre, mpre.data(), mpre.size() * sizeof(int64_t));
             CSK_HIP(hipMemcpyAsync(mbc, mimg, tab_bytes, hipMemcpyHostToDevice, s));
-            // updated mod_vec_base of these repetitions
+            // updated mv of these repetitions
             for (int q : needq)
                 CSK_HIP(hipMemcpyAsync(d_rep + qd[q].rep_base, rd.data() + qd[q].rep_base, qd[q].d * sizeof(RepDesc),
                                        hipMemcpyHostToDevice, s));

@@ -102,9 +102,11 @@ cs_status ensure_scratch(cs_sketch *hs, uint64_t n, const int64_t *weights, int3
 cs_status update_args(cs_sketch *hs, int32_t rel, const uint32_t *keys, const int64_t *weights, uint64_t n,
                       int32_t flags, UpdateArgs *out);
 // Estimates of nq queries at once (one FFT launch per sketch length, one product-reduce
-// launch per length, one finalize launch); reps_out may be null or hold nq entries.
+// launch per length, one finalize launch); reps_out may be null or hold nq
+// entries.  shared: queries may read the same relations' sketches, which are then
+// transformed once.
 cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t *outs, const cs_reps_t *reps_out,
-                         EstimateWork &ws, cs_estimate_t *async_out = nullptr);
+                         EstimateWork &ws, cs_estimate_t *async_out = nullptr, bool shared = false);
 
 }  // namespace csk
 

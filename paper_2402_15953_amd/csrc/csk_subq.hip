@@ -693,7 +693,7 @@ cs_status cs_subq_estimate_all(cs_subq *hs, void *stream, cs_estimate_t *outs)
     SubqHandle &h = hs->h;
     std::vector<Handle *> v(h.sub.size());
     for (size_t i = 0; i < h.sub.size(); ++i) v[i] = &h.sub[i].view;
-    return estimate_batch(v.data(), (int)v.size(), static_cast<hipStream_t>(stream), outs, nullptr, h.est);
+    return estimate_batch(v.data(), (int)v.size(), static_cast<hipStream_t>(stream), outs, nullptr, h.est, nullptr, true);
 }
 
 cs_status cs_subq_layout(const cs_subq *hs, int32_t *n_targets, int32_t *target_of)
