@@ -1180,6 +1180,26 @@ const uint32_t *roots_mod(int device, int log2m, int /*prime*/, bool /*inverse*/
     return ins.first->second;
 }
 
+TwiddleTables twiddle_tables(int device, int log2m, hipStream_t s, cs_status *st)
+{
+    TwiddleTables t{};
+    t.log2T = log2m;
+    t.log2S = std::min(log2m, kStageLog2);
+    t.stage = reinterpret_cast<const double2 *>(twiddles_f64(device, t.log2S, s, st));
+    if (t.stage) t.full = reinterpret_cast<const double2 *>(twiddles_f64(device, log2m, s, st));
+    return t;
+}
+
+ModTables mod_tables(int device, int log2m, hipStream_t s, cs_status *st)
+{
+    ModTables t{};
+    t.log2T = log2m;
+    t.log2S = std::min(log2m, kStageLog2);
+    t.stage = roots_mod(device, t.log2S, 0, false, s, st);
+    if (t.stage) t.full = roots_mod(device, log2m, 0, false, s, st);
+    return t;
+}
+
 // ---------------------------------------------------------------- host: batched estimate engine
 
 namespace {
@@ -1561,10 +1581,10 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 if (hipMalloc(&ws.mod, want) != hipSuccess) return fail(CS_ENOMEM, "modular workspace");
                 ws.mod_bytes = want;
             }
-            std::vector<const uint32_t *> groots;
+            std::vector<ModTables> groots;
             for (auto &kv : groups) {  // tables first: built and uploaded synchronously
-                groots.push_back(roots_mod(device, kv.second.log2m, 0, false, s, &st));
-                if (!groots.back()) return st;
+                groots.push_back(mod_tables(device, kv.second.log2m, s, &st));
+                if (!groots.back().full) return st;
             }
             spec = true;
             if (overlap) {
@@ -1580,7 +1600,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 uint32_t *N = reinterpret_cast<uint32_t *>(mod_cur);
                 mod_cur += align_up((size_t)ks * vpp * ((size_t)1 << G.log2m) * sizeof(uint32_t));
                 st = ntt_forward(reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi]), vpp, ks, N, G.log2m,
-                                 G.S, primes, groots[gi], G.log2m, ms);
+                                 G.S, primes, groots[gi], ms);
                 if (st != CS_OK) return st;
                 hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N,
                                    vpp, d_rep, reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
@@ -1609,12 +1629,12 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         int gi = 0;
         for (auto &kv : groups) {
             Group &G = kv.second;
-            const double *tw = twiddles_f64(device, G.log2m, s, &st);
-            if (!tw) return st;
+            const TwiddleTables tw = twiddle_tables(device, G.log2m, s, &st);
+            if (!tw.full) return st;
             double2 *Z = reinterpret_cast<double2 *>(wb + o_Z + G.z_off);
             st = fft_f64_forward(reinterpret_cast<const int64_t *const *>(wb + o_gre[gi]),
                                  reinterpret_cast<const int64_t *const *>(wb + o_gim[gi]), (int)G.re.size(), Z,
-                                 G.log2m, G.S, reinterpret_cast<const double2 *>(tw), G.log2m, s);
+                                 G.log2m, G.S, tw, s);
             if (st != CS_OK) return st;
             hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_pre[gi].back()), dim3(kThreads), 0, s, Z, d_rep,
                                reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
@@ -1726,8 +1746,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 }
             }
             if (needq.empty()) continue;
-            const uint32_t *roots = roots_mod(device, G.log2m, 0, false, s, &st);
-            if (!roots) return st;
+            const ModTables roots = mod_tables(device, G.log2m, s, &st);
+            if (!roots.full) return st;
             std::vector<const int64_t *> ptrs;
             std::vector<int32_t> idx;
             for (int q : needq) {
@@ -1759,8 +1779,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 CSK_HIP(hipMemcpyAsync(d_rep + qd[q].rep_base, rd.data() + qd[q].rep_base, qd[q].d * sizeof(RepDesc),
                                        hipMemcpyHostToDevice, s));
             uint32_t *N = reinterpret_cast<uint32_t *>(mbc + tab_bytes);
-            st = ntt_forward(reinterpret_cast<const int64_t *const *>(mbc), vpp, K, N, G.log2m, G.S, primes, roots,
-                             G.log2m, s);
+            st = ntt_forward(reinterpret_cast<const int64_t *const *>(mbc), vpp, K, N, G.log2m, G.S, primes, roots, s);
             if (st != CS_OK) return st;
             hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)mpre.back(), K), dim3(kThreads), 0, s, N, vpp, d_rep,
                                reinterpret_cast<const int32_t *>(mbc + align_up(ptrs.size() * sizeof(void *))),
@@ -1781,8 +1800,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             const int L = h.pow2 ? h.log2m : ceil_log2(2 * m - 1);
             const uint32_t Mlen = 1u << L;
             const int S = split_of(L);
-            const uint32_t *roots = roots_mod(device, L, 0, false, s, &st);
-            if (!roots) return st;
+            const ModTables roots = mod_tables(device, L, s, &st);
+            if (!roots.full) return st;
             const size_t reg_elems = (size_t)K * d * m;
             uint32_t *M = reinterpret_cast<uint32_t *>(mod_cur);
             mod_cur += align_up((size_t)h.g.n_regs * reg_elems * sizeof(uint32_t));
@@ -1812,28 +1831,28 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                     case OP_CORR: {
                         uint32_t *src = M + (size_t)op.src * reg_elems;
                         if (h.pow2) {
-                            st = ntt_forward(nullptr, d, K, src, L, S, primes, roots, L, s);
+                            st = ntt_forward(nullptr, d, K, src, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
-                            st = ntt_forward(nullptr, d, K, dst, L, S, primes, roots, L, s);
+                            st = ntt_forward(nullptr, d, K, dst, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
                             hipLaunchKernelGGL(k_mod_mul, dim3(gx, K * d), dim3(256), 0, s, dst, src, m, L, S, d,
                                                primes, 1);
                             CSK_HIP(hipGetLastError());
-                            st = ntt_inverse(d, K, dst, L, S, primes, roots, L, s);
+                            st = ntt_inverse(d, K, dst, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
                         } else {
                             // src star dst = reverse(src) circularly convolved with dst
                             hipLaunchKernelGGL(k_mod_pad, dim3(gxM, K * d), dim3(256), 0, s, padA, src, m, Mlen, 1);
                             hipLaunchKernelGGL(k_mod_pad, dim3(gxM, K * d), dim3(256), 0, s, padB, dst, m, Mlen, 0);
                             CSK_HIP(hipGetLastError());
-                            st = ntt_forward(nullptr, d, K, padA, L, S, primes, roots, L, s);
+                            st = ntt_forward(nullptr, d, K, padA, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
-                            st = ntt_forward(nullptr, d, K, padB, L, S, primes, roots, L, s);
+                            st = ntt_forward(nullptr, d, K, padB, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
                             hipLaunchKernelGGL(k_mod_mul, dim3(gxM, K * d), dim3(256), 0, s, padB, padA, Mlen, L, S, d,
                                                primes, 0);
                             CSK_HIP(hipGetLastError());
-                            st = ntt_inverse(d, K, padB, L, S, primes, roots, L, s);
+                            st = ntt_inverse(d, K, padB, L, S, primes, roots, s);
                             if (st != CS_OK) return st;
                             hipLaunchKernelGGL(k_mod_fold, dim3(gx, K * d), dim3(256), 0, s, dst, padB, m, Mlen, d,
                                                primes);
@@ -1951,10 +1970,10 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
     int device = 0;
     CSK_HIP(hipGetDevice(&device));
     cs_status st = CS_OK;
-    const double *tw = twiddles_f64(device, log2m, s, &st);
-    if (!tw) return st;
-    const uint32_t *roots = roots_mod(device, log2m, 0, false, s, &st);
-    if (!roots) return st;
+    const TwiddleTables tw = twiddle_tables(device, log2m, s, &st);
+    if (!tw.full) return st;
+    const ModTables roots = mod_tables(device, log2m, s, &st);
+    if (!roots.full) return st;
     PrimeDev *primes = nullptr;
     if ((st = device_primes(device, s, &primes)) != CS_OK) return st;
     const size_t m = (size_t)1 << log2m;
@@ -2020,7 +2039,7 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         o.valid = 0;
         o.ms = -1.0f;
         uint32_t *dst = ci == 0 ? Nref : N;
-        if ((st = ntt_forward(nt, n_vec, 1, dst, log2m, S, primes, roots, log2m, s)) != CS_OK) break;
+        if ((st = ntt_forward(nt, n_vec, 1, dst, log2m, S, primes, roots, s)) != CS_OK) break;
         if (ci > 0) {
             unsigned int hflag = 0;
             hipLaunchKernelGGL(k_tune_flag0, dim3(1), dim3(1), 0, s, flag);
@@ -2039,8 +2058,8 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         bool ok = true;
         for (int r = 0; r < 3 && ok; ++r)
             ok = hipEventRecord(e0, s) == hipSuccess &&
-                 fft_f64_forward(re, im, n_vec, Z, log2m, S, reinterpret_cast<const double2 *>(tw), log2m, s) == CS_OK &&
-                 ntt_forward(nt, n_vec, 1, N, log2m, S, primes, roots, log2m, s) == CS_OK &&
+                 fft_f64_forward(re, im, n_vec, Z, log2m, S, tw, s) == CS_OK &&
+                 ntt_forward(nt, n_vec, 1, N, log2m, S, primes, roots, s) == CS_OK &&
                  hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
                  hipEventElapsedTime(&t[r], e0, e1) == hipSuccess;
         if (!ok) {

@@ -59,19 +59,33 @@ __host__ __device__ inline uint32_t pos_freq(uint32_t pos, int log2m, int S)
     return (pos >> S) | ((pos & ((1u << S) - 1)) << (log2m - S));
 }
 
+// A transform's root table (the powers of a primitive 2^log2T-th root) and the one its
+// stages read: 2^12 entries, or the same table for shorter transforms.  A tile of length L
+// takes every 2^(12 - log2 L)-th entry of it; from the table of a long transform it took
+// entries a kilobyte apart, many times the tile's own bytes in cache lines.
+constexpr int kStageLog2 = 12;
+template <class T>
+struct RootTables {
+    const T *full;
+    const T *stage;
+    int log2T, log2S;
+};
+using TwiddleTables = RootTables<double2>;
+using ModTables = RootTables<uint32_t>;
+// Both tables of length 2^log2m on `device`, built on first use (full = null on failure).
+TwiddleTables twiddle_tables(int device, int log2m, hipStream_t s, cs_status *st);
+ModTables mod_tables(int device, int log2m, hipStream_t s, cs_status *st);
+
 // Forward fp64 FFTs of n_vec complex vectors re[v] + i im[v] (device pointer tables of
 // int64 sketches; im[v] may be null) into buf [n_vec][m].
 cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
-                          int S, const double2 *tw, int log2T, hipStream_t s);
+                          int S, const TwiddleTables &tw, hipStream_t s);
 
 // ptrs != null: vector (prime i, j) is loaded from sketch ptrs[j] (device pointer table);
-// ptrs == null: transform buf in place.  rep_of / kp (both device, may be null): vector j
-// serves repetition rep_of[j], which needs kp[rep_of[j]] primes; the blocks of primes
-// beyond that return without touching buf.
+// ptrs == null: transform buf in place.
 cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
-                      const PrimeDev *primes, const uint32_t *roots, int log2T, hipStream_t s,
-                      const int32_t *rep_of = nullptr, const int32_t *kp = nullptr);
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s);
 cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S, const PrimeDev *primes,
-                      const uint32_t *roots, int log2T, hipStream_t s);
+                      const ModTables &roots, hipStream_t s);
 
 }  // namespace csk

@@ -133,7 +133,8 @@ struct F64Src {
 
 template <int TILE>
 __global__ __launch_bounds__(TILE / 4) void k_fft_f64(F64Src src, double2 *buf, PassGeom g,
-                                                     const double2 *__restrict__ tw, int log2T)
+                                                     const double2 *__restrict__ tw, int log2T,
+                                                     const double2 *__restrict__ stage, int log2S)
 {
     constexpr int NT = TILE / 4;
     __shared__ double2 s[lds_len<TILE>()];
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(TILE / 4) void k_fft_f64(F64Src src, double2 *buf, 
             s[lp((bitrev(n, g.log2L) << g.log2C) + c)] = vec[pos];
         }
     }
-    load_stage_twiddles<NT>(stw, g.log2L, tw, log2T);
+    load_stage_twiddles<NT>(stw, g.log2L, stage, log2S);
     __syncthreads();
     RingC R;
     lds_stages<NT, RingC>(s, g.log2L, g.log2C, R, stw);
@@ -188,15 +189,14 @@ struct ModSrc {
 template <int TILE, int NT>
 __global__ __launch_bounds__(NT) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime,
                                            const PrimeDev *__restrict__ primes,
-                                           const uint32_t *__restrict__ roots, int log2T, int inverse,
-                                           const int32_t *__restrict__ rep_of, const int32_t *__restrict__ kp)
+                                           const uint32_t *__restrict__ roots, int log2T,
+                                           const uint32_t *__restrict__ stage, int log2S, int inverse)
 {
     __shared__ uint32_t s[lds_len<TILE>()];
     __shared__ uint32_t stw[TILE / 2];
     __shared__ uint32_t s_row[64];  // row passes with twiddles: w^(j blk), j < 64
     const int v = blockIdx.x;
     const int pi = v / vec_per_prime;
-    if (kp && pi >= kp[rep_of[v % vec_per_prime]]) return;  // prime not needed
     const PrimeDev &P = primes[pi];  // by reference: a copy with minv[] indexed would live in scratch
     const RingM R{P.p, P.pinv_neg};
     const uint32_t *tw = roots + ((size_t)(2 * pi + inverse) << log2T);
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(NT) void k_ntt(ModSrc src, uint32_t *buf, PassGeom 
             s[lp((bitrev(n, g.log2L) << g.log2C) + c)] = vec[pos];
         }
     }
-    load_stage_twiddles<NT>(stw, g.log2L, tw, log2T);
+    load_stage_twiddles<NT>(stw, g.log2L, stage + ((size_t)(2 * pi + inverse) << log2S), log2S);
     if (g.twiddle && g.log2C == 0 && threadIdx.x < 64)
         s_row[threadIdx.x] = tw[(size_t)(((int64_t)threadIdx.x * blk) & (m - 1)) << (log2T - g.log2m)];
     __syncthreads();
@@ -313,7 +313,7 @@ int split_for(int device, int log2m)
 }
 
 cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
-                          int S, const double2 *tw, int log2T, hipStream_t s)
+                          int S, const TwiddleTables &tw, hipStream_t s)
 {
     if (n_vec == 0) return CS_OK;
     F64Src first{re, im};
@@ -321,7 +321,8 @@ cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, in
     auto pass = [&](const PassGeom &g, bool single, const F64Src &src) {
         with_tile(g, single, [&](auto tile) {
             constexpr int T = decltype(tile)::value;
-            hipLaunchKernelGGL(k_fft_f64<T>, dim3(n_vec, g.blocks), dim3(T / 4), 0, s, src, buf, g, tw, log2T);
+            hipLaunchKernelGGL(k_fft_f64<T>, dim3(n_vec, g.blocks), dim3(T / 4), 0, s, src, buf, g, tw.full, tw.log2T,
+                               tw.stage, tw.log2S);
         });
         return hipGetLastError();
     };
@@ -351,14 +352,13 @@ PassGeom widen_columns(PassGeom g)
 }
 
 hipError_t ntt_pass(const PassGeom &g, bool single, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
-                    const PrimeDev *primes, const uint32_t *roots, int log2T, int inverse, const int32_t *rep_of,
-                    const int32_t *kp, hipStream_t s)
+                    const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
 {
     auto go = [&](auto tile) {
         constexpr int T = decltype(tile)::value;
         constexpr int NT = T / 8 < 1024 ? T / 8 : 1024;
         hipLaunchKernelGGL((k_ntt<T, NT>), dim3(n_vec, g.blocks), dim3(NT), 0, s, src, buf, g, vec_per_prime,
-                           primes, roots, log2T, inverse, rep_of, kp);
+                           primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
     };
     const int tile_bits = g.log2L + g.log2C;
     if (single) go(std::integral_constant<int, kSingleTile>{});
@@ -372,8 +372,7 @@ hipError_t ntt_pass(const PassGeom &g, bool single, const ModSrc &src, int n_vec
 }  // namespace
 
 cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
-                      const PrimeDev *primes, const uint32_t *roots, int log2T, hipStream_t s,
-                      const int32_t *rep_of, const int32_t *kp)
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s)
 {
     const int n_vec = vec_per_prime * n_primes;
     if (n_vec == 0) return CS_OK;
@@ -381,19 +380,17 @@ cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_prime
     ModSrc self{nullptr};
     const ModSrc &in = ptrs ? first : self;
     if (log2m <= 12) {
-        CSK_HIP(ntt_pass(single_pass(log2m), true, in, n_vec, buf, vec_per_prime, primes, roots, log2T, 0, rep_of,
-                         kp, s));
+        CSK_HIP(ntt_pass(single_pass(log2m), true, in, n_vec, buf, vec_per_prime, primes, roots, 0, s));
         return CS_OK;
     }
     CSK_HIP(ntt_pass(widen_columns(column_pass(log2m, S, true)), false, in, n_vec, buf, vec_per_prime, primes,
-                     roots, log2T, 0, rep_of, kp, s));
-    CSK_HIP(ntt_pass(row_pass(log2m, S, false), false, self, n_vec, buf, vec_per_prime, primes, roots, log2T, 0,
-                     rep_of, kp, s));
+                     roots, 0, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, false), false, self, n_vec, buf, vec_per_prime, primes, roots, 0, s));
     return CS_OK;
 }
 
 cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S, const PrimeDev *primes,
-                      const uint32_t *roots, int log2T, hipStream_t s)
+                      const ModTables &roots, hipStream_t s)
 {
     const int n_vec = vec_per_prime * n_primes;
     if (n_vec == 0) return CS_OK;
@@ -401,14 +398,13 @@ cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m,
     if (log2m <= 12) {
         PassGeom g = single_pass(log2m);
         g.scale = 1;
-        CSK_HIP(ntt_pass(g, true, self, n_vec, buf, vec_per_prime, primes, roots, log2T, 1, nullptr, nullptr, s));
+        CSK_HIP(ntt_pass(g, true, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(row_pass(log2m, S, true), false, self, n_vec, buf, vec_per_prime, primes, roots, log2T, 1,
-                     nullptr, nullptr, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, true), false, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     PassGeom g2 = widen_columns(column_pass(log2m, S, false));
     g2.scale = 1;
-    CSK_HIP(ntt_pass(g2, false, self, n_vec, buf, vec_per_prime, primes, roots, log2T, 1, nullptr, nullptr, s));
+    CSK_HIP(ntt_pass(g2, false, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     return CS_OK;
 }
 
