@@ -186,69 +186,169 @@ struct ModSrc {
     const int64_t *const *ptr;  // [vec_per_prime] sketch of vector v % vec_per_prime (null: in place)
 };
 
-template <int TILE, int NT>
-__global__ __launch_bounds__(NT) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime,
-                                           const PrimeDev *__restrict__ primes,
-                                           const uint32_t *__restrict__ roots, int log2T,
-                                           const uint32_t *__restrict__ stage, int log2S, int inverse)
+// The NTT holds sixteen elements per thread and takes up to four stages between two trips
+// through LDS: a transform of length 2^LG is one to three rounds of decimation in frequency
+// with radices 2^rbits(LG, round), each round's DFTs in registers.  Element s of the tile
+// after a round is block b (the digits of the frequency found so far, first digit most
+// significant) times the remaining length plus the index within it, so a round reads and
+// writes the same places and the last one's outputs sit at digit-reversed frequencies.
+constexpr int kNttE = 16;  // elements per thread
+constexpr int ntt_rounds(int lg) { return lg <= 4 ? 1 : lg <= 8 ? 2 : 3; }
+constexpr int ntt_rbits(int lg, int round)
 {
-    __shared__ uint32_t s[lds_len<TILE>()];
-    __shared__ uint32_t stw[TILE / 2];
-    __shared__ uint32_t s_row[64];  // row passes with twiddles: w^(j blk), j < 64
+    return ntt_rounds(lg) == 1   ? lg
+           : ntt_rounds(lg) == 2 ? (round == 0 ? (lg + 1) / 2 : lg / 2)
+                                 : (round == 0 ? (lg + 2) / 3 : round == 1 ? (lg + 1) / 3 : lg / 3);
+}
+constexpr int ntt_threads(int lg, int lc) { return (1 << (lg + lc)) / kNttE < 64 ? 64 : (1 << (lg + lc)) / kNttE; }
+
+// DFT of length 2^RB in registers, decimation in frequency: x[k] in, frequency bitrev(k)
+// in x[k] out.  w[j] = w_R^j, j < R / 2.  Inputs below p.  The last stage's results are
+// below 2p when `lazy` (a twiddle multiplies them next), else below p.
+template <int RB, bool LAZY>
+__device__ __forceinline__ void dft_regs(uint32_t (&x)[1 << RB], const RingM &R, const uint32_t *w)
+{
+    constexpr int N = 1 << RB;
+#pragma unroll
+    for (int st = 0; st < RB; ++st) {
+        const int half = N >> (st + 1);
+        const bool last = st == RB - 1;
+#pragma unroll
+        for (int b = 0; b < N; b += 2 * half)
+#pragma unroll
+            for (int k = 0; k < half; ++k) {
+                const uint32_t a = x[b + k], c = x[b + k + half];
+                const uint32_t u = a + c, v = a - c + R.p;  // both below 2p
+                x[b + k] = LAZY && last ? u : min(u, u - R.p);
+                // w_{2 half}^k = w_N^(k N / (2 half))
+                x[b + k + half] = k == 0 ? (LAZY && last ? v : min(v, v - R.p)) : R.mul(v, w[k << st]);
+            }
+    }
+}
+
+constexpr int brev_bits(int x, int bits)
+{
+    int r = 0;
+    for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1) << (bits - 1 - i);
+    return r;
+}
+
+// One round of the tile's transforms (see above).  src(n, c) supplies the first round's
+// inputs, dst(f, c, value) takes the last one's outputs; s is the tile in LDS, stw the
+// powers of w_L.  Every thread of the block calls it.
+template <int LG, int LC, int ROUND, class Src, class Dst>
+__device__ __forceinline__ void ntt_round(uint32_t *s, const uint32_t *stw, const RingM &R, const uint32_t *wr,
+                                          Src &&src, Dst &&dst)
+{
+    constexpr int NR = ntt_rounds(LG), RB = ntt_rbits(LG, ROUND), N = 1 << RB;
+    constexpr int done = ROUND == 0 ? 0 : ROUND == 1 ? ntt_rbits(LG, 0) : ntt_rbits(LG, 0) + ntt_rbits(LG, 1);
+    constexpr int LJ = LG - done, LN = LJ - RB;  // log2 of the length before and after the round
+    constexpr bool first = ROUND == 0, last = ROUND == NR - 1;
+    constexpr int NT = ntt_threads(LG, LC);
+    constexpr int groups = 1 << (LG + LC - RB);
+#pragma unroll
+    for (int g0 = 0; g0 < groups; g0 += NT) {
+        const int g = g0 + threadIdx.x;
+        if (groups < NT && g >= groups) break;
+        const int c = g & ((1 << LC) - 1), h = g >> LC;
+        // middle rounds: h = block * 2^LN + index; last round: h counts the blocks by their
+        // frequency, first digit fastest, so that neighbouring lanes store neighbours
+        int blk = h >> LN, i = h & ((1 << LN) - 1);
+        if (last && NR == 3) {
+            constexpr int r0 = ntt_rbits(LG, 0), r1 = ntt_rbits(LG, 1);
+            blk = ((h & ((1 << r0) - 1)) << r1) | (h >> r0);
+        }
+        const int at = (((blk << LJ) + i) << LC) + c;  // element k at at + k 2^(LN + LC)
+        uint32_t x[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = first ? src(i + (k << LN), c) : s[lp(at + (k << (LN + LC)))];
+        dft_regs<RB, !last>(x, R, wr);
+        if (last) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) dst(h + (k << done), c, k, x[brev_bits(k, RB)]);
+        } else {
+            // frequency digit k of index i: times w_(2^LJ)^(i k)
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                uint32_t v = x[brev_bits(k, RB)];
+                v = k == 0 ? min(v, v - R.p) : R.mul(v, stw[(i * k) << (LG - LJ)]);
+                s[lp(at + (k << (LN + LC)))] = v;
+            }
+        }
+    }
+}
+
+// One pass: a block transforms 2^LC interleaved columns of length 2^LG.  Bound by the vector
+// unit and memory about equally.  Two stages per trip through LDS with four elements per
+// thread cost as much address arithmetic, LDS instructions and barriers as butterflies:
+// 15 vectors of 2^21 at 3 primes took 213 us (columns) and 144 us (rows), 97 and 103 us in
+// registers.
+template <int LG, int LC>
+__global__ __launch_bounds__(ntt_threads(LG, LC)) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime,
+                                                             const PrimeDev *__restrict__ primes,
+                                                             const uint32_t *__restrict__ roots, int log2T,
+                                                             const uint32_t *__restrict__ stage, int log2S, int inverse)
+{
+    constexpr int TILE = 1 << (LG + LC), NT = ntt_threads(LG, LC), NR = ntt_rounds(LG);
+    __shared__ uint32_t s[NR > 1 ? lds_len<TILE>() + 1 : 1];
+    __shared__ uint32_t stw[NR > 1 ? 1 << LG : 1];
     const int v = blockIdx.x;
     const int pi = v / vec_per_prime;
     const PrimeDev &P = primes[pi];  // by reference: a copy with minv[] indexed would live in scratch
     const RingM R{P.p, P.pinv_neg};
     const uint32_t *tw = roots + ((size_t)(2 * pi + inverse) << log2T);
+    const uint32_t *st = stage + ((size_t)(2 * pi + inverse) << log2S);
     const int blk = blockIdx.y;
-    const int C = 1 << g.log2C;
-    const int L = 1 << g.log2L;
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     uint32_t *vec = buf + (size_t)v * m;
-    const int total = L << g.log2C;
-    if (src.ptr) {
-        const int64_t *in = src.ptr[v % vec_per_prime];
-        for (int idx = threadIdx.x; idx < total; idx += NT) {
-            const int n = idx >> g.log2C, c = idx & (C - 1);
-            const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-            s[lp((bitrev(n, g.log2L) << g.log2C) + c)] = mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64);
-        }
-    } else {
-        for (int idx = threadIdx.x; idx < total; idx += NT) {
-            const int n = idx >> g.log2C, c = idx & (C - 1);
-            const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-            s[lp((bitrev(n, g.log2L) << g.log2C) + c)] = vec[pos];
-        }
-    }
-    load_stage_twiddles<NT>(stw, g.log2L, stage + ((size_t)(2 * pi + inverse) << log2S), log2S);
-    if (g.twiddle && g.log2C == 0 && threadIdx.x < 64)
-        s_row[threadIdx.x] = tw[(size_t)(((int64_t)threadIdx.x * blk) & (m - 1)) << (log2T - g.log2m)];
-    __syncthreads();
-    lds_stages<NT, RingM>(s, g.log2L, g.log2C, R, stw);
-    for (int idx = threadIdx.x; idx < total; idx += NT) {
-        const int n = idx >> g.log2C, c = idx & (C - 1);
+    if (NR > 1)
+        for (int e = threadIdx.x; e < (1 << LG); e += NT) stw[e] = st[(size_t)e << (log2S - LG)];
+    // roots of the register DFTs: w_R^j from the table's quarter-length entries (uniform)
+    constexpr int RB0 = ntt_rbits(LG, 0), RB1 = NR > 1 ? ntt_rbits(LG, 1) : 1, RB2 = NR > 2 ? ntt_rbits(LG, 2) : 1;
+    auto small_roots = [&](uint32_t *w, int rb) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = j < (1 << rb) / 2 ? st[(size_t)j << (log2S - rb)] : 0u;
+    };
+    const int64_t *in = src.ptr ? src.ptr[v % vec_per_prime] : nullptr;
+    auto load = [&](int n, int c) {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-        uint32_t val = s[lp((n << g.log2C) + c)];
+        return in ? mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64) : vec[pos];
+    };
+    // Output n of column c is multiplied by w_m^(n colid): a thread's outputs are an
+    // arithmetic progression in n (frequencies f0 + k step), so two entries of the long
+    // table, w^(f0 colid) and w^(step colid), give them all by one product each.  Exact
+    // arithmetic: the same residues as one lookup per element.
+    const int sh = log2T - g.log2m;
+    uint32_t t_cur = 0, t_step = 0;
+    auto store = [&](int f, int c, int k, uint32_t val) {
         if (g.twiddle) {
-            const int sh = log2T - g.log2m;
-            if (g.log2C > 0) {
-                // w^(n (blk C + c)) = w^(n blk C) w^(n c): the first factor is one entry
-                // for the C lanes of one n, the second lies in the table's first L C
-                // entries (n c < L C), so neither is a scattered read of a table of m
-                // entries (exact arithmetic: the same residue as one lookup)
-                const uint32_t a = tw[(size_t)(((int64_t)n * blk * C) & (m - 1)) << sh];
-                const uint32_t b = tw[(size_t)((int64_t)n * c) << sh];
-                val = R.mul(R.mul(val, a), b);
+            if (k == 0) {
+                constexpr int step = 1 << (LG - (NR == 1 ? RB0 : NR == 2 ? RB1 : RB2));
+                const int64_t col = ((int64_t)blk << LC) + c;
+                t_cur = tw[(size_t)((f * col) & (m - 1)) << sh];
+                t_step = tw[(size_t)((step * col) & (m - 1)) << sh];
             } else {
-                // a row (C = 1): w^(n blk) = w^(64 (n >> 6) blk) w^((n & 63) blk), the
-                // first factor one entry for a wavefront's 64 lanes, the second from LDS
-                const uint32_t a = tw[(size_t)(((int64_t)(n >> 6) * 64 * blk) & (m - 1)) << sh];
-                val = R.mul(R.mul(val, a), s_row[n & 63]);
+                t_cur = R.mul(t_cur, t_step);
             }
+            val = R.mul(val, t_cur);
         }
         if (g.scale) val = R.mul(val, P.minv[g.log2m]);
-        vec[pos] = val;
+        vec[base + (int64_t)c * g.col_stride + (int64_t)f * g.elem_stride] = val;
+    };
+    uint32_t w[8];
+    small_roots(w, RB0);
+    if constexpr (NR > 1) __syncthreads();  // stw
+    ntt_round<LG, LC, 0>(s, stw, R, w, load, store);
+    if constexpr (NR > 1) {
+        __syncthreads();
+        if constexpr (RB1 != RB0) small_roots(w, RB1);
+        ntt_round<LG, LC, 1>(s, stw, R, w, load, store);
+    }
+    if constexpr (NR > 2) {
+        __syncthreads();
+        if constexpr (RB2 != RB1) small_roots(w, RB2);
+        ntt_round<LG, LC, 2>(s, stw, R, w, load, store);
     }
 }
 
@@ -336,38 +436,65 @@ cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, in
 }
 
 namespace {
-// The column pass of the NTT reads its columns in runs of C 4-byte residues; with the
-// split shared with the fp64 FFT (runs of >= 8 complex doubles = 128 bytes) C can be as
-// low as 8 (32 bytes), so NTT column passes take up to 32 columns per block (tiles up
-// to 16384 residues, 64 KB of LDS, 1024 threads).  The decomposition, and with it the
-// output order, is unchanged.
+// The column pass of the NTT reads its columns in runs of C 4-byte residues (8 bytes from
+// the sketches): 32 columns per block up to length 2^8, 16 beyond (tiles of at most 2^14
+// residues, 64 KB of LDS).  The decomposition, and with it the output order, is the
+// same as with the fp64 FFT's narrower blocks.
+constexpr int ntt_log2c(int lg) { return lg <= 8 ? 5 : 4; }
 PassGeom widen_columns(PassGeom g)
 {
-    while (g.log2C < 5 && g.blocks > 1 && g.log2L + g.log2C < 14) {
-        ++g.log2C;
-        g.block_stride <<= 1;
-        g.blocks >>= 1;
-    }
+    const int c = ntt_log2c(g.log2L);
+    g.blocks = (g.blocks << g.log2C) >> c;
+    g.log2C = c;
+    g.block_stride = (int64_t)1 << c;
     return g;
 }
 
-hipError_t ntt_pass(const PassGeom &g, bool single, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
+template <int LG, bool ROW>
+void ntt_launch(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
+                const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
+{
+    constexpr int LC = ROW ? 0 : ntt_log2c(LG);
+    hipLaunchKernelGGL((k_ntt<LG, LC>), dim3(n_vec, g.blocks), dim3(ntt_threads(LG, LC)), 0, s, src, buf, g,
+                       vec_per_prime, primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
+}
+
+// Row (and single) passes have one column; two-pass rows are 2^10 to 2^12 long, the columns
+// of lengths up to 2^21 at most 2^10.
+hipError_t ntt_pass(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
                     const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
 {
-    auto go = [&](auto tile) {
-        constexpr int T = decltype(tile)::value;
-        constexpr int NT = T / 8 < 1024 ? T / 8 : 1024;
-        hipLaunchKernelGGL((k_ntt<T, NT>), dim3(n_vec, g.blocks), dim3(NT), 0, s, src, buf, g, vec_per_prime,
-                           primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
+    auto go = [&](auto lg, auto row) {
+        ntt_launch<decltype(lg)::value, decltype(row)::value>(g, src, n_vec, buf, vec_per_prime, primes, roots, inverse,
+                                                              s);
     };
-    const int tile_bits = g.log2L + g.log2C;
-    if (single) go(std::integral_constant<int, kSingleTile>{});
-    else if (tile_bits <= 10) go(std::integral_constant<int, 1024>{});
-    else if (tile_bits == 11) go(std::integral_constant<int, 2048>{});
-    else if (tile_bits == 12) go(std::integral_constant<int, 4096>{});
-    else if (tile_bits == 13) go(std::integral_constant<int, 8192>{});
-    else go(std::integral_constant<int, 16384>{});
-    return hipGetLastError();
+    auto pick = [&](auto row) {
+        switch (g.log2L) {
+#define CSK_NTT_CASE(LG) \
+    case LG: go(std::integral_constant<int, LG>{}, row); break;
+            CSK_NTT_CASE(1)
+            CSK_NTT_CASE(2)
+            CSK_NTT_CASE(3)
+            CSK_NTT_CASE(4)
+            CSK_NTT_CASE(5)
+            CSK_NTT_CASE(6)
+            CSK_NTT_CASE(7)
+            CSK_NTT_CASE(8)
+            CSK_NTT_CASE(9)
+            CSK_NTT_CASE(10)
+            default:
+                if constexpr (decltype(row)::value) {
+                    if (g.log2L == 11) go(std::integral_constant<int, 11>{}, row);
+                    else if (g.log2L == 12) go(std::integral_constant<int, 12>{}, row);
+                    else return hipErrorInvalidValue;
+                } else {
+                    return hipErrorInvalidValue;
+                }
+#undef CSK_NTT_CASE
+        }
+        return hipGetLastError();
+    };
+    return g.log2C == 0 ? pick(std::true_type{}) : pick(std::false_type{});
 }
 }  // namespace
 
@@ -380,12 +507,12 @@ cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_prime
     ModSrc self{nullptr};
     const ModSrc &in = ptrs ? first : self;
     if (log2m <= 12) {
-        CSK_HIP(ntt_pass(single_pass(log2m), true, in, n_vec, buf, vec_per_prime, primes, roots, 0, s));
+        CSK_HIP(ntt_pass(single_pass(log2m), in, n_vec, buf, vec_per_prime, primes, roots, 0, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(widen_columns(column_pass(log2m, S, true)), false, in, n_vec, buf, vec_per_prime, primes,
+    CSK_HIP(ntt_pass(widen_columns(column_pass(log2m, S, true)), in, n_vec, buf, vec_per_prime, primes,
                      roots, 0, s));
-    CSK_HIP(ntt_pass(row_pass(log2m, S, false), false, self, n_vec, buf, vec_per_prime, primes, roots, 0, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, false), self, n_vec, buf, vec_per_prime, primes, roots, 0, s));
     return CS_OK;
 }
 
@@ -398,13 +525,13 @@ cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m,
     if (log2m <= 12) {
         PassGeom g = single_pass(log2m);
         g.scale = 1;
-        CSK_HIP(ntt_pass(g, true, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+        CSK_HIP(ntt_pass(g, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(row_pass(log2m, S, true), false, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, true), self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     PassGeom g2 = widen_columns(column_pass(log2m, S, false));
     g2.scale = 1;
-    CSK_HIP(ntt_pass(g2, false, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+    CSK_HIP(ntt_pass(g2, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     return CS_OK;
 }
 
