@@ -983,6 +983,7 @@ std::vector<PrimeInfo> build_primes()
 struct DeviceTables {
     PrimeDev *primes = nullptr;
     std::map<int, double2 *> tw;       // log2m -> twiddles
+    std::map<int, double2 *> columns;  // log2m * 64 + S -> column pass twiddles
     std::map<int, uint32_t *> roots;   // log2m -> [K][2][m]
 };
 std::mutex g_tab_mu;
@@ -1180,13 +1181,46 @@ const uint32_t *roots_mod(int device, int log2m, int /*prime*/, bool /*inverse*/
     return ins.first->second;
 }
 
-TwiddleTables twiddle_tables(int device, int log2m, hipStream_t s, cs_status *st)
+// The column pass's twiddles of one (length, split), gathered on the device from the table
+// of powers and kept with it.  Built on a stream of the caller, waited for before they are
+// published, like the uploads of the other tables.
+const double2 *column_table(int device, int log2m, int S, const double2 *tw, hipStream_t s, cs_status *st)
+{
+    const int key = log2m * 64 + S;
+    {
+        std::lock_guard<std::mutex> lk(g_tab_mu);
+        auto &cols = g_tabs[device].columns;
+        auto it = cols.find(key);
+        if (it != cols.end()) return it->second;
+    }
+    double2 *dp = nullptr;
+    if (hipMalloc(&dp, sizeof(double2) << log2m) != hipSuccess) {
+        *st = fail(CS_ENOMEM, "column twiddle allocation failed");
+        return nullptr;
+    }
+    *st = column_twiddles(dp, tw, log2m, S, s);
+    if (*st == CS_OK && hipStreamSynchronize(s) != hipSuccess) *st = fail(CS_EDEVICE, "column twiddles");
+    if (*st != CS_OK) {
+        (void)hipFree(dp);
+        return nullptr;
+    }
+    std::lock_guard<std::mutex> lk(g_tab_mu);
+    auto ins = g_tabs[device].columns.emplace(key, dp);
+    if (!ins.second) (void)hipFree(dp);  // built meanwhile by another thread
+    return ins.first->second;
+}
+
+TwiddleTables twiddle_tables(int device, int log2m, int S, hipStream_t s, cs_status *st)
 {
     TwiddleTables t{};
     t.log2T = log2m;
     t.log2S = std::min(log2m, kStageLog2);
     t.stage = reinterpret_cast<const double2 *>(twiddles_f64(device, t.log2S, s, st));
     if (t.stage) t.full = reinterpret_cast<const double2 *>(twiddles_f64(device, log2m, s, st));
+    if (t.full && log2m > kStageLog2) {
+        t.columns = column_table(device, log2m, S, t.full, s, st);
+        if (!t.columns) t.full = nullptr;
+    }
     return t;
 }
 
@@ -1629,7 +1663,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         int gi = 0;
         for (auto &kv : groups) {
             Group &G = kv.second;
-            const TwiddleTables tw = twiddle_tables(device, G.log2m, s, &st);
+            const TwiddleTables tw = twiddle_tables(device, G.log2m, G.S, s, &st);
             if (!tw.full) return st;
             double2 *Z = reinterpret_cast<double2 *>(wb + o_Z + G.z_off);
             st = fft_f64_forward(reinterpret_cast<const int64_t *const *>(wb + o_gre[gi]),
@@ -1970,8 +2004,6 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
     int device = 0;
     CSK_HIP(hipGetDevice(&device));
     cs_status st = CS_OK;
-    const TwiddleTables tw = twiddle_tables(device, log2m, s, &st);
-    if (!tw.full) return st;
     const ModTables roots = mod_tables(device, log2m, s, &st);
     if (!roots.full) return st;
     PrimeDev *primes = nullptr;
@@ -2039,6 +2071,8 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         o.valid = 0;
         o.ms = -1.0f;
         uint32_t *dst = ci == 0 ? Nref : N;
+        const TwiddleTables tw = twiddle_tables(device, log2m, S, s, &st);
+        if (!tw.full) break;
         if ((st = ntt_forward(nt, n_vec, 1, dst, log2m, S, primes, roots, s)) != CS_OK) break;
         if (ci > 0) {
             unsigned int hflag = 0;

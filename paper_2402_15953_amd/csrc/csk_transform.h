@@ -69,12 +69,20 @@ struct RootTables {
     const T *full;
     const T *stage;
     int log2T, log2S;
+    // the fp64 column pass's twiddles in the order it uses them (column_twiddles; null for
+    // lengths of one pass)
+    const T *columns;
 };
 using TwiddleTables = RootTables<double2>;
 using ModTables = RootTables<uint32_t>;
-// Both tables of length 2^log2m on `device`, built on first use (full = null on failure).
-TwiddleTables twiddle_tables(int device, int log2m, hipStream_t s, cs_status *st);
+// Both tables of length 2^log2m on `device`, built on first use (full = null on failure);
+// S is the row length's logarithm of the transforms that will use them.
+TwiddleTables twiddle_tables(int device, int log2m, int S, hipStream_t s, cs_status *st);
 ModTables mod_tables(int device, int log2m, hipStream_t s, cs_status *st);
+
+// out[j] = tw[...], the m twiddles of the fp64 column pass at row length 2^S: a block's
+// outputs in tile order, blocks one after another.
+cs_status column_twiddles(double2 *out, const double2 *tw, int log2m, int S, hipStream_t s);
 
 // Forward fp64 FFTs of n_vec complex vectors re[v] + i im[v] (device pointer tables of
 // int64 sketches; im[v] may be null) into buf [n_vec][m].

@@ -11,8 +11,8 @@
 //            then holds frequency f = f1 + N1 f2 (no final transpose).
 //   inverse: takes that permuted order back to natural order: row pass over f2 with
 //            w_m^(-n2 f1) applied to output n2, then the column pass over f1.
-// Inside LDS each tile is loaded in bit-reversed order and finished by radix-2
-// decimation-in-time stages; twiddles come from host-computed tables.
+// Inside a pass, rounds of register DFTs exchange their elements through LDS; twiddles
+// come from host-computed tables.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -25,101 +25,92 @@ namespace csk {
 
 namespace {
 
-// A block transforms one tile of TILE elements: the fp64 FFT with TILE / 4 threads (two
-// butterflies per thread per stage; the pass is bound by memory and wants the loads of
-// many wavefronts), the NTT with TILE / 8 (four per thread: its passes wait on their
-// barriers, and two independent butterfly groups per thread between two barriers
-// measured 13-20% faster than one; four per thread were slower again).  Two-pass lengths use the smallest tile that keeps the column
-// pass's reads in runs of at least 8 elements: a 2^16-point transform is 64 blocks of
-// 1024 elements per vector (24 KB of LDS each, several blocks per CU) rather than 16
-// blocks of 4096 (96 KB, one per CU), so its passes fill the chip.
-constexpr int kSingleTile = 4096;
-
-// LDS position of tile element i: one padding word after every 32, so that the
-// bit-reversed loads (whose first 64 positions are multiples of the tile length / 64)
-// and the butterflies at small strides spread over the banks instead of meeting on a
-// few of them.
+// LDS position of tile element i: one padding element after every 32, so that accesses at
+// strides of powers of two spread over the banks.
 __device__ __forceinline__ int lp(int i) { return i + (i >> 5); }
 template <int TILE>
 constexpr int lds_len() { return TILE + TILE / 32; }
 
-__device__ __forceinline__ uint32_t bitrev(uint32_t x, int bits)
+// A thread holds 2^EB elements and takes up to EB stages between two trips through LDS: a
+// transform of length 2^LG is a few rounds of decimation in frequency with radices
+// 2^round_bits(LG, EB, round), each round's DFTs in registers.  Element s of the tile
+// after a round is block b (the digits of the frequency found so far, first digit most
+// significant) times the remaining length plus the index within it, so a round reads and
+// writes the same places and the last one's outputs sit at digit-reversed frequencies.
+constexpr int n_rounds(int lg, int eb) { return (lg + eb - 1) / eb; }
+constexpr int round_bits(int lg, int eb, int round)
 {
-    return bits ? (__brev(x) >> (32 - bits)) : 0u;
+    return lg / n_rounds(lg, eb) + (round < lg % n_rounds(lg, eb) ? 1 : 0);
+}
+constexpr int bits_before(int lg, int eb, int round)
+{
+    int b = 0;
+    for (int i = 0; i < round; ++i) b += round_bits(lg, eb, i);
+    return b;
+}
+constexpr int pass_threads(int lg, int lc, int eb) { return (1 << (lg + lc)) >> eb < 64 ? 64 : (1 << (lg + lc)) >> eb; }
+
+constexpr int brev_bits(int x, int bits)
+{
+    int r = 0;
+    for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1) << (bits - 1 - i);
+    return r;
 }
 
-// Copies w_L^j (j < L / 2, L = 2^log2L) from the table tw[k] = w_T^k, T = 2^log2T, into
-// LDS; every stage of a length-L transform takes its twiddles from there.
-template <int NT, class T>
-__device__ __forceinline__ void load_stage_twiddles(T *stw, int log2L, const T *__restrict__ tw, int log2T)
+// One round of the tile's transforms (see above).  src(n, c) supplies the first round's
+// inputs, dst(f, c, k, value) takes the last one's outputs (k counts a DFT's, whose
+// frequencies f are an arithmetic progression); s is the tile in LDS, root(e) the power
+// w_L^e, Dft the ring's register DFTs.
+template <int LG, int LC, int EB, int ROUND, class Dft, class T, class Root, class Src, class Dst>
+__device__ __forceinline__ void pass_round(T *s, const Dft &D, Root &&root, Src &&src, Dst &&dst)
 {
-    for (int j = threadIdx.x; j < (1 << (log2L - 1)); j += NT) stw[j] = tw[(size_t)j << (log2T - log2L)];
+    constexpr int NR = n_rounds(LG, EB), RB = round_bits(LG, EB, ROUND), N = 1 << RB;
+    constexpr int done = bits_before(LG, EB, ROUND);
+    constexpr int LJ = LG - done, LN = LJ - RB;  // log2 of the length before and after the round
+    constexpr bool first = ROUND == 0, last = ROUND == NR - 1;
+    constexpr int NT = pass_threads(LG, LC, EB);
+    constexpr int groups = 1 << (LG + LC - RB);
+#pragma unroll
+    for (int g0 = 0; g0 < groups; g0 += NT) {
+        const int g = g0 + threadIdx.x;
+        if (groups < NT && g >= groups) break;
+        const int c = g & ((1 << LC) - 1), h = g >> LC;
+        // middle rounds: h = block * 2^LN + index; last round: h counts the blocks by their
+        // frequency, first digit fastest, so that neighbouring lanes store neighbours
+        int blk = h >> LN, i = h & ((1 << LN) - 1);
+        if (last && NR > 2) {
+            blk = 0;
+#pragma unroll
+            for (int q = 0; q < NR - 1; ++q) {
+                const int digit = (h >> bits_before(LG, EB, q)) & ((1 << round_bits(LG, EB, q)) - 1);
+                blk = (blk << round_bits(LG, EB, q)) | digit;
+            }
+        }
+        const int at = (((blk << LJ) + i) << LC) + c;  // element k at at + k 2^(LN + LC)
+        T x[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if constexpr (first) x[k] = src(i + (k << LN), c);
+            else x[k] = s[lp(at + (k << (LN + LC)))];
+        }
+        D.template dft<RB, !last>(x);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const T v = x[brev_bits(k, RB)];  // frequency digit k
+            if constexpr (last) dst(h + (k << done), c, k, v);
+            else s[lp(at + (k << (LN + LC)))] = k == 0 ? D.settle(v) : D.mul(v, root((i * k) << (LG - LJ)));
+        }
+    }
 }
 
-// Radix-2 DIT stages on C interleaved transforms of length 2^log2L held in LDS as
-// s[lp(n * C + c)] (bit-reversed input, natural output); stw from load_stage_twiddles.
-// Stages go in pairs: a thread takes the four elements two consecutive stages combine,
-// applies both stages' radix-2 butterflies in registers (the same operations as two
-// separate stages, so the same rounding), and writes them back once.
-//
-// Addressing: with D = half * C the tile distance between a group's elements, group b
-// starts at idx0 = ((b >> log2 D) << (log2 D + 2)) + (b & (D - 1)), and its block of 4D
-// tile positions starts at a multiple of 4D.  A power-of-two block of at most 32
-// positions then lies inside one 32-position stretch, and larger ones start on one, so
-// element j sits jD + (jD >> 5) padded positions after element 0 for every group: one
-// padded address per group, the other three at offsets uniform over the stage.
-template <int NT, class Ring>
-__device__ __forceinline__ void lds_stages(typename Ring::T *s, int log2L, int log2C, const Ring &R,
-                                           const typename Ring::T *stw)
+// Every round of a pass from ROUND on.
+template <int LG, int LC, int EB, int ROUND = 0, class Dft, class T, class Root, class Src, class Dst>
+__device__ __forceinline__ void pass_rounds(T *s, Dft &D, Root &&root, Src &&src, Dst &&dst)
 {
-    using T = typename Ring::T;
-    int lh = 0;
-    for (; lh + 1 < log2L; lh += 2) {
-        const int sD = lh + log2C;
-        const int D = 1 << sD;
-        const int o1 = D + (D >> 5), o2 = 2 * D + ((2 * D) >> 5), o3 = 3 * D + ((3 * D) >> 5);
-        const int sh2 = log2L - lh - 2;           // twiddle index shift of the second stage
-        const int quarter = 1 << (log2L - 2);     // (k + half) << sh2 = (k << sh2) + quarter
-        const int kmask = (1 << lh) - 1;
-        const int ngr = (1 << (log2L - 2)) << log2C;
-        for (int b = threadIdx.x; b < ngr; b += NT) {
-            T *e = s + lp(((b >> sD) << (sD + 2)) + (b & (D - 1)));
-            const int w2i = ((b >> log2C) & kmask) << sh2;
-            const T x0 = e[0], x1 = e[o1], x2 = e[o2], x3 = e[o3];
-            // stage lh: pairs (0, 1) and (2, 3), twiddle w_{2 half}^k
-            const T w1 = stw[w2i << 1];
-            T v = R.mul(x1, w1);
-            const T y0 = R.add(x0, v), y1 = R.sub(x0, v);
-            v = R.mul(x3, w1);
-            const T y2 = R.add(x2, v), y3 = R.sub(x2, v);
-            // stage lh + 1: pairs (0, 2) with w_{4 half}^k and (1, 3) with w_{4 half}^(k + half)
-            const T w2 = stw[w2i];
-            const T w3 = stw[w2i + quarter];
-            v = R.mul(y2, w2);
-            e[0] = R.add(y0, v);
-            e[o2] = R.sub(y0, v);
-            v = R.mul(y3, w3);
-            e[o1] = R.add(y1, v);
-            e[o3] = R.sub(y1, v);
-        }
-        __syncthreads();
-    }
-    for (; lh < log2L; ++lh) {  // the last stage when their number is odd
-        const int sD = lh + log2C;
-        const int D = 1 << sD;
-        const int o1 = D + (D >> 5);
-        const int sh = log2L - lh - 1;
-        const int kmask = (1 << lh) - 1;
-        const int nbf = (1 << (log2L - 1)) << log2C;
-        for (int b = threadIdx.x; b < nbf; b += NT) {
-            T *e = s + lp(((b >> sD) << (sD + 1)) + (b & (D - 1)));
-            const T u = e[0];
-            const T v = R.mul(e[o1], stw[((b >> log2C) & kmask) << sh]);
-            e[0] = R.add(u, v);
-            e[o1] = R.sub(u, v);
-        }
-        __syncthreads();
-    }
+    if constexpr (ROUND > 0) __syncthreads();
+    D.template load_roots<round_bits(LG, EB, ROUND)>();
+    pass_round<LG, LC, EB, ROUND>(s, D, root, src, dst);
+    if constexpr (ROUND + 1 < n_rounds(LG, EB)) pass_rounds<LG, LC, EB, ROUND + 1>(s, D, root, src, dst);
 }
 
 // ---------------------------------------------------------------- fp64 complex FFT pass
@@ -131,53 +122,77 @@ struct F64Src {
     const int64_t *const *im;  // [n_vec] sketch loaded as the imaginary part (entry null: 0)
 };
 
-template <int TILE>
-__global__ __launch_bounds__(TILE / 4) void k_fft_f64(F64Src src, double2 *buf, PassGeom g,
-                                                     const double2 *__restrict__ tw, int log2T,
-                                                     const double2 *__restrict__ stage, int log2S)
+// Register DFTs of complex doubles, decimation in frequency: x[k] in, frequency
+// brev_bits(k) in x[k] out.  Along any path of a round of RB stages there are at most RB
+// complex products, the round's twiddle among them (the last stage's is by 1), as in RB
+// radix-2 stages: the error bound of the estimate counts one per stage.
+struct DftC {
+    const double2 *stage;  // w_(2^log2S) powers
+    int log2S;
+    double2 w[8];
+    RingC R;
+    template <int RB>
+    __device__ __forceinline__ void load_roots()
+    {
+#pragma unroll
+        for (int j = 0; j < (1 << RB) / 2; ++j) w[j] = stage[(size_t)j << (log2S - RB)];
+    }
+    __device__ __forceinline__ double2 settle(double2 v) const { return v; }
+    __device__ __forceinline__ double2 mul(double2 v, double2 t) const { return R.mul(v, t); }
+    template <int RB, bool LAZY>
+    __device__ __forceinline__ void dft(double2 (&x)[1 << RB]) const
+    {
+        constexpr int N = 1 << RB;
+#pragma unroll
+        for (int st = 0; st < RB; ++st) {
+            const int half = N >> (st + 1);
+#pragma unroll
+            for (int b = 0; b < N; b += 2 * half)
+#pragma unroll
+                for (int k = 0; k < half; ++k) {
+                    const double2 a = x[b + k], c = x[b + k + half];
+                    x[b + k] = R.add(a, c);
+                    const double2 v = R.sub(a, c);
+                    // w_4 = -i exactly
+                    x[b + k + half] = k == 0          ? v
+                                      : 2 * k == half ? make_double2(v.y, -v.x)
+                                                      : R.mul(v, w[k << st]);
+                }
+        }
+    }
+};
+
+// One pass: a block transforms 2^LC interleaved columns of length 2^LG.  Bound by memory
+// (16 bytes read and written per element: the row pass at 5 TB/s, the column pass, whose
+// sources are runs of 128 bytes, at 3.6; 38 vectors of 2^18 take 64 and 88 us, 106 each
+// with two stages per trip through LDS).  The stage roots are read through the cache: in LDS
+// they would take as much of it as the tile and halve the blocks per CU.
+template <int LG, int LC, int EB>
+__global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_fft_f64(F64Src src, double2 *buf, PassGeom g,
+                                                                  const double2 *__restrict__ columns,
+                                                                  const double2 *__restrict__ stage, int log2S)
 {
-    constexpr int NT = TILE / 4;
-    __shared__ double2 s[lds_len<TILE>()];
-    __shared__ double2 stw[TILE / 2];
+    __shared__ double2 s[n_rounds(LG, EB) > 1 ? lds_len<(1 << (LG + LC))>() : 1];
     const int v = blockIdx.x;
     const int blk = blockIdx.y;
-    const int C = 1 << g.log2C;
-    const int L = 1 << g.log2L;
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     double2 *vec = buf + (size_t)v * m;
-    const int total = L << g.log2C;
-    if (src.re) {
-        const int64_t *re = src.re[v];
-        const int64_t *im = src.im[v];
-        for (int idx = threadIdx.x; idx < total; idx += NT) {
-            const int n = idx >> g.log2C, c = idx & (C - 1);
-            const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-            s[lp((bitrev(n, g.log2L) << g.log2C) + c)] =
-                make_double2((double)re[pos], im ? (double)im[pos] : 0.0);
-        }
-    } else {
-        for (int idx = threadIdx.x; idx < total; idx += NT) {
-            const int n = idx >> g.log2C, c = idx & (C - 1);
-            const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-            s[lp((bitrev(n, g.log2L) << g.log2C) + c)] = vec[pos];
-        }
-    }
-    load_stage_twiddles<NT>(stw, g.log2L, stage, log2S);
-    __syncthreads();
-    RingC R;
-    lds_stages<NT, RingC>(s, g.log2L, g.log2C, R, stw);
-    for (int idx = threadIdx.x; idx < total; idx += NT) {
-        const int n = idx >> g.log2C, c = idx & (C - 1);
+    const int64_t *re = src.re ? src.re[v] : nullptr;
+    const int64_t *im = src.re ? src.im[v] : nullptr;
+    auto load = [&](int n, int c) {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-        double2 val = s[lp((n << g.log2C) + c)];
-        if (g.twiddle) {
-            const int64_t colid = (int64_t)blk * C + c;
-            const int64_t e = ((int64_t)n * colid) & (m - 1);
-            val = R.mul(val, tw[(size_t)e << (log2T - g.log2m)]);
-        }
-        vec[pos] = val;
-    }
+        return re ? make_double2((double)re[pos], im ? (double)im[pos] : 0.0) : vec[pos];
+    };
+    DftC D{stage, log2S};
+    auto store = [&](int f, int c, int k, double2 val) {
+        // w_m^(f column), from the table in tile order: looked up in the table of powers, a
+        // tile's 2^11 twiddles lie in as many cache lines
+        if (g.twiddle) val = D.R.mul(val, columns[((size_t)blk << (LG + LC)) + ((size_t)f << LC) + c]);
+        vec[base + (int64_t)c * g.col_stride + (int64_t)f * g.elem_stride] = val;
+    };
+    auto root = [&](int e) { return stage[(size_t)e << (log2S - LG)]; };
+    pass_rounds<LG, LC, EB>(s, D, root, load, store);
 }
 
 // ---------------------------------------------------------------- NTT pass
@@ -186,145 +201,97 @@ struct ModSrc {
     const int64_t *const *ptr;  // [vec_per_prime] sketch of vector v % vec_per_prime (null: in place)
 };
 
-// The NTT holds sixteen elements per thread and takes up to four stages between two trips
-// through LDS: a transform of length 2^LG is one to three rounds of decimation in frequency
-// with radices 2^rbits(LG, round), each round's DFTs in registers.  Element s of the tile
-// after a round is block b (the digits of the frequency found so far, first digit most
-// significant) times the remaining length plus the index within it, so a round reads and
-// writes the same places and the last one's outputs sit at digit-reversed frequencies.
-constexpr int kNttE = 16;  // elements per thread
-constexpr int ntt_rounds(int lg) { return lg <= 4 ? 1 : lg <= 8 ? 2 : 3; }
-constexpr int ntt_rbits(int lg, int round)
-{
-    return ntt_rounds(lg) == 1   ? lg
-           : ntt_rounds(lg) == 2 ? (round == 0 ? (lg + 1) / 2 : lg / 2)
-                                 : (round == 0 ? (lg + 2) / 3 : round == 1 ? (lg + 1) / 3 : lg / 3);
-}
-constexpr int ntt_threads(int lg, int lc) { return (1 << (lg + lc)) / kNttE < 64 ? 64 : (1 << (lg + lc)) / kNttE; }
-
-// DFT of length 2^RB in registers, decimation in frequency: x[k] in, frequency bitrev(k)
-// in x[k] out.  w[j] = w_R^j, j < R / 2.  Inputs below p.  The last stage's results are
-// below 2p when `lazy` (a twiddle multiplies them next), else below p.
-template <int RB, bool LAZY>
-__device__ __forceinline__ void dft_regs(uint32_t (&x)[1 << RB], const RingM &R, const uint32_t *w)
-{
-    constexpr int N = 1 << RB;
+// Register DFTs of residues.  Inputs below p; the last stage's results are below 2p when
+// LAZY (a twiddle multiplies them next), else below p.
+struct DftM {
+    RingM R;
+    const uint32_t *stage;  // w_(2^log2S) powers
+    int log2S;
+    uint32_t w[8];
+    template <int RB>
+    __device__ __forceinline__ void load_roots()
+    {
 #pragma unroll
-    for (int st = 0; st < RB; ++st) {
-        const int half = N >> (st + 1);
-        const bool last = st == RB - 1;
-#pragma unroll
-        for (int b = 0; b < N; b += 2 * half)
-#pragma unroll
-            for (int k = 0; k < half; ++k) {
-                const uint32_t a = x[b + k], c = x[b + k + half];
-                const uint32_t u = a + c, v = a - c + R.p;  // both below 2p
-                x[b + k] = LAZY && last ? u : min(u, u - R.p);
-                // w_{2 half}^k = w_N^(k N / (2 half))
-                x[b + k + half] = k == 0 ? (LAZY && last ? v : min(v, v - R.p)) : R.mul(v, w[k << st]);
-            }
+        for (int j = 0; j < (1 << RB) / 2; ++j) w[j] = stage[(size_t)j << (log2S - RB)];
     }
-}
-
-constexpr int brev_bits(int x, int bits)
-{
-    int r = 0;
-    for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1) << (bits - 1 - i);
-    return r;
-}
-
-// One round of the tile's transforms (see above).  src(n, c) supplies the first round's
-// inputs, dst(f, c, value) takes the last one's outputs; s is the tile in LDS, stw the
-// powers of w_L.  Every thread of the block calls it.
-template <int LG, int LC, int ROUND, class Src, class Dst>
-__device__ __forceinline__ void ntt_round(uint32_t *s, const uint32_t *stw, const RingM &R, const uint32_t *wr,
-                                          Src &&src, Dst &&dst)
-{
-    constexpr int NR = ntt_rounds(LG), RB = ntt_rbits(LG, ROUND), N = 1 << RB;
-    constexpr int done = ROUND == 0 ? 0 : ROUND == 1 ? ntt_rbits(LG, 0) : ntt_rbits(LG, 0) + ntt_rbits(LG, 1);
-    constexpr int LJ = LG - done, LN = LJ - RB;  // log2 of the length before and after the round
-    constexpr bool first = ROUND == 0, last = ROUND == NR - 1;
-    constexpr int NT = ntt_threads(LG, LC);
-    constexpr int groups = 1 << (LG + LC - RB);
+    __device__ __forceinline__ uint32_t settle(uint32_t v) const { return min(v, v - R.p); }
+    __device__ __forceinline__ uint32_t mul(uint32_t v, uint32_t t) const { return R.mul(v, t); }
+    template <int RB, bool LAZY>
+    __device__ __forceinline__ void dft(uint32_t (&x)[1 << RB]) const
+    {
+        constexpr int N = 1 << RB;
 #pragma unroll
-    for (int g0 = 0; g0 < groups; g0 += NT) {
-        const int g = g0 + threadIdx.x;
-        if (groups < NT && g >= groups) break;
-        const int c = g & ((1 << LC) - 1), h = g >> LC;
-        // middle rounds: h = block * 2^LN + index; last round: h counts the blocks by their
-        // frequency, first digit fastest, so that neighbouring lanes store neighbours
-        int blk = h >> LN, i = h & ((1 << LN) - 1);
-        if (last && NR == 3) {
-            constexpr int r0 = ntt_rbits(LG, 0), r1 = ntt_rbits(LG, 1);
-            blk = ((h & ((1 << r0) - 1)) << r1) | (h >> r0);
-        }
-        const int at = (((blk << LJ) + i) << LC) + c;  // element k at at + k 2^(LN + LC)
-        uint32_t x[N];
+        for (int st = 0; st < RB; ++st) {
+            const int half = N >> (st + 1);
+            const bool lazy = LAZY && st == RB - 1;
 #pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = first ? src(i + (k << LN), c) : s[lp(at + (k << (LN + LC)))];
-        dft_regs<RB, !last>(x, R, wr);
-        if (last) {
+            for (int b = 0; b < N; b += 2 * half)
 #pragma unroll
-            for (int k = 0; k < N; ++k) dst(h + (k << done), c, k, x[brev_bits(k, RB)]);
-        } else {
-            // frequency digit k of index i: times w_(2^LJ)^(i k)
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                uint32_t v = x[brev_bits(k, RB)];
-                v = k == 0 ? min(v, v - R.p) : R.mul(v, stw[(i * k) << (LG - LJ)]);
-                s[lp(at + (k << (LN + LC)))] = v;
-            }
+                for (int k = 0; k < half; ++k) {
+                    const uint32_t a = x[b + k], c = x[b + k + half];
+                    const uint32_t u = a + c, v = a - c + R.p;  // both below 2p
+                    x[b + k] = lazy ? u : settle(u);
+                    // w_(2 half)^k = w_N^(k 2^st)
+                    x[b + k + half] = k == 0 ? (lazy ? v : settle(v)) : R.mul(v, w[k << st]);
+                }
         }
     }
-}
+};
 
 // One pass: a block transforms 2^LC interleaved columns of length 2^LG.  Bound by the vector
 // unit and memory about equally.  Two stages per trip through LDS with four elements per
 // thread cost as much address arithmetic, LDS instructions and barriers as butterflies:
 // 15 vectors of 2^21 at 3 primes took 213 us (columns) and 144 us (rows), 97 and 103 us in
 // registers.
-template <int LG, int LC>
-__global__ __launch_bounds__(ntt_threads(LG, LC)) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime,
-                                                             const PrimeDev *__restrict__ primes,
-                                                             const uint32_t *__restrict__ roots, int log2T,
-                                                             const uint32_t *__restrict__ stage, int log2S, int inverse)
+template <int LG, int LC, int EB>
+__global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime, int n_primes,
+                                                              const PrimeDev *__restrict__ primes,
+                                                              const uint32_t *__restrict__ roots, int log2T,
+                                                              const uint32_t *__restrict__ stage, int log2S, int inverse)
 {
-    constexpr int TILE = 1 << (LG + LC), NT = ntt_threads(LG, LC), NR = ntt_rounds(LG);
-    __shared__ uint32_t s[NR > 1 ? lds_len<TILE>() + 1 : 1];
-    __shared__ uint32_t stw[NR > 1 ? 1 << LG : 1];
-    const int v = blockIdx.x;
-    const int pi = v / vec_per_prime;
+    constexpr int TILE = 1 << (LG + LC), NT = pass_threads(LG, LC, EB), NR = n_rounds(LG, EB);
+    __shared__ uint32_t s[NR > 1 ? lds_len<TILE>() : 1];
+    __shared__ uint32_t stw[NR > 1 ? 1 << LG : 1];  // w_L^e
+    // Workgroups go to the 8 XCDs round-robin.  When the sketches are read, the primes of
+    // one tile follow each other on one XCD, whose L2 then fetches its int64 values once.
+    int pi, j, blk;
+    {
+        const uint32_t tiles = (uint32_t)vec_per_prime * g.blocks, id = blockIdx.x;
+        uint32_t tile;
+        if (src.ptr && (tiles & 7) == 0) {
+            const uint32_t w = id >> 3, K = n_primes;
+            pi = (int)(w % K);
+            tile = (w / K) * 8 + (id & 7);
+        } else {
+            pi = (int)(id / tiles);
+            tile = id % tiles;
+        }
+        j = (int)(tile / g.blocks);
+        blk = (int)(tile % g.blocks);
+    }
+    const int v = pi * vec_per_prime + j;
     const PrimeDev &P = primes[pi];  // by reference: a copy with minv[] indexed would live in scratch
     const RingM R{P.p, P.pinv_neg};
     const uint32_t *tw = roots + ((size_t)(2 * pi + inverse) << log2T);
-    const uint32_t *st = stage + ((size_t)(2 * pi + inverse) << log2S);
-    const int blk = blockIdx.y;
+    DftM D{R, stage + ((size_t)(2 * pi + inverse) << log2S), log2S};
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     uint32_t *vec = buf + (size_t)v * m;
-    if (NR > 1)
-        for (int e = threadIdx.x; e < (1 << LG); e += NT) stw[e] = st[(size_t)e << (log2S - LG)];
-    // roots of the register DFTs: w_R^j from the table's quarter-length entries (uniform)
-    constexpr int RB0 = ntt_rbits(LG, 0), RB1 = NR > 1 ? ntt_rbits(LG, 1) : 1, RB2 = NR > 2 ? ntt_rbits(LG, 2) : 1;
-    auto small_roots = [&](uint32_t *w, int rb) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = j < (1 << rb) / 2 ? st[(size_t)j << (log2S - rb)] : 0u;
-    };
-    const int64_t *in = src.ptr ? src.ptr[v % vec_per_prime] : nullptr;
+    const int64_t *in = src.ptr ? src.ptr[j] : nullptr;
     auto load = [&](int n, int c) {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
         return in ? mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64) : vec[pos];
     };
     // Output n of column c is multiplied by w_m^(n colid): a thread's outputs are an
-    // arithmetic progression in n (frequencies f0 + k step), so two entries of the long
-    // table, w^(f0 colid) and w^(step colid), give them all by one product each.  Exact
-    // arithmetic: the same residues as one lookup per element.
+    // arithmetic progression in n, so two entries of the long table, w^(f0 colid) and
+    // w^(step colid), give them all by one product each.  Exact arithmetic: the same
+    // residues as one lookup per element.
     const int sh = log2T - g.log2m;
     uint32_t t_cur = 0, t_step = 0;
     auto store = [&](int f, int c, int k, uint32_t val) {
         if (g.twiddle) {
             if (k == 0) {
-                constexpr int step = 1 << (LG - (NR == 1 ? RB0 : NR == 2 ? RB1 : RB2));
+                constexpr int step = 1 << (LG - round_bits(LG, EB, NR - 1));
                 const int64_t col = ((int64_t)blk << LC) + c;
                 t_cur = tw[(size_t)((f * col) & (m - 1)) << sh];
                 t_step = tw[(size_t)((step * col) & (m - 1)) << sh];
@@ -336,20 +303,11 @@ __global__ __launch_bounds__(ntt_threads(LG, LC)) void k_ntt(ModSrc src, uint32_
         if (g.scale) val = R.mul(val, P.minv[g.log2m]);
         vec[base + (int64_t)c * g.col_stride + (int64_t)f * g.elem_stride] = val;
     };
-    uint32_t w[8];
-    small_roots(w, RB0);
-    if constexpr (NR > 1) __syncthreads();  // stw
-    ntt_round<LG, LC, 0>(s, stw, R, w, load, store);
     if constexpr (NR > 1) {
+        for (int e = threadIdx.x; e < (1 << LG); e += NT) stw[e] = D.stage[(size_t)e << (log2S - LG)];
         __syncthreads();
-        if constexpr (RB1 != RB0) small_roots(w, RB1);
-        ntt_round<LG, LC, 1>(s, stw, R, w, load, store);
     }
-    if constexpr (NR > 2) {
-        __syncthreads();
-        if constexpr (RB2 != RB1) small_roots(w, RB2);
-        ntt_round<LG, LC, 2>(s, stw, R, w, load, store);
-    }
+    pass_rounds<LG, LC, EB>(s, D, [&](int e) { return stw[e]; }, load, store);
 }
 
 // Two-pass lengths: tiles of N2 = 2^S elements, columns of N1 = 2^(log2m - S) <= N2.
@@ -381,17 +339,6 @@ PassGeom row_pass(int log2m, int S, bool twiddle)
     return g;
 }
 
-// Launch of one pass with the tile its geometry needs (single pass: the whole vector in
-// one 4096-element tile; two-pass lengths: 2^S elements).
-template <class F>
-void with_tile(const PassGeom &g, bool single, F &&f)
-{
-    const int tile_bits = g.log2L + g.log2C;  // = S for both passes
-    if (single || tile_bits == 12) f(std::integral_constant<int, kSingleTile>{});
-    else if (tile_bits == 10) f(std::integral_constant<int, 1024>{});
-    else f(std::integral_constant<int, 2048>{});
-}
-
 PassGeom single_pass(int log2m)
 {
     PassGeom g{};
@@ -412,91 +359,137 @@ int split_for(int device, int log2m)
     return t && split_ok(log2m, t) ? t : default_split_bits(log2m);
 }
 
+namespace {
+// Columns per block: the NTT reads runs of 4-byte residues (8 bytes from the sketches), 32
+// columns up to length 2^8 and 16 beyond (tiles of at most 2^14 residues, 64 KB of LDS);
+// the FFT runs of 16-byte elements, 16 columns down to 4 (tiles of 2^11 or 2^12, at most
+// 66 KB).  The decomposition, and with it the output order, is the same for both.
+constexpr int ntt_log2c(int lg) { return lg <= 8 ? 5 : 4; }
+constexpr int fft_log2c(int lg) { return lg <= 7 ? 4 : lg <= 9 ? 3 : 2; }
+
+// log2 of the elements per thread, measured (microseconds; 38 complex vectors, 76 x 3
+// residue vectors):                    2^18          2^16 (15, 30)   2^10 (2, 4 x 3)
+//   fft columns  4 / 8 / 16            87 / 102 / 148   9 / 12 / 17
+//   fft rows                           74 / 64 / 59     9.8 / 8.3 / 8.8   4.5 / 5.3 / 8.2
+//   ntt columns                        273 / 200 / 175  21 / 19.5 / 19.2
+//   ntt rows                           193 / 136 / 153  19.4 / 19 / 22    4.5 / 5.8 / 8.9
+// Single passes up to 2^10 run on few workgroups, where a thread's chain counts, and the
+// int64 sources of the fp64 columns want the loads of many wavefronts.
+constexpr int fft_elems(int lg, int lc, bool single) { return lc > 0 || (single && lg <= 10) ? 2 : 3; }
+constexpr int ntt_elems(int lg, int lc, bool single) { return lc > 0 && lg >= 7 ? 4 : single && lg <= 10 ? 2 : 3; }
+PassGeom with_columns(PassGeom g, int log2c)
+{
+    g.blocks = (g.blocks << g.log2C) >> log2c;
+    g.log2C = log2c;
+    g.block_stride = (int64_t)1 << log2c;
+    return g;
+}
+
+// f(log2L, row, single) as integral constants.  Row and single passes have one column; two-pass
+// rows are 2^10 to 2^12 long, the columns of lengths up to 2^21 at most 2^10.
+template <class F>
+hipError_t with_length(const PassGeom &g, F &&f)
+{
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+    if (g.log2C > 0) {
+        switch (g.log2L) {
+#define CSK_LENGTH(LG, ROW, SINGLE) \
+    case LG: f(std::integral_constant<int, LG>{}, ROW{}, SINGLE{}); break;
+            CSK_LENGTH(1, F_, F_)
+            CSK_LENGTH(2, F_, F_)
+            CSK_LENGTH(3, F_, F_)
+            CSK_LENGTH(4, F_, F_)
+            CSK_LENGTH(5, F_, F_)
+            CSK_LENGTH(6, F_, F_)
+            CSK_LENGTH(7, F_, F_)
+            CSK_LENGTH(8, F_, F_)
+            CSK_LENGTH(9, F_, F_)
+            CSK_LENGTH(10, F_, F_)
+            default: return hipErrorInvalidValue;
+        }
+    } else if (g.blocks == 1) {
+        switch (g.log2L) {
+            CSK_LENGTH(1, T_, T_)
+            CSK_LENGTH(2, T_, T_)
+            CSK_LENGTH(3, T_, T_)
+            CSK_LENGTH(4, T_, T_)
+            CSK_LENGTH(5, T_, T_)
+            CSK_LENGTH(6, T_, T_)
+            CSK_LENGTH(7, T_, T_)
+            CSK_LENGTH(8, T_, T_)
+            CSK_LENGTH(9, T_, T_)
+            CSK_LENGTH(10, T_, T_)
+            CSK_LENGTH(11, T_, T_)
+            CSK_LENGTH(12, T_, T_)
+            default: return hipErrorInvalidValue;
+        }
+    } else {
+        switch (g.log2L) {
+            CSK_LENGTH(10, T_, F_)
+            CSK_LENGTH(11, T_, F_)
+            CSK_LENGTH(12, T_, F_)
+            default: return hipErrorInvalidValue;
+        }
+    }
+#undef CSK_LENGTH
+    return hipGetLastError();
+}
+
+hipError_t fft_pass(const PassGeom &g, const F64Src &src, int n_vec, double2 *buf, const TwiddleTables &tw,
+                    hipStream_t s)
+{
+    return with_length(g, [&](auto lg, auto row, auto single) {
+        constexpr int LG = decltype(lg)::value, LC = decltype(row)::value ? 0 : fft_log2c(LG);
+        constexpr int EB = fft_elems(LG, LC, decltype(single)::value);
+        hipLaunchKernelGGL((k_fft_f64<LG, LC, EB>), dim3(n_vec, g.blocks), dim3(pass_threads(LG, LC, EB)), 0, s, src, buf, g,
+                           tw.columns, tw.stage, tw.log2S);
+    });
+}
+
+__global__ void k_column_twiddles(double2 *out, const double2 *__restrict__ tw, int log2m, int log2L, int log2C)
+{
+    const uint32_t m = 1u << log2m;
+    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
+        const uint32_t c = j & ((1u << log2C) - 1), f = (j >> log2C) & ((1u << log2L) - 1);
+        const uint32_t col = ((j >> (log2C + log2L)) << log2C) + c;
+        out[j] = tw[(uint32_t)(((uint64_t)f * col) & (m - 1))];
+    }
+}
+
+hipError_t ntt_pass(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
+                    const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
+{
+    return with_length(g, [&](auto lg, auto row, auto single) {
+        constexpr int LG = decltype(lg)::value, LC = decltype(row)::value ? 0 : ntt_log2c(LG);
+        constexpr int EB = ntt_elems(LG, LC, decltype(single)::value);
+        hipLaunchKernelGGL((k_ntt<LG, LC, EB>), dim3((unsigned)n_vec * g.blocks), dim3(pass_threads(LG, LC, EB)), 0, s,
+                           src, buf, g, vec_per_prime, n_vec / vec_per_prime, primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
+    });
+}
+}  // namespace
+
+cs_status column_twiddles(double2 *out, const double2 *tw, int log2m, int S, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_column_twiddles, dim3(1024), dim3(256), 0, s, out, tw, log2m, log2m - S, fft_log2c(log2m - S));
+    CSK_HIP(hipGetLastError());
+    return CS_OK;
+}
+
 cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
                           int S, const TwiddleTables &tw, hipStream_t s)
 {
     if (n_vec == 0) return CS_OK;
     F64Src first{re, im};
     F64Src self{nullptr, nullptr};
-    auto pass = [&](const PassGeom &g, bool single, const F64Src &src) {
-        with_tile(g, single, [&](auto tile) {
-            constexpr int T = decltype(tile)::value;
-            hipLaunchKernelGGL(k_fft_f64<T>, dim3(n_vec, g.blocks), dim3(T / 4), 0, s, src, buf, g, tw.full, tw.log2T,
-                               tw.stage, tw.log2S);
-        });
-        return hipGetLastError();
-    };
     if (log2m <= 12) {
-        CSK_HIP(pass(single_pass(log2m), true, first));
+        CSK_HIP(fft_pass(single_pass(log2m), first, n_vec, buf, tw, s));
         return CS_OK;
     }
-    CSK_HIP(pass(column_pass(log2m, S, true), false, first));
-    CSK_HIP(pass(row_pass(log2m, S, false), false, self));
+    CSK_HIP(fft_pass(with_columns(column_pass(log2m, S, true), fft_log2c(log2m - S)), first, n_vec, buf, tw, s));
+    CSK_HIP(fft_pass(row_pass(log2m, S, false), self, n_vec, buf, tw, s));
     return CS_OK;
 }
-
-namespace {
-// The column pass of the NTT reads its columns in runs of C 4-byte residues (8 bytes from
-// the sketches): 32 columns per block up to length 2^8, 16 beyond (tiles of at most 2^14
-// residues, 64 KB of LDS).  The decomposition, and with it the output order, is the
-// same as with the fp64 FFT's narrower blocks.
-constexpr int ntt_log2c(int lg) { return lg <= 8 ? 5 : 4; }
-PassGeom widen_columns(PassGeom g)
-{
-    const int c = ntt_log2c(g.log2L);
-    g.blocks = (g.blocks << g.log2C) >> c;
-    g.log2C = c;
-    g.block_stride = (int64_t)1 << c;
-    return g;
-}
-
-template <int LG, bool ROW>
-void ntt_launch(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
-                const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
-{
-    constexpr int LC = ROW ? 0 : ntt_log2c(LG);
-    hipLaunchKernelGGL((k_ntt<LG, LC>), dim3(n_vec, g.blocks), dim3(ntt_threads(LG, LC)), 0, s, src, buf, g,
-                       vec_per_prime, primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
-}
-
-// Row (and single) passes have one column; two-pass rows are 2^10 to 2^12 long, the columns
-// of lengths up to 2^21 at most 2^10.
-hipError_t ntt_pass(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *buf, int vec_per_prime,
-                    const PrimeDev *primes, const ModTables &roots, int inverse, hipStream_t s)
-{
-    auto go = [&](auto lg, auto row) {
-        ntt_launch<decltype(lg)::value, decltype(row)::value>(g, src, n_vec, buf, vec_per_prime, primes, roots, inverse,
-                                                              s);
-    };
-    auto pick = [&](auto row) {
-        switch (g.log2L) {
-#define CSK_NTT_CASE(LG) \
-    case LG: go(std::integral_constant<int, LG>{}, row); break;
-            CSK_NTT_CASE(1)
-            CSK_NTT_CASE(2)
-            CSK_NTT_CASE(3)
-            CSK_NTT_CASE(4)
-            CSK_NTT_CASE(5)
-            CSK_NTT_CASE(6)
-            CSK_NTT_CASE(7)
-            CSK_NTT_CASE(8)
-            CSK_NTT_CASE(9)
-            CSK_NTT_CASE(10)
-            default:
-                if constexpr (decltype(row)::value) {
-                    if (g.log2L == 11) go(std::integral_constant<int, 11>{}, row);
-                    else if (g.log2L == 12) go(std::integral_constant<int, 12>{}, row);
-                    else return hipErrorInvalidValue;
-                } else {
-                    return hipErrorInvalidValue;
-                }
-#undef CSK_NTT_CASE
-        }
-        return hipGetLastError();
-    };
-    return g.log2C == 0 ? pick(std::true_type{}) : pick(std::false_type{});
-}
-}  // namespace
 
 cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
                       const PrimeDev *primes, const ModTables &roots, hipStream_t s)
@@ -510,7 +503,7 @@ cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_prime
         CSK_HIP(ntt_pass(single_pass(log2m), in, n_vec, buf, vec_per_prime, primes, roots, 0, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(widen_columns(column_pass(log2m, S, true)), in, n_vec, buf, vec_per_prime, primes,
+    CSK_HIP(ntt_pass(with_columns(column_pass(log2m, S, true), ntt_log2c(log2m - S)), in, n_vec, buf, vec_per_prime, primes,
                      roots, 0, s));
     CSK_HIP(ntt_pass(row_pass(log2m, S, false), self, n_vec, buf, vec_per_prime, primes, roots, 0, s));
     return CS_OK;
@@ -529,7 +522,7 @@ cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m,
         return CS_OK;
     }
     CSK_HIP(ntt_pass(row_pass(log2m, S, true), self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
-    PassGeom g2 = widen_columns(column_pass(log2m, S, false));
+    PassGeom g2 = with_columns(column_pass(log2m, S, false), ntt_log2c(log2m - S));
     g2.scale = 1;
     CSK_HIP(ntt_pass(g2, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     return CS_OK;
