@@ -201,10 +201,14 @@ cs_status analyze_graph(const cs_graph *g, GraphPlan *out)
             for (int u2 : P.omega[k]) {
                 if (u2 == u) continue;
                 visited[u2] = 1;
-                const int a = alloc();
-                P.ops.push_back({OP_ONES, a, 0});
+                // Hadamard product of the joined attributes' results, from the first one on
+                int a = -1;
                 for (int v : P.gamma[u2]) {
                     const int y = combine(v);
+                    if (a < 0) {
+                        a = y;
+                        continue;
+                    }
                     P.ops.push_back({OP_HAD, a, y});
                     free_regs.push_back(y);
                 }

@@ -239,6 +239,7 @@ struct RepDesc {
 struct QDesc {
     int32_t plan, r, d, log2m, rep_base, nb;
     uint32_t m;
+    int32_t pairwise;  // every component joins two attributes
     // where this query's partials start (its first repetition's spectral sums and
     // residues, each relation's first norm pair): the finalize reads them without going
     // through the repetition and sketch descriptors first
@@ -457,15 +458,6 @@ __global__ void k_mod_load(uint32_t *reg, const int64_t *__restrict__ sk, uint32
         o[j] = mont_from_i64(R, c[j], P.r2, P.r3, P.neg2_64);
 }
 
-__global__ void k_mod_ones(uint32_t *reg, uint32_t m, int d, const PrimeDev *__restrict__ primes)
-{
-    const int v = blockIdx.y;
-    const uint32_t one = primes[v / d].one;
-    uint32_t *o = reg + (size_t)v * m;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += (int64_t)gridDim.x * blockDim.x)
-        o[j] = one;
-}
-
 // dst = dst o src (time domain) or dst[pos] = src[-f] * dst[f] (frequency domain, the
 // pointwise step of the cross-correlation src star dst).
 __global__ void k_mod_mul(uint32_t *dst, const uint32_t *__restrict__ src, uint32_t m, int log2m, int S, int d,
@@ -483,8 +475,26 @@ __global__ void k_mod_mul(uint32_t *dst, const uint32_t *__restrict__ src, uint3
     }
 }
 
-// Sum of register vector (prime i, repetition t) -> partials[i * plane + mod_off(rep) + b].
-__global__ __launch_bounds__(kThreads) void k_mod_sum(const uint32_t *__restrict__ reg, uint32_t m, int d,
+// One vector of Alg. 3's register program where it stands: the sketch itself, residues, or
+// an unfolded linear convolution of length M >= 2m - 1.
+struct ModVal {
+    const int64_t *sketch = nullptr;  // [d][m]
+    const uint32_t *reg = nullptr;    // [K][d][m]
+    const uint32_t *lin = nullptr;    // [K][d][M]
+    uint32_t M = 0;
+    __device__ __forceinline__ uint32_t at(uint32_t j, int v, int t, uint32_t m, const PrimeDev &P, const RingM &R) const
+    {
+        if (sketch) return mont_from_i64(R, sketch[(size_t)t * m + j], P.r2, P.r3, P.neg2_64);
+        if (reg) return reg[(size_t)v * m + j];
+        const uint32_t *l = lin + (size_t)v * M;
+        return j + m < M ? R.add(l[j], l[j + m]) : l[j];
+    }
+};
+
+// Sum over j of a[j] (times b[j] when `two`) of vector (prime i, repetition t) ->
+// partials[i * plane + mod_off(rep) + b]: the last Hadamard product and the SumElements of
+// Alg. 3, converting and folding on the way.
+__global__ __launch_bounds__(kThreads) void k_mod_sum(ModVal a, ModVal b, int two, uint32_t m, int d,
                                                       const PrimeDev *__restrict__ primes, int nb,
                                                       const RepDesc *__restrict__ reps, int rep_base,
                                                       int64_t plane, uint32_t *partials)
@@ -492,11 +502,14 @@ __global__ __launch_bounds__(kThreads) void k_mod_sum(const uint32_t *__restrict
     __shared__ uint32_t sh[kThreads];
     const int v = blockIdx.y;  // i * d + t
     const int pi = v / d, t = v % d;
-    const PrimeDev P = primes[pi];
+    const PrimeDev &P = primes[pi];
     const RingM R{P.p, P.pinv_neg};
-    const uint32_t *a = reg + (size_t)v * m;
     uint32_t acc = 0;
-    for (uint32_t j = blockIdx.x * kThreads + threadIdx.x; j < m; j += (uint32_t)nb * kThreads) acc = R.add(acc, a[j]);
+#pragma unroll 4
+    for (uint32_t j = blockIdx.x * kThreads + threadIdx.x; j < m; j += (uint32_t)nb * kThreads) {
+        const uint32_t x = a.at(j, v, t, m, P, R);
+        acc = R.add(acc, two ? R.mul(x, b.at(j, v, t, m, P, R)) : x);
+    }
     sh[threadIdx.x] = acc;
     __syncthreads();
     for (int s = kThreads / 2; s > 0; s >>= 1) {
@@ -504,21 +517,6 @@ __global__ __launch_bounds__(kThreads) void k_mod_sum(const uint32_t *__restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) partials[(size_t)pi * plane + reps[rep_base + t].mod_off + blockIdx.x] = sh[0];
-}
-
-// Zero-padded copy of length-m register vectors into length-M buffers (M >= 2m - 1, a
-// power of two), reversed (i -> (m - i) mod m) when `reverse`: the operands of a linear
-// convolution whose wrap-around sum is the cross-correlation of Def. 3.1 for any m.
-__global__ void k_mod_pad(uint32_t *out, const uint32_t *__restrict__ in, uint32_t m, uint32_t M, int reverse)
-{
-    const int v = blockIdx.y;
-    const uint32_t *a = in + (size_t)v * m;
-    uint32_t *o = out + (size_t)v * M;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x) {
-        uint32_t val = 0;
-        if (i < m) val = a[reverse ? (i == 0 ? 0 : m - i) : i];
-        o[i] = val;
-    }
 }
 
 // dst[j] = lin[j] + lin[j + m]: the circular (length m) result of a linear one.
@@ -761,13 +759,26 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                             rp.status = 1;
                         }
                     }
-                } else {  // GENERAL: primes to cover 2 * prod_k ||c_k||_1 + 2
-                    double lb = 0.0;
+                } else {
+                    // GENERAL: primes to cover 2 |X| + 2 <= 4 max(|X|, 1).  |X| <= prod_k ||c_k||_1;
+                    // where every component joins two attributes, X is the mean over the
+                    // frequencies of a product of one spectrum value per relation, and by
+                    // Parseval two relations may enter with ||c_k||_2 (a skewed relation's is
+                    // a tenth of its ||c_k||_1: often one prime less)
+                    double lb = 0.0, g0 = 0.0, g1 = 0.0;  // the two largest log2(||.||_1 / ||.||_2)
                     bool zero = false;
                     for (int k = 0; k < Q.r; ++k) {
                         if (s1(k) == 0.0) zero = true;
                         lb += log2(s1(k));
+                        const double gain = log2(s1(k)) - 0.5 * log2(s2(k));
+                        if (gain > g0) {
+                            g1 = g0;
+                            g0 = gain;
+                        } else if (gain > g1) {
+                            g1 = gain;
+                        }
                     }
+                    if (Q.pairwise) lb -= g0 + g1;
                     rp.exact = 0;
                     rp.value = 0.0;
                     rp.xf = 0.0;
@@ -775,7 +786,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                         rp.exact = 1;
                         rp.lo = rp.hi = 0;
                     } else {
-                        const double need = lb + 3.0;
+                        const double need = fmax(lb, 0.0) + 2.0 + 1e-6;
                         double have = 0.0;
                         int K = 0;
                         while (K < kMaxPrimes && have <= need) have += a.crt.log2p[K++];
@@ -1342,6 +1353,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         const int nb = nblocks_for(h.m);
         QDesc &Q = qd[q];
         Q.plan = h.g.plan;
+        Q.pairwise = std::all_of(h.g.comp_size.begin(), h.g.comp_size.end(), [](int32_t c) { return c == 2; });
         Q.r = r;
         Q.d = d;
         Q.log2m = L;
@@ -1633,7 +1645,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 const int vpp = (int)G.mod_ptrs.size();
                 uint32_t *N = reinterpret_cast<uint32_t *>(mod_cur);
                 mod_cur += align_up((size_t)ks * vpp * ((size_t)1 << G.log2m) * sizeof(uint32_t));
-                st = ntt_forward(reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi]), vpp, ks, N, G.log2m,
+                st = ntt_forward(ModSrc::from_table(reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi])), vpp, ks, N, G.log2m,
                                  G.S, primes, groots[gi], ms);
                 if (st != CS_OK) return st;
                 hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N,
@@ -1813,7 +1825,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 CSK_HIP(hipMemcpyAsync(d_rep + qd[q].rep_base, rd.data() + qd[q].rep_base, qd[q].d * sizeof(RepDesc),
                                        hipMemcpyHostToDevice, s));
             uint32_t *N = reinterpret_cast<uint32_t *>(mbc + tab_bytes);
-            st = ntt_forward(reinterpret_cast<const int64_t *const *>(mbc), vpp, K, N, G.log2m, G.S, primes, roots, s);
+            st = ntt_forward(ModSrc::from_table(reinterpret_cast<const int64_t *const *>(mbc)), vpp, K, N, G.log2m, G.S, primes, roots, s);
             if (st != CS_OK) return st;
             hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)mpre.back(), K), dim3(kThreads), 0, s, N, vpp, d_rep,
                                reinterpret_cast<const int32_t *>(mbc + align_up(ptrs.size() * sizeof(void *))),
@@ -1847,49 +1859,80 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 mod_cur += align_up((size_t)K * d * Mlen * sizeof(uint32_t));
             }
             const int gx = (int)std::min<size_t>(64, ((size_t)m + 255) / 256);
-            const int gxM = (int)std::min<size_t>(256, ((size_t)Mlen + 255) / 256);
-            for (const Op &op : h.g.ops) {
-                uint32_t *dst = M + (size_t)op.dst * reg_elems;
+            // Registers stay where their value is until an operation needs them elsewhere: a
+            // loaded relation in its sketch, a correlation's result as the unfolded linear
+            // convolution in padB.
+            std::vector<ModVal> val(h.g.n_regs);
+            auto reg_buf = [&](int x) { return M + (size_t)x * reg_elems; };
+            auto materialize = [&](int x) -> cs_status {  // as residues [K][d][m]
+                if (val[x].sketch) {
+                    hipLaunchKernelGGL(k_mod_load, dim3(gx, K * d), dim3(256), 0, s, reg_buf(x), val[x].sketch, m, d,
+                                       primes);
+                    CSK_HIP(hipGetLastError());
+                } else if (val[x].lin) {
+                    hipLaunchKernelGGL(k_mod_fold, dim3(gx, K * d), dim3(256), 0, s, reg_buf(x), val[x].lin, m, Mlen, d,
+                                       primes);
+                    CSK_HIP(hipGetLastError());
+                }
+                val[x] = ModVal{};
+                val[x].reg = reg_buf(x);
+                return CS_OK;
+            };
+            auto spare_pads = [&]() -> cs_status {  // padB is about to be overwritten
+                for (int x = 0; x < h.g.n_regs; ++x)
+                    if (val[x].lin && (st = materialize(x)) != CS_OK) return st;
+                return CS_OK;
+            };
+            auto forward = [&](int x, bool reverse, uint32_t *out) {  // its transform, zero-padded for m no power of two
+                if (h.pow2) {
+                    ModSrc src;  // in place: x is in its register
+                    return ntt_forward(src, d, K, out, L, S, primes, roots, s);
+                }
+                return ntt_forward(val[x].sketch ? ModSrc::padded_sketch(val[x].sketch, m, reverse)
+                                                 : ModSrc::padded_reg(val[x].reg, m, reverse),
+                                   d, K, out, L, S, primes, roots, s);
+            };
+            const size_t n_ops = h.g.ops.size();
+            ModVal sum_a, sum_b;
+            int two = 0;
+            for (size_t oi = 0; oi < n_ops; ++oi) {
+                const Op &op = h.g.ops[oi];
                 switch (op.code) {
                     case OP_LOAD:
-                        hipLaunchKernelGGL(k_mod_load, dim3(gx, K * d), dim3(256), 0, s, dst,
-                                           rel_counters(h, op.src), m, d, primes);
-                        break;
-                    case OP_ONES:
-                        hipLaunchKernelGGL(k_mod_ones, dim3(gx, K * d), dim3(256), 0, s, dst, m, d, primes);
+                        val[op.dst] = ModVal{};
+                        val[op.dst].sketch = rel_counters(h, op.src);
                         break;
                     case OP_HAD:
-                        hipLaunchKernelGGL(k_mod_mul, dim3(gx, K * d), dim3(256), 0, s, dst,
-                                           M + (size_t)op.src * reg_elems, m, 0, S, d, primes, 0);
+                        if (oi + 1 == n_ops) {  // the last product is summed as it is formed
+                            sum_a = val[op.dst];
+                            sum_b = val[op.src];
+                            two = 1;
+                            break;
+                        }
+                        if ((st = materialize(op.dst)) != CS_OK || (st = materialize(op.src)) != CS_OK) return st;
+                        hipLaunchKernelGGL(k_mod_mul, dim3(gx, K * d), dim3(256), 0, s, reg_buf(op.dst),
+                                           reg_buf(op.src), m, 0, S, d, primes, 0);
                         break;
                     case OP_CORR: {
-                        uint32_t *src = M + (size_t)op.src * reg_elems;
                         if (h.pow2) {
-                            st = ntt_forward(nullptr, d, K, src, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
-                            st = ntt_forward(nullptr, d, K, dst, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
+                            if ((st = materialize(op.dst)) != CS_OK || (st = materialize(op.src)) != CS_OK) return st;
+                            uint32_t *src = reg_buf(op.src), *dst = reg_buf(op.dst);
+                            if ((st = forward(op.src, false, src)) != CS_OK) return st;
+                            if ((st = forward(op.dst, false, dst)) != CS_OK) return st;
                             hipLaunchKernelGGL(k_mod_mul, dim3(gx, K * d), dim3(256), 0, s, dst, src, m, L, S, d,
                                                primes, 1);
                             CSK_HIP(hipGetLastError());
-                            st = ntt_inverse(d, K, dst, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
+                            if ((st = ntt_inverse(ModSrc{}, d, K, dst, L, S, primes, roots, s)) != CS_OK) return st;
                         } else {
                             // src star dst = reverse(src) circularly convolved with dst
-                            hipLaunchKernelGGL(k_mod_pad, dim3(gxM, K * d), dim3(256), 0, s, padA, src, m, Mlen, 1);
-                            hipLaunchKernelGGL(k_mod_pad, dim3(gxM, K * d), dim3(256), 0, s, padB, dst, m, Mlen, 0);
-                            CSK_HIP(hipGetLastError());
-                            st = ntt_forward(nullptr, d, K, padA, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
-                            st = ntt_forward(nullptr, d, K, padB, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
-                            hipLaunchKernelGGL(k_mod_mul, dim3(gxM, K * d), dim3(256), 0, s, padB, padA, Mlen, L, S, d,
-                                               primes, 0);
-                            CSK_HIP(hipGetLastError());
-                            st = ntt_inverse(d, K, padB, L, S, primes, roots, s);
-                            if (st != CS_OK) return st;
-                            hipLaunchKernelGGL(k_mod_fold, dim3(gx, K * d), dim3(256), 0, s, dst, padB, m, Mlen, d,
-                                               primes);
+                            if ((st = spare_pads()) != CS_OK) return st;
+                            if ((st = forward(op.src, true, padA)) != CS_OK) return st;
+                            if ((st = forward(op.dst, false, padB)) != CS_OK) return st;
+                            if ((st = ntt_inverse(ModSrc::times(padA), d, K, padB, L, S, primes, roots, s)) != CS_OK)
+                                return st;
+                            val[op.dst] = ModVal{};
+                            val[op.dst].lin = padB;
+                            val[op.dst].M = Mlen;
                         }
                         break;
                     }
@@ -1898,9 +1941,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 }
                 CSK_HIP(hipGetLastError());
             }
-            hipLaunchKernelGGL(k_mod_sum, dim3(qd[q].nb, K * d), dim3(kThreads), 0, s,
-                               M + (size_t)h.g.result_reg * reg_elems, m, d, primes, qd[q].nb, d_rep, qd[q].rep_base,
-                               mod_plane, d_modp);
+            if (!two) sum_a = val[h.g.result_reg];
+            hipLaunchKernelGGL(k_mod_sum, dim3(qd[q].nb, K * d), dim3(kThreads), 0, s, sum_a, sum_b, two, m, d, primes,
+                               qd[q].nb, d_rep, qd[q].rep_base, mod_plane, d_modp);
             CSK_HIP(hipGetLastError());
         }
         fa.stage = 2;
@@ -2073,7 +2116,7 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         uint32_t *dst = ci == 0 ? Nref : N;
         const TwiddleTables tw = twiddle_tables(device, log2m, S, s, &st);
         if (!tw.full) break;
-        if ((st = ntt_forward(nt, n_vec, 1, dst, log2m, S, primes, roots, s)) != CS_OK) break;
+        if ((st = ntt_forward(ModSrc::from_table(nt), n_vec, 1, dst, log2m, S, primes, roots, s)) != CS_OK) break;
         if (ci > 0) {
             unsigned int hflag = 0;
             hipLaunchKernelGGL(k_tune_flag0, dim3(1), dim3(1), 0, s, flag);
@@ -2093,7 +2136,7 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         for (int r = 0; r < 3 && ok; ++r)
             ok = hipEventRecord(e0, s) == hipSuccess &&
                  fft_f64_forward(re, im, n_vec, Z, log2m, S, tw, s) == CS_OK &&
-                 ntt_forward(nt, n_vec, 1, N, log2m, S, primes, roots, s) == CS_OK &&
+                 ntt_forward(ModSrc::from_table(nt), n_vec, 1, N, log2m, S, primes, roots, s) == CS_OK &&
                  hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
                  hipEventElapsedTime(&t[r], e0, e1) == hipSuccess;
         if (!ok) {

@@ -80,7 +80,7 @@ struct RelPlan {
 };
 
 // Modular op list (Alg. 3 in modular arithmetic) for general queries.
-enum OpCode : int32_t { OP_LOAD = 0, OP_ONES = 1, OP_HAD = 2, OP_CORR = 3 };
+enum OpCode : int32_t { OP_LOAD = 0, OP_HAD = 2, OP_CORR = 3 };
 struct Op {
     int32_t code;
     int32_t dst;   // register

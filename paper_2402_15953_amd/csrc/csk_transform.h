@@ -89,11 +89,58 @@ cs_status column_twiddles(double2 *out, const double2 *tw, int log2m, int S, hip
 cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
                           int S, const TwiddleTables &tw, hipStream_t s);
 
-// ptrs != null: vector (prime i, j) is loaded from sketch ptrs[j] (device pointer table);
-// ptrs == null: transform buf in place.
-cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+// Where the first pass of a modular transform takes element `pos` of vector v = (prime, j)
+// from: the sketch's int64 value or a residue, converted, padded or multiplied on the way
+// instead of by passes of their own.
+struct ModSrc {
+    enum Mode : int32_t {
+        kInPlace,    // the buffer itself
+        kTable,      // sketch table[j]
+        kPadSketch,  // sketch base + j m, zero beyond m; reversed (i -> (m - i) mod m) when asked
+        kPadReg,     // the same of residue vector reg + v m
+        kMul,        // the buffer's element times mul's at the same place
+    } mode = kInPlace;
+    const int64_t *const *table = nullptr;
+    const int64_t *sketch = nullptr;
+    const uint32_t *reg = nullptr;  // kPadReg, kMul
+    uint32_t m = 0;
+    int32_t reverse = 0;
+    static ModSrc from_table(const int64_t *const *t)
+    {
+        ModSrc s;
+        s.mode = kTable;
+        s.table = t;
+        return s;
+    }
+    static ModSrc padded_sketch(const int64_t *p, uint32_t m, bool reverse)
+    {
+        ModSrc s;
+        s.mode = kPadSketch;
+        s.sketch = p;
+        s.m = m;
+        s.reverse = reverse;
+        return s;
+    }
+    static ModSrc padded_reg(const uint32_t *p, uint32_t m, bool reverse)
+    {
+        ModSrc s;
+        s.mode = kPadReg;
+        s.reg = p;
+        s.m = m;
+        s.reverse = reverse;
+        return s;
+    }
+    static ModSrc times(const uint32_t *p)
+    {
+        ModSrc s;
+        s.mode = kMul;
+        s.reg = p;
+        return s;
+    }
+};
+cs_status ntt_forward(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
                       const PrimeDev *primes, const ModTables &roots, hipStream_t s);
-cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S, const PrimeDev *primes,
-                      const ModTables &roots, hipStream_t s);
+cs_status ntt_inverse(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s);
 
 }  // namespace csk

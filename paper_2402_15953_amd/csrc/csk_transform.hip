@@ -197,10 +197,6 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_fft_f64(F64Src src
 
 // ---------------------------------------------------------------- NTT pass
 
-struct ModSrc {
-    const int64_t *const *ptr;  // [vec_per_prime] sketch of vector v % vec_per_prime (null: in place)
-};
-
 // Register DFTs of residues.  Inputs below p; the last stage's results are below 2p when
 // LAZY (a twiddle multiplies them next), else below p.
 struct DftM {
@@ -243,7 +239,10 @@ struct DftM {
 // thread cost as much address arithmetic, LDS instructions and barriers as butterflies:
 // 15 vectors of 2^21 at 3 primes took 213 us (columns) and 144 us (rows), 97 and 103 us in
 // registers.
-template <int LG, int LC, int EB>
+// MODE: the source's where it is kInPlace or kTable, so that their loads carry no branch (one
+// per element cost the 5-chain's estimate 3%); kGeneric for the others.
+constexpr int kGeneric = -1;
+template <int LG, int LC, int EB, int MODE>
 __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, uint32_t *buf, PassGeom g, int vec_per_prime, int n_primes,
                                                               const PrimeDev *__restrict__ primes,
                                                               const uint32_t *__restrict__ roots, int log2T,
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
     {
         const uint32_t tiles = (uint32_t)vec_per_prime * g.blocks, id = blockIdx.x;
         uint32_t tile;
-        if (src.ptr && (tiles & 7) == 0) {
+        if ((src.mode == ModSrc::kTable || src.mode == ModSrc::kPadSketch) && (tiles & 7) == 0) {
             const uint32_t w = id >> 3, K = n_primes;
             pi = (int)(w % K);
             tile = (w / K) * 8 + (id & 7);
@@ -277,10 +276,21 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     uint32_t *vec = buf + (size_t)v * m;
-    const int64_t *in = src.ptr ? src.ptr[j] : nullptr;
-    auto load = [&](int n, int c) {
+    const int64_t *in = src.mode == ModSrc::kTable ? src.table[j] : src.sketch + (size_t)j * src.m;
+    const uint32_t *reg = src.reg + (size_t)v * (src.mode == ModSrc::kMul ? m : (int64_t)src.m);
+    auto load = [&](int n, int c) -> uint32_t {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-        return in ? mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64) : vec[pos];
+        if constexpr (MODE == ModSrc::kInPlace) return vec[pos];
+        if constexpr (MODE == ModSrc::kTable) return mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64);
+        const bool pad = src.mode == ModSrc::kPadSketch || src.mode == ModSrc::kPadReg;
+        if (pad && pos >= src.m) return 0u;
+        const int64_t at = pad && src.reverse && pos > 0 ? src.m - pos : pos;
+        switch (src.mode) {
+            case ModSrc::kInPlace: return vec[pos];
+            case ModSrc::kMul: return R.mul(vec[pos], reg[pos]);
+            case ModSrc::kPadReg: return reg[at];
+            default: return mont_from_i64(R, in[at], P.r2, P.r3, P.neg2_64);
+        }
     };
     // Output n of column c is multiplied by w_m^(n colid): a thread's outputs are an
     // arithmetic progression in n, so two entries of the long table, w^(f0 colid) and
@@ -463,8 +473,14 @@ hipError_t ntt_pass(const PassGeom &g, const ModSrc &src, int n_vec, uint32_t *b
     return with_length(g, [&](auto lg, auto row, auto single) {
         constexpr int LG = decltype(lg)::value, LC = decltype(row)::value ? 0 : ntt_log2c(LG);
         constexpr int EB = ntt_elems(LG, LC, decltype(single)::value);
-        hipLaunchKernelGGL((k_ntt<LG, LC, EB>), dim3((unsigned)n_vec * g.blocks), dim3(pass_threads(LG, LC, EB)), 0, s,
-                           src, buf, g, vec_per_prime, n_vec / vec_per_prime, primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
+        auto go = [&](auto mode) {
+            hipLaunchKernelGGL((k_ntt<LG, LC, EB, decltype(mode)::value>), dim3((unsigned)n_vec * g.blocks),
+                               dim3(pass_threads(LG, LC, EB)), 0, s, src, buf, g, vec_per_prime, n_vec / vec_per_prime,
+                               primes, roots.full, roots.log2T, roots.stage, roots.log2S, inverse);
+        };
+        if (src.mode == ModSrc::kInPlace) go(std::integral_constant<int, ModSrc::kInPlace>{});
+        else if (src.mode == ModSrc::kTable) go(std::integral_constant<int, ModSrc::kTable>{});
+        else go(std::integral_constant<int, kGeneric>{});
     });
 }
 }  // namespace
@@ -491,40 +507,36 @@ cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, in
     return CS_OK;
 }
 
-cs_status ntt_forward(const int64_t *const *ptrs, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+cs_status ntt_forward(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
                       const PrimeDev *primes, const ModTables &roots, hipStream_t s)
 {
     const int n_vec = vec_per_prime * n_primes;
     if (n_vec == 0) return CS_OK;
-    ModSrc first{ptrs};
-    ModSrc self{nullptr};
-    const ModSrc &in = ptrs ? first : self;
     if (log2m <= 12) {
-        CSK_HIP(ntt_pass(single_pass(log2m), in, n_vec, buf, vec_per_prime, primes, roots, 0, s));
+        CSK_HIP(ntt_pass(single_pass(log2m), src, n_vec, buf, vec_per_prime, primes, roots, 0, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(with_columns(column_pass(log2m, S, true), ntt_log2c(log2m - S)), in, n_vec, buf, vec_per_prime, primes,
-                     roots, 0, s));
-    CSK_HIP(ntt_pass(row_pass(log2m, S, false), self, n_vec, buf, vec_per_prime, primes, roots, 0, s));
+    CSK_HIP(ntt_pass(with_columns(column_pass(log2m, S, true), ntt_log2c(log2m - S)), src, n_vec, buf, vec_per_prime,
+                     primes, roots, 0, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, false), ModSrc{}, n_vec, buf, vec_per_prime, primes, roots, 0, s));
     return CS_OK;
 }
 
-cs_status ntt_inverse(int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S, const PrimeDev *primes,
-                      const ModTables &roots, hipStream_t s)
+cs_status ntt_inverse(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s)
 {
     const int n_vec = vec_per_prime * n_primes;
     if (n_vec == 0) return CS_OK;
-    ModSrc self{nullptr};
     if (log2m <= 12) {
         PassGeom g = single_pass(log2m);
         g.scale = 1;
-        CSK_HIP(ntt_pass(g, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+        CSK_HIP(ntt_pass(g, src, n_vec, buf, vec_per_prime, primes, roots, 1, s));
         return CS_OK;
     }
-    CSK_HIP(ntt_pass(row_pass(log2m, S, true), self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+    CSK_HIP(ntt_pass(row_pass(log2m, S, true), src, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     PassGeom g2 = with_columns(column_pass(log2m, S, false), ntt_log2c(log2m - S));
     g2.scale = 1;
-    CSK_HIP(ntt_pass(g2, self, n_vec, buf, vec_per_prime, primes, roots, 1, s));
+    CSK_HIP(ntt_pass(g2, ModSrc{}, n_vec, buf, vec_per_prime, primes, roots, 1, s));
     return CS_OK;
 }
 
