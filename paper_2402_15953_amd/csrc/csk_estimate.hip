@@ -209,44 +209,35 @@ __device__ bool digits_to_i128(const uint32_t *dig, int K, const CrtTables &T, _
 
 // ---------------------------------------------------------------- descriptors
 
-// One sketch vector c_k[t] (norm partials at off * 2 doubles).
-struct SkDesc {
+// The d sketches of one relation: sketch t at p + t m, its norm partials at off + t nb (pairs).
+struct NormDesc {
     const int64_t *p;
-    int32_t log2m;
-    int32_t nb;
     int64_t off;
     uint32_t m;
-    uint32_t pad;
+    int32_t d, nb, pad;
 };
 
-// One repetition t of query q.
-struct RepDesc {
-    const int64_t *c0;     // DOT plan: relation 0 and 1 at repetition t
-    const int64_t *c1;
-    int32_t q, t, log2m, r, d;
-    int32_t S;             // row length 2^S of the two-pass transforms of this length
-    uint32_t m;            // buckets (log2m is exact only for powers of two)
-    uint32_t conj;         // SPECTRAL: relations taken conjugated
-    int32_t nb;            // blocks of this repetition's reductions
-    // SPECTRAL, relation k's sketch of this repetition: packed fp64 vector times 2 plus the
-    // half it is, and vector of the modular pass, in its group's buffers
-    int32_t zv[kMaxRel], mv[kMaxRel];
-    int64_t spec_off;      // fp64 spectral partials, (2 + r) doubles per block
-    int64_t dot_off;       // DOT partials, 4 words per block (int128 sum, fp64 sum, fp64 sum of |terms|)
-    int64_t mod_off;       // modular partials (per prime plane)
-};
-
+// One query; repetition t's partials follow the first one's.
 struct QDesc {
-    int32_t plan, r, d, log2m, rep_base, nb;
-    uint32_t m;
-    int32_t pairwise;  // every component joins two attributes
-    // where this query's partials start (its first repetition's spectral sums and
-    // residues, each relation's first norm pair): the finalize reads them without going
-    // through the repetition and sketch descriptors first
-    int64_t spec_off0, mod_off0;
-    int64_t norm_off[kMaxRel];
+    const int64_t *c0, *c1;  // DOT plan: relations 0 and 1 [d][m]
+    int32_t plan, r, d, log2m, rep_base;
+    int32_t nb;              // blocks of a repetition's reductions
+    int32_t S;               // row length 2^S of the two-pass transforms of this length
+    uint32_t m;              // buckets (log2m is exact only for powers of two)
+    uint32_t conj;           // SPECTRAL: relations taken conjugated
+    int32_t pairwise;        // every component joins two attributes
+    int64_t spec_off;        // fp64 spectral partials, (2 + r) doubles per block
+    int64_t dot_off;         // DOT partials, 4 words per block (int128 sum, fp64 sum, fp64 sum of |terms|)
+    int64_t mod_off;         // modular partials (per prime plane)
+    int64_t norm_off[kMaxRel];  // relation k's norm pairs, nb per repetition
     // odd d: norm pair of the sketch packed with relation k's last one (-1: none)
     int64_t pair_off[kMaxRel];
+    // SPECTRAL: relation k's first packed fp64 vector (repetitions 2i and 2i + 1 share one),
+    // twice the vector of its last sketch plus the half it is (odd d), and its first vector
+    // of the modular pass, in its group's buffers
+    int32_t vec0[kMaxRel], last[kMaxRel], mod0[kMaxRel];
+    // packed vector of relation k's repetition t times 2, plus the half it is
+    __device__ __forceinline__ int packed(int k, int t) const { return (t ^ 1) < d ? 2 * vec0[k] + t : last[k]; }
 };
 
 // ---------------------------------------------------------------- kernels
@@ -264,24 +255,25 @@ __device__ __forceinline__ int find_item(const int64_t *__restrict__ prefix, int
 }
 
 // Sum of squares and of absolute values of each sketch vector (fp64), per block.
-__global__ __launch_bounds__(kThreads) void k_norms(const SkDesc *__restrict__ sks, const int64_t *__restrict__ prefix,
-                                                    int n_items, double *partials)
+__global__ __launch_bounds__(kThreads) void k_norms(const NormDesc *__restrict__ rels,
+                                                    const int64_t *__restrict__ prefix, int n_items, double *partials)
 {
     __shared__ double sh[kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
-    const SkDesc S = sks[item];
-    const int blk = (int)(blockIdx.x - prefix[item]);
+    const NormDesc S = rels[item];
+    const int within = (int)(blockIdx.x - prefix[item]), t = within / S.nb, blk = within - t * S.nb;
     const int64_t m = S.m;
+    const int64_t *__restrict__ p = S.p + t * m;
     double s2 = 0.0, s1 = 0.0;
     for (int64_t j = (int64_t)blk * kThreads + threadIdx.x; j < m; j += (int64_t)S.nb * kThreads) {
-        const double v = (double)S.p[j];
+        const double v = (double)p[j];
         s2 += v * v;
         s1 += fabs(v);
     }
     const double a = block_sum(s2, sh);
     const double b = block_sum(s1, sh);
     if (threadIdx.x == 0) {
-        double *o = partials + (S.off + blk) * 2;
+        double *o = partials + (S.off + within) * 2;
         o[0] = a;
         o[1] = b;
     }
@@ -291,20 +283,21 @@ __global__ __launch_bounds__(kThreads) void k_norms(const SkDesc *__restrict__ s
 // an fp64 sum of the products and an fp64 sum of their absolute values beside it: the
 // latter bounds every partial sum, so the finalize knows whether the wrapped integer is
 // the true one (the sum of |terms| stays below 2^126).
-__global__ __launch_bounds__(kThreads) void k_dot(const RepDesc *__restrict__ reps, const int32_t *__restrict__ idx,
+__global__ __launch_bounds__(kThreads) void k_dot(const QDesc *__restrict__ qs, const int32_t *__restrict__ idx,
                                                   const int64_t *__restrict__ prefix, int n_items,
                                                   unsigned long long *partials)
 {
     __shared__ unsigned __int128 sh[kThreads];
     __shared__ double shf[kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
-    const RepDesc D = reps[idx[item]];
-    const int blk = (int)(blockIdx.x - prefix[item]);
+    const QDesc &D = qs[idx[item]];
+    const int within = (int)(blockIdx.x - prefix[item]), t = within / D.nb, blk = within - t * D.nb;
     const int64_t m = D.m;
+    const int64_t *__restrict__ c0 = D.c0 + t * m, *__restrict__ c1 = D.c1 + t * m;
     __int128 acc = 0;
     double fs = 0.0, fa = 0.0;
     for (int64_t j = (int64_t)blk * kThreads + threadIdx.x; j < m; j += (int64_t)D.nb * kThreads) {
-        const int64_t x = D.c0[j], y = D.c1[j];
+        const int64_t x = c0[j], y = c1[j];
         acc += (__int128)x * (__int128)y;
         const double p = (double)x * (double)y;
         fs += p;
@@ -319,7 +312,7 @@ __global__ __launch_bounds__(kThreads) void k_dot(const RepDesc *__restrict__ re
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        unsigned long long *o = partials + (D.dot_off + blk) * 4;
+        unsigned long long *o = partials + (D.dot_off + within) * 4;
         o[0] = (unsigned long long)(uint64_t)sh[0];
         o[1] = (unsigned long long)(uint64_t)(sh[0] >> 64);
         o[2] = (unsigned long long)__double_as_longlong(bs);
@@ -327,19 +320,18 @@ __global__ __launch_bounds__(kThreads) void k_dot(const RepDesc *__restrict__ re
     }
 }
 
-// fp64 spectral product-reduce for repetitions idx[blockIdx.y] of one m-group.
-// Relation k's sketch of the repetition is half zv & 1 of packed vector zv / 2.
+// fp64 spectral product-reduce for the queries idx of one m-group.
 // partials: sum Re(term), sum |Re|+|Im| of terms, max |C_k| per relation.
 __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict__ Z,
-                                                       const RepDesc *__restrict__ reps,
+                                                       const QDesc *__restrict__ qs,
                                                        const int32_t *__restrict__ idx,
                                                        const int64_t *__restrict__ prefix, int n_items,
                                                        double *partials)
 {
     __shared__ double sh[kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
-    const RepDesc &D = reps[idx[item]];
-    const int blk = (int)(blockIdx.x - prefix[item]);
+    const QDesc &D = qs[idx[item]];
+    const int within = (int)(blockIdx.x - prefix[item]), t = within / D.nb, blk = within - t * D.nb;
     const int log2m = D.log2m, S = D.S;
     const uint32_t m = 1u << log2m;
     const int r = D.r;
@@ -354,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
 #pragma unroll
         for (int k = 0; k < kMaxRel; ++k) {
             if (k < r) {
-                const int sidx = D.zv[k];
+                const int sidx = D.packed(k, t);
                 const double2 *zv = Z + (size_t)(sidx >> 1) * m;
                 const double2 a = zv[pos], b = zv[npos];
                 double cr, ci;
@@ -376,7 +368,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
         acc += pr;
         acc_abs += fabs(pr) + fabs(pi);
     }
-    double *o = partials + (D.spec_off + (int64_t)blk * (2 + r));
+    double *o = partials + (D.spec_off + (int64_t)within * (2 + r));
     const double s0 = block_sum(acc, sh);
     if (threadIdx.x == 0) o[0] = s0;
     const double s1 = block_sum(acc_abs, sh);
@@ -387,20 +379,19 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
     }
 }
 
-// Modular spectral product-reduce.  Buffer [K][vpp][m]; relation k's sketch of the
-// repetition is vector mv[k].  partials [K][plane] at mod_off.
+// Modular spectral product-reduce.  Buffer [K][vpp][m]; relation k's sketch of repetition t
+// is vector mod0[k] + t.  partials [K][plane] at mod_off.
 __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restrict__ N, int vpp,
-                                                       const RepDesc *__restrict__ reps,
+                                                       const QDesc *__restrict__ qs,
                                                        const int32_t *__restrict__ idx,
                                                        const int64_t *__restrict__ prefix, int n_items,
                                                        const PrimeDev *__restrict__ primes, int64_t plane,
-                                                       uint32_t *partials, const int32_t *__restrict__ kp)
+                                                       uint32_t *partials)
 {
     __shared__ uint32_t sh[kThreads];
     const int item = find_item(prefix, n_items, blockIdx.x);
-    if (kp && (int)blockIdx.y >= kp[idx[item]]) return;  // prime not needed by this repetition
-    const RepDesc &D = reps[idx[item]];
-    const int blk = (int)(blockIdx.x - prefix[item]);
+    const QDesc &D = qs[idx[item]];
+    const int within = (int)(blockIdx.x - prefix[item]), t = within / D.nb, blk = within - t * D.nb;
     const int pi = blockIdx.y;
     const PrimeDev P = primes[pi];
     const RingM R{P.p, P.pinv_neg};
@@ -423,7 +414,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restric
             prod[u] = P.one;
         }
         for (int k = 0; k < D.r; ++k) {
-            const uint32_t *v = base + (size_t)D.mv[k] * m;
+            const uint32_t *v = base + (size_t)(D.mod0[k] + t) * m;
             const bool cj = (D.conj >> k) & 1u;
             uint32_t val[U];
 #pragma unroll
@@ -441,7 +432,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_mod(const uint32_t *__restric
         if ((int)threadIdx.x < s) sh[threadIdx.x] = R.add(sh[threadIdx.x], sh[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) partials[(size_t)pi * plane + D.mod_off + blk] = sh[0];
+    if (threadIdx.x == 0) partials[(size_t)pi * plane + D.mod_off + within] = sh[0];
 }
 
 // ---- general plan register operations, buffers [K][d][m] per register
@@ -492,11 +483,10 @@ struct ModVal {
 };
 
 // Sum over j of a[j] (times b[j] when `two`) of vector (prime i, repetition t) ->
-// partials[i * plane + mod_off(rep) + b]: the last Hadamard product and the SumElements of
+// partials[i * plane + mod_off + t nb + b]: the last Hadamard product and the SumElements of
 // Alg. 3, converting and folding on the way.
 __global__ __launch_bounds__(kThreads) void k_mod_sum(ModVal a, ModVal b, int two, uint32_t m, int d,
-                                                      const PrimeDev *__restrict__ primes, int nb,
-                                                      const RepDesc *__restrict__ reps, int rep_base,
+                                                      const PrimeDev *__restrict__ primes, int nb, int64_t mod_off,
                                                       int64_t plane, uint32_t *partials)
 {
     __shared__ uint32_t sh[kThreads];
@@ -516,7 +506,7 @@ __global__ __launch_bounds__(kThreads) void k_mod_sum(ModVal a, ModVal b, int tw
         if ((int)threadIdx.x < s) sh[threadIdx.x] = R.add(sh[threadIdx.x], sh[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) partials[(size_t)pi * plane + reps[rep_base + t].mod_off + blockIdx.x] = sh[0];
+    if (threadIdx.x == 0) partials[(size_t)pi * plane + mod_off + (int64_t)t * nb + blockIdx.x] = sh[0];
 }
 
 // dst[j] = lin[j] + lin[j + m]: the circular (length m) result of a linear one.
@@ -537,8 +527,6 @@ __global__ void k_mod_fold(uint32_t *dst, const uint32_t *__restrict__ lin, uint
 struct FinalizeArgs {
     int32_t stage;        // 1: after the fp64 / dot / norms pass; 2: after the modular pass
     const QDesc *qs;
-    const RepDesc *reps;
-    const SkDesc *sks;
     const double *norms;
     const double *spec;
     const unsigned long long *dot;
@@ -548,7 +536,10 @@ struct FinalizeArgs {
     CrtTables crt;
     RepDev *rs;
     OutDev *outs;
-    int32_t *kp;    // stage 1 also stores each repetition's prime count here
+    // host copies of the records and outputs, written beside the device's (null: the caller
+    // downloads them)
+    RepDev *rs_host;
+    OutDev *outs_host;
     int32_t kcap;   // stage 2 finishes repetitions needing at most kcap primes
 };
 
@@ -558,6 +549,10 @@ struct FinalizeArgs {
 constexpr int kFinThreadsFew = 1024, kFinThreadsMany = 256;
 constexpr int kStage = kMaxD * 3 * kMaxRel;  // doubles of per-repetition bound terms
 constexpr int kSpecPrimes = 5;                       // speculative modular step: primes (155 bits)
+// Tables up to kDirectTables bytes go up by a kernel that reads the pinned staging area, and
+// the results of up to kDirectReps repetitions are written to it by the finalize.
+constexpr size_t kDirectTables = (size_t)1 << 15;
+constexpr int kDirectReps = 512;
 constexpr size_t kSpecBudget = (size_t)1 << 30;      // and its largest workspace
 constexpr int kOverlapPrimes = 3;                    // at most this many: beside the fp64 chain
 constexpr size_t kOverlapMinResidues = (size_t)1 << 24;  // and at least this many residues
@@ -577,7 +572,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
     __shared__ double s_sum[kMaxD], s_sabs[kMaxD], s_mx[kMaxD * kMaxRel];
     __shared__ double s_stage[kStage];  // scratch of the bound computation
     __shared__ uint32_t s_res[kMaxD * kMaxPrimes], s_dig[kMaxD * kMaxPrimes];
-    const QDesc Q = a.qs[blockIdx.x];
+    const QDesc &Q = a.qs[blockIdx.x];
     const int t = threadIdx.x;
     const double u = 0x1p-53;
     const double m = (double)Q.m;
@@ -594,7 +589,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             double q2 = 0.0, l1 = 0.0;
             if (lane < nb) {
                 const int k = o / Q.d;
-                const double *p = a.norms + (a.qs[blockIdx.x].norm_off[k] + (int64_t)(o - k * Q.d) * nb + lane) * 2;
+                const double *p = a.norms + (Q.norm_off[k] + (int64_t)(o - k * Q.d) * nb + lane) * 2;
                 q2 = p[0];
                 l1 = p[1];
             }
@@ -607,14 +602,14 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
         }
         if (plan == CS_PLAN_SPECTRAL && (Q.d & 1)) {
             for (int k = wv; k < Q.r; k += kWaves) {
-                const int64_t po = a.qs[blockIdx.x].pair_off[k];
+                const int64_t po = Q.pair_off[k];
                 const double q2 = warp_sum(po >= 0 && lane < nb ? a.norms[(po + lane) * 2] : 0.0);
                 if (lane == 0) s_p2[k] = q2;
             }
         }
         if (plan == CS_PLAN_SPECTRAL) {
             const int w = 2 + Q.r;
-            const double *spc = a.spec + Q.spec_off0;
+            const double *spc = a.spec + Q.spec_off;
             for (int o = wv; o < Q.d; o += kWaves) {
                 const double *p = spc + ((int64_t)o * nb + lane) * w;
                 double sm = lane < nb ? p[0] : 0.0, sa = lane < nb ? p[1] : 0.0;
@@ -638,7 +633,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
         for (int o = wv; o < Q.d && (STAGE == 2 || plan == CS_PLAN_SPECTRAL); o += kWaves) {
             const int K = STAGE == 3 ? a.kcap : a.rs[Q.rep_base + o].kprimes;
             if (K <= 0 || K > a.kcap) continue;
-            const int64_t mod_off = Q.mod_off0 + (int64_t)o * Q.nb;  // repetitions' residues follow each other
+            const int64_t mod_off = Q.mod_off + (int64_t)o * Q.nb;  // repetitions' residues follow each other
             for (int i = 0; i < K; ++i) {
                 const PrimeDev &P = a.primes[i];
                 const RingM R{P.p, P.pinv_neg};
@@ -650,13 +645,13 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
     }
     __syncthreads();
     if (t < Q.d) {
-        const RepDesc D = a.reps[Q.rep_base + t];
         // this repetition's record lives in registers; written back once at the end
-        RepDev rp = a.rs[Q.rep_base + t];
+        RepDev rp{};
+        if constexpr (STAGE == 2) rp = a.rs[Q.rep_base + t];
         // additions on any term's path to a sum: its thread's serial sum (per_thread - 1),
         // block_sum (6 shuffle levels, then the kThreads / 64 wavefront sums one after
         // another) and the tree of depth 6 over the nb <= 64 block partials above
-        const double per_thread = ceil(m / ((double)D.nb * kThreads));
+        const double per_thread = ceil(m / ((double)Q.nb * kThreads));
         const double n_eff = per_thread + 6.0 + kThreads / 64 + 6.0;
         if constexpr (STAGE != 2) {
             rp.kprimes = 0;
@@ -666,8 +661,8 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             if (plan == CS_PLAN_DOT) {
                 unsigned __int128 s = 0;
                 double fs = 0.0, fa = 0.0;
-                for (int b = 0; b < D.nb; ++b) {
-                    const unsigned long long *p = a.dot + (D.dot_off + b) * 4;
+                for (int b = 0; b < Q.nb; ++b) {
+                    const unsigned long long *p = a.dot + (Q.dot_off + (int64_t)t * Q.nb + b) * 4;
                     s += ((unsigned __int128)p[1] << 64) | p[0];
                     fs += __longlong_as_double((long long)p[2]);
                     fa += __longlong_as_double((long long)p[3]);
@@ -676,7 +671,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                 // product rounded once): the true sum of |terms| is at most
                 // fa (1 + (n_eff + nb + 2) u) and bounds every partial sum, so below 2^126
                 // the wrapped 128-bit integer is the exact inner product
-                const double bnd = fa * (1.0 + (n_eff + D.nb + 4.0) * u * 1.01);
+                const double bnd = fa * (1.0 + (n_eff + Q.nb + 4.0) * u * 1.01);
                 if (bnd < 0x1p126) {
                     const __int128 x = (__int128)s;
                     rp.lo = (int64_t)(uint64_t)s;
@@ -842,7 +837,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             }
         }
         a.rs[Q.rep_base + t] = rp;
-        if constexpr (STAGE != 2) a.kp[Q.rep_base + t] = rp.kprimes;
+        if (a.rs_host) a.rs_host[Q.rep_base + t] = rp;
         s_val[t] = rp.value;
         s_ex[t] = rp.exact;
         s_lo[t] = rp.lo;
@@ -874,7 +869,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             rank += less;
         }
         if (rank == (Q.d - 1) / 2) {
-            OutDev &o = a.outs[blockIdx.x];
+            OutDev o;
             o.value = v;
             o.lo = s_lo[t];
             o.hi = s_hi[t];
@@ -882,8 +877,17 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             o.fits = ex && x >= (__int128)INT64_MIN && x <= (__int128)INT64_MAX;
             o.n_modular = n_mod;
             o.median_rep = t;
+            a.outs[blockIdx.x] = o;
+            if (a.outs_host) a.outs_host[blockIdx.x] = o;
         }
     }
+}
+
+// The tables of a small estimate, read from the pinned staging area (16-byte words).
+__global__ __launch_bounds__(kThreads) void k_copy_tables(uint4 *__restrict__ dst, const uint4 *__restrict__ src, uint32_t n)
+{
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) dst[i] = src[i];
 }
 
 // Asynchronous results: the finalize outputs written as cs_estimate_t into memory the
@@ -1318,13 +1322,11 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
 
     // ---- host tables
     std::vector<QDesc> qd(nq);
-    std::vector<RepDesc> rd;
-    std::vector<SkDesc> sd;
-    std::vector<int32_t> dot_idx;
+    std::vector<NormDesc> nd;       // relations to norm
+    std::vector<int32_t> dot_idx;   // queries with the DOT plan
     struct Group {
         int log2m, S;
-        std::vector<int> queries;
-        std::vector<int32_t> rep_idx;
+        std::vector<int32_t> queries;
         std::vector<const int64_t *> re, im;
         std::vector<const int64_t *> mod_ptrs;  // every sketch once
         size_t z_off = 0;
@@ -1347,6 +1349,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     std::map<int, Group> groups;
     std::vector<int> general_q;
     int64_t norm_off = 0, spec_off = 0, dot_off = 0, mod_off = 0;
+    int32_t n_rep = 0;
     for (int q = 0; q < nq; ++q) {
         const Handle &h = *hs[q];
         const int r = h.g.n_rel, d = (int)h.d, L = h.log2m;
@@ -1358,10 +1361,22 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         Q.d = d;
         Q.log2m = L;
         Q.m = h.m;
-        Q.rep_base = (int32_t)rd.size();
+        Q.S = split_of(L);
+        Q.conj = h.g.conj_mask;
+        Q.c0 = rel_counters(h, 0);
+        Q.c1 = rel_counters(h, 1);
+        Q.rep_base = n_rep;
+        n_rep += d;
         Q.nb = nb;
-        Q.spec_off0 = spec_off;
-        Q.mod_off0 = mod_off;
+        Q.spec_off = spec_off;
+        Q.dot_off = dot_off;
+        Q.mod_off = mod_off;
+        mod_off += (int64_t)d * nb;
+        if (Q.plan == CS_PLAN_SPECTRAL) spec_off += (int64_t)d * nb * (2 + r);
+        if (Q.plan == CS_PLAN_DOT) {
+            dot_off += (int64_t)d * nb;
+            dot_idx.push_back(q);
+        }
         const size_t m = h.m;
         Group *G = nullptr;
         if (Q.plan == CS_PLAN_SPECTRAL) {
@@ -1389,16 +1404,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 B.group = G;
                 B.pair_off = -1;
                 B.norm_off = norm_off;
-                for (int t = 0; t < d; ++t) {
-                    SkDesc S;
-                    S.p = base + (size_t)t * m;
-                    S.log2m = L;
-                    S.m = h.m;
-                    S.nb = nb;
-                    S.off = norm_off;
-                    norm_off += nb;
-                    sd.push_back(S);
-                }
+                nd.push_back(NormDesc{base, norm_off, h.m, d, nb, 0});
+                norm_off += (int64_t)d * nb;
                 if (G) {
                     B.mod0 = (int32_t)G->mod_ptrs.size();
                     B.vec0 = (int32_t)G->re.size();
@@ -1427,44 +1434,15 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             }
         }
         for (size_t k = 0; k < q_blocks.size(); ++k) {
-            Q.norm_off[k] = blocks[q_blocks[k]].norm_off;
-            Q.pair_off[k] = blocks[q_blocks[k]].pair_off;
+            const RelBlock &B = blocks[q_blocks[k]];
+            Q.norm_off[k] = B.norm_off;
+            Q.pair_off[k] = B.pair_off;
+            Q.vec0[k] = B.vec0;
+            Q.last[k] = B.last;
+            Q.mod0[k] = B.mod0;
         }
         if (Q.plan == CS_PLAN_GENERAL) general_q.push_back(q);
-        for (int t = 0; t < d; ++t) {
-            RepDesc D{};
-            D.c0 = rel_counters(h, 0) + (size_t)t * m;
-            D.c1 = rel_counters(h, 1) + (size_t)t * m;
-            D.q = q;
-            D.t = t;
-            D.log2m = L;
-            D.S = split_of(L);
-            D.m = h.m;
-            D.r = r;
-            D.d = d;
-            D.conj = h.g.conj_mask;
-            D.nb = nb;
-            for (size_t k = 0; G && k < q_blocks.size(); ++k) {
-                const RelBlock &B = blocks[q_blocks[k]];
-                D.zv[k] = (t ^ 1) < d ? 2 * B.vec0 + t : B.last;
-                D.mv[k] = B.mod0 + t;
-            }
-            D.spec_off = spec_off;
-            D.dot_off = dot_off;
-            D.mod_off = mod_off;
-            mod_off += nb;
-            if (Q.plan == CS_PLAN_SPECTRAL) {
-                spec_off += (int64_t)nb * (2 + r);
-                G->rep_idx.push_back((int32_t)rd.size());
-            }
-            if (Q.plan == CS_PLAN_DOT) {
-                dot_off += nb;
-                dot_idx.push_back((int32_t)rd.size());
-            }
-            rd.push_back(D);
-        }
     }
-    const int n_rep = (int)rd.size();
     const int64_t mod_plane = mod_off;
     if (async_out && !general_q.empty())
         return fail(CS_EINVAL, "asynchronous estimates need queries without the general plan");
@@ -1472,25 +1450,27 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     // ---- workspace layout
     Carve c;
     const size_t o_q = c.take(qd.size() * sizeof(QDesc));
-    const size_t o_rep = c.take(rd.size() * sizeof(RepDesc));
-    const size_t o_sk = c.take(std::max<size_t>(1, sd.size()) * sizeof(SkDesc));
-    const size_t o_dotidx = c.take(std::max<size_t>(1, dot_idx.size()) * sizeof(int32_t));
-    // block prefixes of the flattened launches
-    std::vector<int64_t> sk_pre(sd.size() + 1, 0), dot_pre(dot_idx.size() + 1, 0);
-    for (size_t i = 0; i < sd.size(); ++i) sk_pre[i + 1] = sk_pre[i] + sd[i].nb;
-    for (size_t i = 0; i < dot_idx.size(); ++i) dot_pre[i + 1] = dot_pre[i] + rd[dot_idx[i]].nb;
-    const size_t o_skpre = c.take(sk_pre.size() * sizeof(int64_t));
+    const size_t o_nd = c.take(nd.size() * sizeof(NormDesc));
+    const size_t o_dotidx = c.take(dot_idx.size() * sizeof(int32_t));
+    // block prefixes of the flattened launches (an item is a relation or a query)
+    auto prefix_of = [](size_t n, auto &&blocks_of) {
+        std::vector<int64_t> pre(n + 1, 0);
+        for (size_t i = 0; i < n; ++i) pre[i + 1] = pre[i] + blocks_of(i);
+        return pre;
+    };
+    auto q_blocks_of = [&](int32_t q) { return (int64_t)qd[q].d * qd[q].nb; };
+    const std::vector<int64_t> nd_pre = prefix_of(nd.size(), [&](size_t i) { return (int64_t)nd[i].d * nd[i].nb; });
+    const std::vector<int64_t> dot_pre = prefix_of(dot_idx.size(), [&](size_t i) { return q_blocks_of(dot_idx[i]); });
+    const size_t o_ndpre = c.take(nd_pre.size() * sizeof(int64_t));
     const size_t o_dotpre = c.take(dot_pre.size() * sizeof(int64_t));
     std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr;
     std::vector<std::vector<int64_t>> g_pre;
     size_t z_total = 0;
     for (auto &kv : groups) {
         Group &G = kv.second;
-        o_gidx.push_back(c.take(G.rep_idx.size() * sizeof(int32_t)));
-        std::vector<int64_t> pre(G.rep_idx.size() + 1, 0);
-        for (size_t i = 0; i < G.rep_idx.size(); ++i) pre[i + 1] = pre[i] + rd[G.rep_idx[i]].nb;
-        o_gpre.push_back(c.take(pre.size() * sizeof(int64_t)));
-        g_pre.push_back(std::move(pre));
+        o_gidx.push_back(c.take(G.queries.size() * sizeof(int32_t)));
+        g_pre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_blocks_of(G.queries[i]); }));
+        o_gpre.push_back(c.take(g_pre.back().size() * sizeof(int64_t)));
         o_gre.push_back(c.take(G.re.size() * sizeof(void *)));
         o_gim.push_back(c.take(G.im.size() * sizeof(void *)));
         o_gptr.push_back(c.take(G.mod_ptrs.size() * sizeof(void *)));
@@ -1504,7 +1484,6 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const size_t o_modp = c.take((size_t)kMaxPrimes * std::max<int64_t>(1, mod_plane) * sizeof(uint32_t));
     const size_t o_rs = c.take((size_t)n_rep * sizeof(RepDev));  // [records | outputs]: one download
     const size_t o_outs = c.take((size_t)nq * sizeof(OutDev));
-    const size_t o_kp = c.take((size_t)n_rep * sizeof(int32_t));
     const size_t o_Z = c.take(z_total);
     if (ws.bytes < c.off) {
         if (ws.buf) {
@@ -1554,38 +1533,45 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     } img{hb + h_img, host_tables};
     std::memset(img.data(), 0, img.size());
     std::memcpy(img.data() + o_q, qd.data(), qd.size() * sizeof(QDesc));
-    std::memcpy(img.data() + o_rep, rd.data(), rd.size() * sizeof(RepDesc));
-    if (!sd.empty()) std::memcpy(img.data() + o_sk, sd.data(), sd.size() * sizeof(SkDesc));
-    if (!dot_idx.empty()) std::memcpy(img.data() + o_dotidx, dot_idx.data(), dot_idx.size() * sizeof(int32_t));
-    std::memcpy(img.data() + o_skpre, sk_pre.data(), sk_pre.size() * sizeof(int64_t));
-    std::memcpy(img.data() + o_dotpre, dot_pre.data(), dot_pre.size() * sizeof(int64_t));
+    auto put = [&](size_t at, const auto &v) {
+        if (!v.empty()) std::memcpy(img.data() + at, v.data(), v.size() * sizeof(v[0]));
+    };
+    put(o_nd, nd);
+    put(o_dotidx, dot_idx);
+    put(o_ndpre, nd_pre);
+    put(o_dotpre, dot_pre);
     {
         int gi = 0;
         for (auto &kv : groups) {
             Group &G = kv.second;
-            std::memcpy(img.data() + o_gidx[gi], G.rep_idx.data(), G.rep_idx.size() * sizeof(int32_t));
-            std::memcpy(img.data() + o_gpre[gi], g_pre[gi].data(), g_pre[gi].size() * sizeof(int64_t));
-            std::memcpy(img.data() + o_gre[gi], G.re.data(), G.re.size() * sizeof(void *));
-            std::memcpy(img.data() + o_gim[gi], G.im.data(), G.im.size() * sizeof(void *));
-            std::memcpy(img.data() + o_gptr[gi], G.mod_ptrs.data(), G.mod_ptrs.size() * sizeof(void *));
+            put(o_gidx[gi], G.queries);
+            put(o_gpre[gi], g_pre[gi]);
+            put(o_gre[gi], G.re);
+            put(o_gim[gi], G.im);
+            put(o_gptr[gi], G.mod_ptrs);
             ++gi;
         }
     }
-    CSK_HIP(hipMemcpyAsync(wb, img.data(), img.size(), hipMemcpyHostToDevice, s));
+    if (host_tables <= kDirectTables) {
+        const uint32_t words = (uint32_t)(host_tables / sizeof(uint4));  // pieces are multiples of 256 bytes
+        hipLaunchKernelGGL(k_copy_tables, dim3((words + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
+                           reinterpret_cast<uint4 *>(wb), reinterpret_cast<const uint4 *>(img.data()), words);
+        CSK_HIP(hipGetLastError());
+    } else {
+        CSK_HIP(hipMemcpyAsync(wb, img.data(), img.size(), hipMemcpyHostToDevice, s));
+    }
     if (async_out) {
         if (!ws.ev_upload) CSK_HIP(hipEventCreateWithFlags(&ws.ev_upload, hipEventDisableTiming));
         CSK_HIP(hipEventRecord(ws.ev_upload, s));
         ws.upload_pending = true;
     }
-    const QDesc *d_q = reinterpret_cast<const QDesc *>(wb + o_q);
-    RepDesc *d_rep = reinterpret_cast<RepDesc *>(wb + o_rep);
-    const SkDesc *d_sk = reinterpret_cast<const SkDesc *>(wb + o_sk);
+    QDesc *d_q = reinterpret_cast<QDesc *>(wb + o_q);
+    const NormDesc *d_nd = reinterpret_cast<const NormDesc *>(wb + o_nd);
     double *d_norms = reinterpret_cast<double *>(wb + o_norms);
     double *d_spec = reinterpret_cast<double *>(wb + o_spec);
     unsigned long long *d_dot = reinterpret_cast<unsigned long long *>(wb + o_dot);
     uint32_t *d_modp = reinterpret_cast<uint32_t *>(wb + o_modp);
     RepDev *d_rs = reinterpret_cast<RepDev *>(wb + o_rs);
-    int32_t *d_kp = reinterpret_cast<int32_t *>(wb + o_kp);
     OutDev *d_outs = reinterpret_cast<OutDev *>(wb + o_outs);
 
     // ---- speculative modular step: when no query has a general plan and the workspace
@@ -1649,9 +1635,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                                  G.S, primes, groots[gi], ms);
                 if (st != CS_OK) return st;
                 hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N,
-                                   vpp, d_rep, reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
-                                   reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.rep_idx.size(),
-                                   primes, mod_plane, d_modp, nullptr);
+                                   vpp, d_q, reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
+                                   reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.queries.size(),
+                                   primes, mod_plane, d_modp);
                 CSK_HIP(hipGetLastError());
                 ++gi;
             }
@@ -1660,13 +1646,13 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     }
 
     // ---- stage 1
-    if (!sd.empty()) {
-        hipLaunchKernelGGL(k_norms, dim3((unsigned)sk_pre.back()), dim3(kThreads), 0, s, d_sk,
-                           reinterpret_cast<const int64_t *>(wb + o_skpre), (int)sd.size(), d_norms);
+    if (!nd.empty()) {
+        hipLaunchKernelGGL(k_norms, dim3((unsigned)nd_pre.back()), dim3(kThreads), 0, s, d_nd,
+                           reinterpret_cast<const int64_t *>(wb + o_ndpre), (int)nd.size(), d_norms);
         CSK_HIP(hipGetLastError());
     }
     if (!dot_idx.empty()) {
-        hipLaunchKernelGGL(k_dot, dim3((unsigned)dot_pre.back()), dim3(kThreads), 0, s, d_rep,
+        hipLaunchKernelGGL(k_dot, dim3((unsigned)dot_pre.back()), dim3(kThreads), 0, s, d_q,
                            reinterpret_cast<const int32_t *>(wb + o_dotidx),
                            reinterpret_cast<const int64_t *>(wb + o_dotpre), (int)dot_idx.size(), d_dot);
         CSK_HIP(hipGetLastError());
@@ -1682,9 +1668,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                                  reinterpret_cast<const int64_t *const *>(wb + o_gim[gi]), (int)G.re.size(), Z,
                                  G.log2m, G.S, tw, s);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_pre[gi].back()), dim3(kThreads), 0, s, Z, d_rep,
+            hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_pre[gi].back()), dim3(kThreads), 0, s, Z, d_q,
                                reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
-                               reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.rep_idx.size(), d_spec);
+                               reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.queries.size(), d_spec);
             CSK_HIP(hipGetLastError());
             ++gi;
         }
@@ -1692,8 +1678,6 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     if (overlap) CSK_HIP(hipStreamWaitEvent(s, ws.ev_join, 0));  // the modular chain joins here
     FinalizeArgs fa{};
     fa.qs = d_q;
-    fa.reps = d_rep;
-    fa.sks = d_sk;
     fa.norms = d_norms;
     fa.spec = d_spec;
     fa.dot = d_dot;
@@ -1703,7 +1687,11 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     fa.crt = g_crt;
     fa.rs = d_rs;
     fa.outs = d_outs;
-    fa.kp = d_kp;
+    const bool direct = !async_out && n_rep <= kDirectReps;
+    if (direct) {
+        fa.rs_host = hr;
+        fa.outs_host = ho;
+    }
     fa.kcap = kMaxPrimes;
     if (spec) {
         // both finalize stages in one launch
@@ -1726,7 +1714,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         CSK_HIP(hipGetLastError());
         return CS_OK;
     }
-    CSK_HIP(hipMemcpyAsync(hr, d_rs, (o_outs - o_rs) + nq * sizeof(OutDev), hipMemcpyDeviceToHost, s));
+    if (!direct) CSK_HIP(hipMemcpyAsync(hr, d_rs, (o_outs - o_rs) + nq * sizeof(OutDev), hipMemcpyDeviceToHost, s));
     st = wait_results(s);
     if (st != CS_OK) return st;
     {
@@ -1778,12 +1766,29 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         }
         char *mod_cur = static_cast<char *>(ws.mod);
         char *mod_host = hb + h_mod;
-        // spectral groups: every repetition of a query that needs one is recomputed
+        // spectral groups: every repetition of a query that needs one is recomputed; their
+        // mod0 then name vectors of their group's buffer, set for all groups and uploaded once
+        bool moved = false;
+        for (auto &kv : groups) {
+            int32_t vec = 0;
+            for (int32_t q : kv.second.queries) {
+                int kq = 0;
+                for (int t = 0; t < qd[q].d; ++t) kq = std::max(kq, hr[qd[q].rep_base + t].kprimes);
+                if (kq <= kdone) continue;
+                for (int k = 0; k < qd[q].r; ++k, vec += qd[q].d) qd[q].mod0[k] = vec;
+                moved = true;
+            }
+        }
+        if (moved) {
+            // the staging area's first upload has ended (the results came behind it)
+            std::memcpy(img.data() + o_q, qd.data(), qd.size() * sizeof(QDesc));
+            CSK_HIP(hipMemcpyAsync(d_q, img.data() + o_q, qd.size() * sizeof(QDesc), hipMemcpyHostToDevice, s));
+        }
         for (auto &kv : groups) {
             Group &G = kv.second;
             int K = 0;
-            std::vector<int> needq;
-            for (int q : G.queries) {
+            std::vector<int32_t> needq;
+            for (int32_t q : G.queries) {
                 int kq = 0;
                 for (int t = 0; t < qd[q].d; ++t) kq = std::max(kq, hr[qd[q].rep_base + t].kprimes);
                 if (kq > kdone) {
@@ -1795,42 +1800,30 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             const ModTables roots = mod_tables(device, G.log2m, s, &st);
             if (!roots.full) return st;
             std::vector<const int64_t *> ptrs;
-            std::vector<int32_t> idx;
-            for (int q : needq) {
-                const int base = (int)ptrs.size();
+            for (int32_t q : needq)
                 for (int k = 0; k < qd[q].r; ++k)
                     for (int t = 0; t < qd[q].d; ++t) ptrs.push_back(rel_counters(*hs[q], k) + (size_t)t * hs[q]->m);
-                for (int t = 0; t < qd[q].d; ++t) {
-                    RepDesc &D = rd[qd[q].rep_base + t];
-                    for (int k = 0; k < D.r; ++k) D.mv[k] = base + k * D.d + t;
-                    idx.push_back(qd[q].rep_base + t);
-                }
-            }
             const int vpp = (int)ptrs.size();
             const size_t m = (size_t)1 << G.log2m;
-            std::vector<int64_t> mpre(idx.size() + 1, 0);
-            for (size_t i = 0; i < idx.size(); ++i) mpre[i + 1] = mpre[i] + rd[idx[i]].nb;
-            const size_t o_mpre = align_up(ptrs.size() * sizeof(void *)) + align_up(idx.size() * sizeof(int32_t));
+            const std::vector<int64_t> mpre = prefix_of(needq.size(), [&](size_t i) { return q_blocks_of(needq[i]); });
+            const size_t o_idx = align_up(ptrs.size() * sizeof(void *));
+            const size_t o_mpre = o_idx + align_up(needq.size() * sizeof(int32_t));
             const size_t tab_bytes = o_mpre + align_up(mpre.size() * sizeof(int64_t));
             char *mbc = mod_cur;
             mod_cur += tab_bytes + align_up((size_t)K * vpp * m * sizeof(uint32_t));
             char *mimg = mod_host;  // pinned; stays untouched until the call returns
             mod_host += tab_bytes;
             std::memcpy(mimg, ptrs.data(), ptrs.size() * sizeof(void *));
-            std::memcpy(mimg + align_up(ptrs.size() * sizeof(void *)), idx.data(), idx.size() * sizeof(int32_t));
+            std::memcpy(mimg + o_idx, needq.data(), needq.size() * sizeof(int32_t));
             std::memcpy(mimg + o_mpre, mpre.data(), mpre.size() * sizeof(int64_t));
             CSK_HIP(hipMemcpyAsync(mbc, mimg, tab_bytes, hipMemcpyHostToDevice, s));
-            // updated mv of these repetitions
-            for (int q : needq)
-                CSK_HIP(hipMemcpyAsync(d_rep + qd[q].rep_base, rd.data() + qd[q].rep_base, qd[q].d * sizeof(RepDesc),
-                                       hipMemcpyHostToDevice, s));
             uint32_t *N = reinterpret_cast<uint32_t *>(mbc + tab_bytes);
             st = ntt_forward(ModSrc::from_table(reinterpret_cast<const int64_t *const *>(mbc)), vpp, K, N, G.log2m, G.S, primes, roots, s);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)mpre.back(), K), dim3(kThreads), 0, s, N, vpp, d_rep,
-                               reinterpret_cast<const int32_t *>(mbc + align_up(ptrs.size() * sizeof(void *))),
-                               reinterpret_cast<const int64_t *>(mbc + o_mpre), (int)idx.size(), primes,
-                               mod_plane, d_modp, nullptr);
+            hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)mpre.back(), K), dim3(kThreads), 0, s, N, vpp, d_q,
+                               reinterpret_cast<const int32_t *>(mbc + o_idx),
+                               reinterpret_cast<const int64_t *>(mbc + o_mpre), (int)needq.size(), primes,
+                               mod_plane, d_modp);
             CSK_HIP(hipGetLastError());
         }
         // general plans: Alg. 3's register program per query
@@ -1943,7 +1936,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             }
             if (!two) sum_a = val[h.g.result_reg];
             hipLaunchKernelGGL(k_mod_sum, dim3(qd[q].nb, K * d), dim3(kThreads), 0, s, sum_a, sum_b, two, m, d, primes,
-                               qd[q].nb, d_rep, qd[q].rep_base, mod_plane, d_modp);
+                               qd[q].nb, qd[q].mod_off, mod_plane, d_modp);
             CSK_HIP(hipGetLastError());
         }
         fa.stage = 2;
@@ -1951,9 +1944,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         if (nq <= 256) hipLaunchKernelGGL((k_finalize<2, kFinThreadsFew>), dim3(nq), dim3(kFinThreadsFew), 0, s, fa);
         else hipLaunchKernelGGL((k_finalize<2, kFinThreadsMany>), dim3(nq), dim3(kFinThreadsMany), 0, s, fa);
         CSK_HIP(hipGetLastError());
-        CSK_HIP(hipMemcpyAsync(ho, d_outs, nq * sizeof(OutDev), hipMemcpyDeviceToHost, s));
-        if (reps_out) CSK_HIP(hipMemcpyAsync(hr, d_rs, n_rep * sizeof(RepDev), hipMemcpyDeviceToHost, s));
-        CSK_HIP(hipStreamSynchronize(s));
+        if (!direct) CSK_HIP(hipMemcpyAsync(ho, d_outs, nq * sizeof(OutDev), hipMemcpyDeviceToHost, s));
+        if (!direct && reps_out) CSK_HIP(hipMemcpyAsync(hr, d_rs, n_rep * sizeof(RepDev), hipMemcpyDeviceToHost, s));
+        if ((st = wait_results(s)) != CS_OK) return st;
     }
     for (int q = 0; q < nq; ++q) {
         cs_estimate_t &o = outs[q];

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include <algorithm>
+#include <cmath>
 #include <map>
 #include <mutex>
 
@@ -49,10 +50,9 @@ __global__ __launch_bounds__(kBlock) void k_update_global(const uint32_t *__rest
         uint32_t x[NC];
         load_keys<NC>(keys, i, vec2, x);
         const int64_t delta = weights ? weights[i] : 1;
-        const uint64_t *cf = coef;
-        for (int t = 0; t < d; ++t, cf += cpr) {
+        for (int t = blockIdx.y; t < d; t += gridDim.y) {
             uint32_t j, neg;
-            hash_rep<NC>(cf, plan, x, j, neg);
+            hash_rep<NC>(coef + (size_t)t * cpr, plan, x, j, neg);
             const uint64_t val = neg ? (uint64_t)0 - (uint64_t)delta : (uint64_t)delta;
             atomicAdd(sketch + (size_t)t * m + j, (unsigned long long)val);
         }
@@ -1688,7 +1688,10 @@ cs_status launch_nc(const UpdateArgs &a, int strategy, int grid_blocks, hipStrea
         if (blocks > need) blocks = need;
         CSK_MARK(a.ev_start, s);
         if (strategy == CS_UPDATE_GLOBAL_ATOMIC)
-            hipLaunchKernelGGL(k_update_global<NC>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a.keys,
+            // few tuples: a workgroup per repetition as well, while they fit one round (a
+            // thousand one-column tuples, d = 5: 4.6 us, the five in turn 8 us)
+            hipLaunchKernelGGL(k_update_global<NC>,
+                               dim3((unsigned)blocks, blocks * a.d <= (uint64_t)n_cu ? (unsigned)a.d : 1u), dim3(kBlock), 0, s, a.keys,
                                a.weights, a.n, a.coef, a.plan.coef_per_rep, sk, a.m, a.d, plan, vec2);
         else
             hipLaunchKernelGGL(k_update_waveagg<NC>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a.keys,
@@ -1930,6 +1933,8 @@ static SegGeom balanced_geometry(uint32_t m, int32_t d, uint32_t max_r, int elem
     const uint64_t cells = (uint64_t)d * m;
     const uint64_t cap = std::min<uint64_t>(256, std::max<uint64_t>(1, scratch_bytes / (cells * elem)));
     const int32_t q_max = m <= max_r ? (int32_t)std::min<uint64_t>(d, max_r / m) : 1;
+    const double per_chunk = (double)cells * elem * 2 / 4e6 + 0.03;  // us of partial sums
+    const double kilo = (double)n / 1024.0;
     SegGeom best{};
     double best_us = 0.0;
     int32_t last_segments = 0;
@@ -1939,24 +1944,30 @@ static SegGeom balanced_geometry(uint32_t m, int32_t d, uint32_t max_r, int elem
         g.segments = (int32_t)((cells + g.R - 1) / g.R);
         if (g.segments == last_segments) continue;
         last_segments = g.segments;
-        const double lds = (double)g.R * elem / 131072.0;       // share of 128 KB
-        const double fixed = 1.5 + 1.5 * lds;                    // us
-        const int per_round = lds <= 0.6 ? 512 : 256;            // two workgroups per CU when two fit
-        for (int32_t c = 1; c <= (int32_t)cap; c += c < 8 ? 1 : c / 8) {
-            // whole rounds: also the largest count that fits the rounds c needs
-            for (int32_t C : {c, (int32_t)std::min<uint64_t>(cap, 256 * ((g.segments * (uint64_t)c + 255) / 256) / g.segments)}) {
-                const uint64_t wgs = (uint64_t)g.segments * C;
-                const double iters = (double)((n / C >> 10) + 1);  // of 1024 tuples
-                const double us = fixed * ((wgs + per_round - 1) / per_round) +
-                                  0.3 * iters * q * ((wgs + 255) / 256) + (double)C * cells * elem * 2 / 4e6 +
-                                  0.03 * C;
-                if (best.chunks == 0 || us < best_us) {
-                    best = g;
-                    best.chunks = C;
-                    best_us = us;
-                }
+        const double lds = (double)g.R * elem / 131072.0;  // share of 128 KB
+        const double fixed = 1.5 + 1.5 * lds;               // us
+        const uint64_t per_round = lds <= 0.6 ? 512 : 256;  // two workgroups per CU when two fit
+        auto consider = [&](double c) {
+            const int32_t C = (int32_t)std::max(1.0, std::min((double)cap, c));
+            const uint64_t wgs = (uint64_t)g.segments * C;
+            const double us = fixed * ((wgs + per_round - 1) / per_round) +
+                              0.3 * (std::floor(kilo / C) + 1.0) * q * ((wgs + 255) / 256) + C * per_chunk;
+            if (best.chunks == 0 || us < best_us) {
+                best = g;
+                best.chunks = C;
+                best_us = us;
             }
-        }
+        };
+        // within one round the time is a / C + b C, least at c0 (the iterations are whole: also
+        // the counts that just save one); else whole rounds of workgroups, and the small counts
+        const double c0 = std::min((double)cap, std::sqrt(0.3 * kilo * q / per_chunk));
+        const int32_t one = 256 / g.segments;
+        const double it = std::floor(kilo / std::max(1.0, c0));
+        consider(c0);
+        for (double i : {it, it + 1.0, it - 1.0})
+            if (i > 0.0) consider(std::floor(kilo / i) + 1.0);
+        for (int k = 1; k < 8 && one < 8; ++k) consider(k);
+        for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(256 * k / g.segments);
     }
     return best;
 }
