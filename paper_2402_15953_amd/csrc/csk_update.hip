@@ -940,11 +940,11 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(const CT *__restrict__ pa
 // miss a key of 6% of the stream in a third of the blocks; the hints carry the stream's
 // heavy keys from one update call to the next.
 //
-// Pass 2 (k_part_accum): workgroup (range r, repetition t) zeroes two copies of 2^14
-// int32 LDS counters (even and odd lanes add to different copies, which halves the
-// lanes of one add that meet on a skewed bucket's word), adds +-1 for every record of
-// its group from every block (8-byte loads of four records, four runs in flight per
-// wavefront), adds the hot tuples whose bucket falls in its range, and adds the non-zero
+// Pass 2 (k_part_accum): workgroup (range r, repetition t) zeroes 2^14 int32 LDS counters
+// (two copies where the grid fits the CUs: even and odd lanes add to different ones, which
+// halves the lanes of one add that meet on a skewed bucket's word), adds +-1 for every
+// record of its group from every block (8-byte loads of four records, four runs in flight
+// per group of lanes), adds the hot tuples whose bucket falls in its range, and adds the non-zero
 // sums of the two copies into the sketch (it owns those counters: plain
 // read-modify-write, no atomics).  One extra workgroup writes the relation's hints: the
 // distinct hot tuples of the first eight blocks, ranked by their |Delta sum| over all
@@ -1505,30 +1505,34 @@ __device__ void part_hints(const PartHot *__restrict__ hot, uint64_t nblk, PartH
 }
 static_assert(8 * kPartHot == 64, "one wavefront ranks the hint candidates");
 
-// Pass 2.  Block (range r, repetition t).
-template <int NC, bool FAST>
+// Pass 2.  Block (range r, repetition t).  COPIES: counter copies, 2 where a workgroup per
+// CU covers the grid, else 1 (64 KB, two workgroups share a CU).  log2w: lanes that read a
+// run together.
+template <int NC, bool FAST, int COPIES>
 __global__ __launch_bounds__(kPAB) void k_part_accum(const uint16_t *__restrict__ rec,
                                                      const uint16_t *__restrict__ tab,
                                                      const PartHot *__restrict__ hot, uint64_t nblk,
                                                      int32_t ranges, uint32_t m, const uint64_t *__restrict__ coef,
                                                      int32_t cpr, DevPlan plan, uint64_t *sketch,
-                                                     uint32_t canon_thresh, int32_t d, PartHints *hints_out)
+                                                     uint32_t canon_thresh, int32_t d, PartHints *hints_out,
+                                                     int32_t log2w)
 {
     extern __shared__ __align__(16) uint32_t s_dyn[];
     if ((int)blockIdx.y == d) {  // the hints workgroup (row d of the grid: column 0 only)
         if (blockIdx.x == 0 && hints_out) part_hints(hot, nblk, hints_out);
         return;
     }
-    // two copies of the counters, taken by even and odd lanes: the lanes of one add that
+    // two copies of the counters are taken by even and odd lanes: the lanes of one add that
     // hit a skewed bucket's word are split over two words
-    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_dyn);   // [2][kPartR]
-    uint32_t *s_run = s_dyn + 2 * kPartR;                   // [nblk]: start / 4 | words << 16
+    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_dyn);  // [COPIES][kPartR]
+    uint32_t *s_run = s_dyn + COPIES * kPartR;             // [nblk]: start / 4 | words << 16
     const int r = blockIdx.x, t = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t *my_cnt = s_cnt + (lane & 1) * kPartR;
+    int32_t *my_cnt = s_cnt + (lane & (COPIES - 1)) * kPartR;
     constexpr int kWaves = kPAB / 64;
-    constexpr int kInFlight = 4;  // runs per wavefront whose loads are issued together
-    for (uint32_t e = threadIdx.x; e < 2 * kPartR / 4; e += kPAB) reinterpret_cast<int4 *>(s_cnt)[e] = make_int4(0, 0, 0, 0);
+    constexpr int kInFlight = 4;  // runs per group of lanes whose loads are issued together
+    for (uint32_t e = threadIdx.x; e < COPIES * kPartR / 4; e += kPAB)
+        reinterpret_cast<int4 *>(s_cnt)[e] = make_int4(0, 0, 0, 0);
     for (uint64_t b = threadIdx.x; b < nblk; b += kPAB) {
         const uint16_t *tb = tab + ((uint64_t)t * nblk + b) * (uint64_t)(ranges + 1);
         const uint32_t beg = tb[r], end = tb[r + 1];  // multiples of 4
@@ -1541,26 +1545,45 @@ __global__ __launch_bounds__(kPAB) void k_part_accum(const uint16_t *__restrict_
         for (int k = 0; k < 4; ++k)
             if (v[k] != kPartPad) atomicAdd(&my_cnt[v[k] & (kPartR - 1)], (v[k] >> kPartLog2R) & 1u ? -1 : 1);
     };
-    // records: wavefront w takes blocks w, w + kWaves, ..., kInFlight of them at a time;
-    // a run of L words is read by lanes 0..L-1 (one 8-byte word of four records each)
+    // two copies: this thread's words of the sketch are fetched while the records are added
+    // (one copy leaves no registers for them with two workgroups in a CU)
+    uint64_t *out = sketch + (uint64_t)t * m + ((uint64_t)r << kPartLog2R);
+    const uint32_t span = min(kPartR, m - ((uint32_t)r << kPartLog2R));  // the last range may be partial
+    constexpr int kOwn = kPartR / kPAB;
+    uint64_t own[COPIES == 2 ? kOwn : 1];
+    if constexpr (COPIES == 2) {
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) own[u] = threadIdx.x + u * kPAB < span ? out[threadIdx.x + u * kPAB] : 0u;
+    }
+    // records: a group of 2^log2w lanes takes kInFlight blocks at a time, a run's 8-byte
+    // words (four records each) in turn, the next ones in flight while these are added
     const uint2 *rt = reinterpret_cast<const uint2 *>(rec + (uint64_t)t * nblk * kPartBlkCap);
-    for (uint64_t b0 = wave; b0 < nblk; b0 += (uint64_t)kWaves * kInFlight) {
-        uint32_t run[kInFlight];
+    const uint32_t width = 1u << log2w, sub = (uint32_t)lane & (width - 1u);
+    const uint32_t groups = 64u >> log2w;  // per wavefront
+    for (uint64_t b0 = (uint64_t)wave * groups + ((uint32_t)lane >> log2w); b0 < nblk;
+         b0 += (uint64_t)kWaves * groups * kInFlight) {
+        uint32_t len[kInFlight];
         const uint2 *p[kInFlight];
+        uint2 w[kInFlight];
         uint32_t lmax = 0;
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-            const uint64_t b = b0 + (uint64_t)u * kWaves;
-            run[u] = b < nblk ? s_run[b] : 0u;
-            p[u] = rt + (b < nblk ? b : 0) * (kPartBlkCap / 4) + (run[u] & 0xFFFFu);
-            lmax = max(lmax, run[u] >> 16);
+            const uint64_t b = b0 + (uint64_t)u * kWaves * groups;
+            const uint32_t run = b < nblk ? s_run[b] : 0u;
+            len[u] = run >> 16;
+            p[u] = rt + (b < nblk ? b : 0) * (kPartBlkCap / 4) + (run & 0xFFFFu);
+            lmax = max(lmax, len[u]);
+            w[u] = sub < len[u] ? p[u][sub] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
         }
-        for (uint32_t i = lane; i < lmax; i += 64) {
-            uint2 w[kInFlight];
+        for (uint32_t i = sub; i < lmax; i += width) {
+            uint2 next[kInFlight];
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) w[u] = i < (run[u] >> 16) ? p[u][i] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
+            for (int u = 0; u < kInFlight; ++u)
+                next[u] = i + width < len[u] ? p[u][i + width] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) add4(w[u]);
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) w[u] = next[u];
         }
     }
     // hot tuples of every wavefront quarter whose bucket falls in this range
@@ -1585,11 +1608,30 @@ __global__ __launch_bounds__(kPAB) void k_part_accum(const uint16_t *__restrict_
         }
     }
     __syncthreads();
-    uint64_t *out = sketch + (uint64_t)t * m + ((uint64_t)r << kPartLog2R);
-    const uint32_t span = min(kPartR, m - ((uint32_t)r << kPartLog2R));  // the last range may be partial
-    for (uint32_t e = threadIdx.x; e < span; e += kPAB) {
-        const int64_t v = (int64_t)s_cnt[e] + (int64_t)s_cnt[kPartR + e];
-        if (v) out[e] += (uint64_t)v;
+    if constexpr (COPIES == 2) {
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            const uint32_t e = threadIdx.x + u * kPAB;
+            const int64_t v = (int64_t)s_cnt[e] + (int64_t)s_cnt[kPartR + e];
+            if (e < span && v) out[e] = own[u] + (uint64_t)v;
+        }
+        return;
+    }
+    constexpr int U = 8;  // counters per thread whose loads are issued together
+    for (uint32_t e0 = threadIdx.x; e0 < span; e0 += kPAB * U) {
+        int64_t v[U];
+        uint64_t o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = e0 + u * kPAB;
+            v[u] = 0;
+            if (e < span) v[u] = s_cnt[e];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = v[u] ? out[e0 + u * kPAB] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v[u]) out[e0 + u * kPAB] = o[u] + (uint64_t)v[u];
     }
 }
 
@@ -1902,14 +1944,24 @@ cs_status launch_nc(const UpdateArgs &a, int strategy, int grid_blocks, hipStrea
                                    a.canon_thresh, ab, a.n_attrs, fs, a.kept, a.hints);
                 CSK_HIP(hipGetLastError());
                 if (one_chunk) CSK_MARK(a.ev_stop, s);
-                auto ak = fast ? &k_part_accum<NC, true> : &k_part_accum<NC, false>;
-                const size_t lds = (size_t)kPartR * 8 + (size_t)nblk * 4;
+                // one counter copy where a workgroup per CU is not enough for the grid: two
+                // share a CU then (310 workgroups, one- and two-column relations of 2 * 10^6
+                // tuples: 60 and 45 us; two copies in two rounds 73 and 65)
+                const bool one_copy = (uint64_t)pg.ranges * a.d > (uint64_t)n_cu;
+                auto ak = fast ? (one_copy ? &k_part_accum<NC, true, 1> : &k_part_accum<NC, true, 2>)
+                               : (one_copy ? &k_part_accum<NC, false, 1> : &k_part_accum<NC, false, 2>);
+                const size_t lds = (size_t)kPartR * (one_copy ? 4 : 8) + (size_t)nblk * 4;
+                // lanes that read a run of about 1024 / ranges words together: so many that a run
+                // takes them a few times and few idle at its end (16 ranges: 16 lanes 23.4 us,
+                // 64 lanes 25.1; 62 ranges: 8 to 32 lanes 44-45 us, 64 lanes 47.4)
+                int log2w = 6;
+                while (log2w > 3 && (1024 / pg.ranges) < (3 << (log2w - 1))) --log2w;
                 CSK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ak),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
                 // grid row d: the workgroup that writes the relation's hints
                 hipLaunchKernelGGL(ak, dim3((unsigned)pg.ranges, (unsigned)a.d + (a.hints ? 1u : 0u)), dim3(kPAB), lds,
                                    s, rec, tab, hot, nblk, pg.ranges, a.m, a.coef, a.plan.coef_per_rep, plan,
-                                   a.sketch, a.canon_thresh, a.d, a.hints);
+                                   a.sketch, a.canon_thresh, a.d, a.hints, log2w);
                 CSK_HIP(hipGetLastError());
             }
             if (!one_chunk) CSK_MARK(a.ev_stop, s);
