@@ -222,6 +222,7 @@ struct QDesc {
     const int64_t *c0, *c1;  // DOT plan: relations 0 and 1 [d][m]
     int32_t plan, r, d, log2m, rep_base;
     int32_t nb;              // blocks of a repetition's reductions
+    int32_t nbm;             // modular partials of a repetition
     int32_t S;               // row length 2^S of the two-pass transforms of this length
     uint32_t m;              // buckets (log2m is exact only for powers of two)
     uint32_t conj;           // SPECTRAL: relations taken conjugated
@@ -241,18 +242,6 @@ struct QDesc {
 };
 
 // ---------------------------------------------------------------- kernels
-
-// Flattened launches: block b belongs to item i with prefix[i] <= b < prefix[i + 1].
-__device__ __forceinline__ int find_item(const int64_t *__restrict__ prefix, int n, int64_t b)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
 
 // Sum of squares and of absolute values of each sketch vector (fp64), per block.
 __global__ __launch_bounds__(kThreads) void k_norms(const NormDesc *__restrict__ rels,
@@ -633,11 +622,12 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
         for (int o = wv; o < Q.d && (STAGE == 2 || plan == CS_PLAN_SPECTRAL); o += kWaves) {
             const int K = STAGE == 3 ? a.kcap : a.rs[Q.rep_base + o].kprimes;
             if (K <= 0 || K > a.kcap) continue;
-            const int64_t mod_off = Q.mod_off + (int64_t)o * Q.nb;  // repetitions' residues follow each other
+            const int64_t mod_off = Q.mod_off + (int64_t)o * Q.nbm;  // repetitions' residues follow each other
             for (int i = 0; i < K; ++i) {
                 const PrimeDev &P = a.primes[i];
                 const RingM R{P.p, P.pinv_neg};
-                uint32_t v = lane < Q.nb ? a.modp[(size_t)i * a.mod_plane + mod_off + lane] : 0u;
+                uint32_t v = 0u;
+                for (int b = lane; b < Q.nbm; b += 64) v = R.add(v, a.modp[(size_t)i * a.mod_plane + mod_off + b]);
                 for (int off = 32; off > 0; off >>= 1) v = R.add(v, __shfl_down(v, off, 64));
                 if (lane == 0) s_res[o * kMaxPrimes + i] = v;
             }
@@ -1283,6 +1273,22 @@ int nblocks_for(uint32_t m)
     return (int)nb;
 }
 
+// Length of the linear convolutions of an m that is no power of two.
+int conv_log2(const Handle &h) { return ceil_log2(2 * h.m - 1); }
+
+// Whether a general plan's last two operations are a correlation and its product with
+// another register, summed: the sum then comes from the frequencies (Parseval), without the
+// inverse transform.  Where the convolution takes one pass the transforms are too short for
+// that to matter.
+bool parseval_end(const Handle &h)
+{
+    const size_t n = h.g.ops.size();
+    if (h.pow2 || n < 2 || conv_log2(h) <= 12) return false;
+    const Op &c = h.g.ops[n - 2], &p = h.g.ops[n - 1];
+    return c.code == OP_CORR && p.code == OP_HAD && p.dst != p.src && (c.dst == p.dst || c.dst == p.src) &&
+           c.dst != c.src;
+}
+
 // Workspace growth by at least half the current size, so that batches of varying size
 // (the serving loop's) reallocate a logarithmic number of times.
 size_t grown(size_t have, size_t need) { return std::max(need, have + have / 2); }
@@ -1371,7 +1377,11 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         Q.spec_off = spec_off;
         Q.dot_off = dot_off;
         Q.mod_off = mod_off;
-        mod_off += (int64_t)d * nb;
+        // products of transforms that nothing else reads are summed as their rows are transformed
+        Q.nbm = Q.plan == CS_PLAN_SPECTRAL && !shared   ? product_blocks(L, Q.S)
+                : Q.plan == CS_PLAN_GENERAL && parseval_end(h) ? product_blocks(conv_log2(h), split_of(conv_log2(h)))
+                                                               : nb;
+        mod_off += (int64_t)d * Q.nbm;
         if (Q.plan == CS_PLAN_SPECTRAL) spec_off += (int64_t)d * nb * (2 + r);
         if (Q.plan == CS_PLAN_DOT) {
             dot_off += (int64_t)d * nb;
@@ -1463,14 +1473,37 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const std::vector<int64_t> dot_pre = prefix_of(dot_idx.size(), [&](size_t i) { return q_blocks_of(dot_idx[i]); });
     const size_t o_ndpre = c.take(nd_pre.size() * sizeof(int64_t));
     const size_t o_dotpre = c.take(dot_pre.size() * sizeof(int64_t));
-    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr;
-    std::vector<std::vector<int64_t>> g_pre;
+    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_gitem, o_gipre;
+    std::vector<std::vector<int64_t>> g_pre, g_ipre;
+    std::vector<std::vector<ProductItem>> g_items;
+    // workgroups of a spectral query's product: powers of two, within its partials (a shared
+    // call's are those of k_spec_mod)
+    auto product_parts = [&](int32_t q) { return std::min(product_blocks(qd[q].log2m, qd[q].S), qd[q].nbm); };
+    auto product_item = [&](int32_t q) {
+        ProductItem I{};
+        I.r = qd[q].r;
+        I.nb = product_parts(q);
+        I.stride = qd[q].nbm;
+        I.conj = qd[q].conj;
+        I.out = qd[q].mod_off;
+        return I;
+    };
+    auto q_products_of = [&](int32_t q) { return (int64_t)qd[q].d * product_parts(q); };
     size_t z_total = 0;
     for (auto &kv : groups) {
         Group &G = kv.second;
         o_gidx.push_back(c.take(G.queries.size() * sizeof(int32_t)));
         g_pre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_blocks_of(G.queries[i]); }));
         o_gpre.push_back(c.take(g_pre.back().size() * sizeof(int64_t)));
+        g_items.emplace_back();
+        for (size_t i = 0; i < G.queries.size() && !shared; ++i) {
+            const int32_t q = G.queries[i];
+            g_items.back().push_back(product_item(q));
+            for (int k = 0; k < qd[q].r; ++k) g_items.back().back().vec[k] = qd[q].mod0[k];
+        }
+        g_ipre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_products_of(G.queries[i]); }));
+        o_gitem.push_back(c.take(g_items.back().size() * sizeof(ProductItem)));
+        o_gipre.push_back(c.take(g_ipre.back().size() * sizeof(int64_t)));
         o_gre.push_back(c.take(G.re.size() * sizeof(void *)));
         o_gim.push_back(c.take(G.im.size() * sizeof(void *)));
         o_gptr.push_back(c.take(G.mod_ptrs.size() * sizeof(void *)));
@@ -1504,9 +1537,11 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const size_t h_outs = hc.take((size_t)nq * sizeof(OutDev));
     size_t n_sk = 0;  // every query's sketches, shared ones counted each time
     for (const QDesc &Q : qd) n_sk += Q.plan == CS_PLAN_DOT ? 0 : (size_t)Q.r * Q.d;
-    const size_t h_mod = hc.take(align_up(n_sk * sizeof(void *)) + align_up((size_t)n_rep * sizeof(int32_t)) +
-                                 (size_t)(n_rep + 1 + (int)groups.size()) * sizeof(int64_t) +
-                                 3 * 256 * (groups.size() + 1));
+    size_t n_items = 0;  // products of the modular step: the spectral queries' and one per general one
+    for (const QDesc &Q : qd) n_items += Q.plan != CS_PLAN_DOT;
+    const size_t h_mod = hc.take(align_up(n_sk * sizeof(void *)) + align_up(n_items * sizeof(ProductItem)) +
+                                 (n_items + 1 + groups.size()) * sizeof(int64_t) +
+                                 3 * 256 * (groups.size() + general_q.size() + 1) + general_q.size() * 768);
     // an asynchronous estimate may still be uploading from the staging area
     if (ws.upload_pending) {
         CSK_HIP(hipEventSynchronize(ws.ev_upload));
@@ -1546,6 +1581,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             Group &G = kv.second;
             put(o_gidx[gi], G.queries);
             put(o_gpre[gi], g_pre[gi]);
+            put(o_gitem[gi], g_items[gi]);
+            put(o_gipre[gi], g_ipre[gi]);
             put(o_gre[gi], G.re);
             put(o_gim[gi], G.im);
             put(o_gptr[gi], G.mod_ptrs);
@@ -1573,6 +1610,19 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     uint32_t *d_modp = reinterpret_cast<uint32_t *>(wb + o_modp);
     RepDev *d_rs = reinterpret_cast<RepDev *>(wb + o_rs);
     OutDev *d_outs = reinterpret_cast<OutDev *>(wb + o_outs);
+
+    // transforms of a group's sketches and the sums of their products, on stream `on`
+    auto products = [&](const int64_t *const *table, uint32_t *N, int vpp, int K, const char *items, const char *pre,
+                        const std::vector<int64_t> &host_pre, int log2m, int S, const ModTables &roots,
+                        hipStream_t on) -> cs_status {
+        if (log2m > 12) {
+            const cs_status e = ntt_columns(ModSrc::from_table(table), vpp, K, N, log2m, S, primes, roots, on);
+            if (e != CS_OK) return e;
+        }
+        return ntt_products(table, N, vpp, K, reinterpret_cast<const ProductItem *>(items),
+                            reinterpret_cast<const int64_t *>(pre), (int)host_pre.size() - 1, host_pre.back(), log2m, S,
+                            primes, roots, d_modp, mod_plane, false, on);
+    };
 
     // ---- speculative modular step: when no query has a general plan and the workspace
     // is modest, the residues of the first ks primes are computed for every repetition
@@ -1631,14 +1681,21 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 const int vpp = (int)G.mod_ptrs.size();
                 uint32_t *N = reinterpret_cast<uint32_t *>(mod_cur);
                 mod_cur += align_up((size_t)ks * vpp * ((size_t)1 << G.log2m) * sizeof(uint32_t));
-                st = ntt_forward(ModSrc::from_table(reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi])), vpp, ks, N, G.log2m,
-                                 G.S, primes, groots[gi], ms);
-                if (st != CS_OK) return st;
-                hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N,
-                                   vpp, d_q, reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
-                                   reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.queries.size(),
-                                   primes, mod_plane, d_modp);
-                CSK_HIP(hipGetLastError());
+                const auto *table = reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi]);
+                const ModSrc src = ModSrc::from_table(table);
+                if (shared) {
+                    st = ntt_forward(src, vpp, ks, N, G.log2m, G.S, primes, groots[gi], ms);
+                    if (st != CS_OK) return st;
+                    hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N, vpp,
+                                       d_q, reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
+                                       reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.queries.size(),
+                                       primes, mod_plane, d_modp);
+                    CSK_HIP(hipGetLastError());
+                } else {
+                    st = products(table, N, vpp, ks, wb + o_gitem[gi], wb + o_gipre[gi], g_ipre[gi], G.log2m, G.S,
+                                  groots[gi], ms);
+                    if (st != CS_OK) return st;
+                }
                 ++gi;
             }
             if (overlap) CSK_HIP(hipEventRecord(ws.ev_join, ws.side));
@@ -1731,18 +1788,18 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         size_t mod_need = 0;
         for (auto &kv : groups) {
             const Group &G = kv.second;
-            int K = 0, vpp = 0, nidx = 0;
+            int K = 0, vpp = 0, nidx = 0;  // nidx: queries
             for (int q : G.queries) {
                 int kq = 0;
                 for (int t = 0; t < qd[q].d; ++t) kq = std::max(kq, hr[qd[q].rep_base + t].kprimes);
                 if (kq > kdone) {
                     K = std::max(K, kq);
                     vpp += qd[q].r * qd[q].d;
-                    nidx += qd[q].d;
+                    ++nidx;
                 }
             }
             if (K == 0) continue;
-            const size_t tabs = align_up((size_t)vpp * sizeof(void *)) + align_up((size_t)nidx * sizeof(int32_t)) +
+            const size_t tabs = align_up((size_t)vpp * sizeof(void *)) + align_up((size_t)nidx * sizeof(ProductItem)) +
                                 align_up((size_t)(nidx + 1) * sizeof(int64_t));
             mod_need += tabs + align_up((size_t)K * vpp * ((size_t)1 << G.log2m) * sizeof(uint32_t));
         }
@@ -1752,8 +1809,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             if (K <= kdone) continue;
             mod_need += align_up((size_t)hs[q]->g.n_regs * K * qd[q].d * hs[q]->m * sizeof(uint32_t));
             if (!hs[q]->pow2)
-                mod_need += 2 * align_up((size_t)K * qd[q].d * ((size_t)1 << ceil_log2(2 * hs[q]->m - 1)) *
-                                         sizeof(uint32_t));
+                mod_need += (parseval_end(*hs[q]) ? 3 : 2) *
+                                align_up((size_t)K * qd[q].d * ((size_t)1 << conv_log2(*hs[q])) * sizeof(uint32_t)) +
+                            align_up(sizeof(ProductItem)) + align_up(2 * sizeof(int64_t));
         }
         if (ws.mod_bytes < mod_need) {
             const size_t want = grown(ws.mod_bytes, mod_need);
@@ -1766,24 +1824,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         }
         char *mod_cur = static_cast<char *>(ws.mod);
         char *mod_host = hb + h_mod;
-        // spectral groups: every repetition of a query that needs one is recomputed; their
-        // mod0 then name vectors of their group's buffer, set for all groups and uploaded once
-        bool moved = false;
-        for (auto &kv : groups) {
-            int32_t vec = 0;
-            for (int32_t q : kv.second.queries) {
-                int kq = 0;
-                for (int t = 0; t < qd[q].d; ++t) kq = std::max(kq, hr[qd[q].rep_base + t].kprimes);
-                if (kq <= kdone) continue;
-                for (int k = 0; k < qd[q].r; ++k, vec += qd[q].d) qd[q].mod0[k] = vec;
-                moved = true;
-            }
-        }
-        if (moved) {
-            // the staging area's first upload has ended (the results came behind it)
-            std::memcpy(img.data() + o_q, qd.data(), qd.size() * sizeof(QDesc));
-            CSK_HIP(hipMemcpyAsync(d_q, img.data() + o_q, qd.size() * sizeof(QDesc), hipMemcpyHostToDevice, s));
-        }
+        // spectral groups: every repetition of a query that needs one is recomputed
         for (auto &kv : groups) {
             Group &G = kv.second;
             int K = 0;
@@ -1800,31 +1841,32 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             const ModTables roots = mod_tables(device, G.log2m, s, &st);
             if (!roots.full) return st;
             std::vector<const int64_t *> ptrs;
-            for (int32_t q : needq)
-                for (int k = 0; k < qd[q].r; ++k)
+            std::vector<ProductItem> items;
+            for (int32_t q : needq) {
+                items.push_back(product_item(q));
+                for (int k = 0; k < qd[q].r; ++k) {
+                    items.back().vec[k] = (int32_t)ptrs.size();
                     for (int t = 0; t < qd[q].d; ++t) ptrs.push_back(rel_counters(*hs[q], k) + (size_t)t * hs[q]->m);
+                }
+            }
             const int vpp = (int)ptrs.size();
             const size_t m = (size_t)1 << G.log2m;
-            const std::vector<int64_t> mpre = prefix_of(needq.size(), [&](size_t i) { return q_blocks_of(needq[i]); });
-            const size_t o_idx = align_up(ptrs.size() * sizeof(void *));
-            const size_t o_mpre = o_idx + align_up(needq.size() * sizeof(int32_t));
+            const std::vector<int64_t> mpre =
+                prefix_of(needq.size(), [&](size_t i) { return q_products_of(needq[i]); });
+            const size_t o_items = align_up(ptrs.size() * sizeof(void *));
+            const size_t o_mpre = o_items + align_up(items.size() * sizeof(ProductItem));
             const size_t tab_bytes = o_mpre + align_up(mpre.size() * sizeof(int64_t));
             char *mbc = mod_cur;
             mod_cur += tab_bytes + align_up((size_t)K * vpp * m * sizeof(uint32_t));
             char *mimg = mod_host;  // pinned; stays untouched until the call returns
             mod_host += tab_bytes;
             std::memcpy(mimg, ptrs.data(), ptrs.size() * sizeof(void *));
-            std::memcpy(mimg + o_idx, needq.data(), needq.size() * sizeof(int32_t));
+            std::memcpy(mimg + o_items, items.data(), items.size() * sizeof(ProductItem));
             std::memcpy(mimg + o_mpre, mpre.data(), mpre.size() * sizeof(int64_t));
             CSK_HIP(hipMemcpyAsync(mbc, mimg, tab_bytes, hipMemcpyHostToDevice, s));
-            uint32_t *N = reinterpret_cast<uint32_t *>(mbc + tab_bytes);
-            st = ntt_forward(ModSrc::from_table(reinterpret_cast<const int64_t *const *>(mbc)), vpp, K, N, G.log2m, G.S, primes, roots, s);
+            st = products(reinterpret_cast<const int64_t *const *>(mbc), reinterpret_cast<uint32_t *>(mbc + tab_bytes), vpp,
+                          K, mbc + o_items, mbc + o_mpre, mpre, G.log2m, G.S, roots, s);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)mpre.back(), K), dim3(kThreads), 0, s, N, vpp, d_q,
-                               reinterpret_cast<const int32_t *>(mbc + o_idx),
-                               reinterpret_cast<const int64_t *>(mbc + o_mpre), (int)needq.size(), primes,
-                               mod_plane, d_modp);
-            CSK_HIP(hipGetLastError());
         }
         // general plans: Alg. 3's register program per query
         for (int q : general_q) {
@@ -1836,7 +1878,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             const uint32_t m = h.m;
             // transform length: m itself, or (m not a power of two) the power of two
             // LM >= 2m - 1 of a zero-padded linear convolution
-            const int L = h.pow2 ? h.log2m : ceil_log2(2 * m - 1);
+            const int L = h.pow2 ? h.log2m : conv_log2(h);
             const uint32_t Mlen = 1u << L;
             const int S = split_of(L);
             const ModTables roots = mod_tables(device, L, s, &st);
@@ -1845,11 +1887,15 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             uint32_t *M = reinterpret_cast<uint32_t *>(mod_cur);
             mod_cur += align_up((size_t)h.g.n_regs * reg_elems * sizeof(uint32_t));
             uint32_t *padA = nullptr, *padB = nullptr;
+            const bool parseval = parseval_end(h);
+            char *item_dev = nullptr;
             if (!h.pow2) {
                 padA = reinterpret_cast<uint32_t *>(mod_cur);
                 mod_cur += align_up((size_t)K * d * Mlen * sizeof(uint32_t));
                 padB = reinterpret_cast<uint32_t *>(mod_cur);
-                mod_cur += align_up((size_t)K * d * Mlen * sizeof(uint32_t));
+                mod_cur += align_up((size_t)K * d * Mlen * sizeof(uint32_t)) * (parseval ? 2 : 1);
+                item_dev = mod_cur;
+                mod_cur += align_up(sizeof(ProductItem)) + align_up(2 * sizeof(int64_t));
             }
             const int gx = (int)std::min<size_t>(64, ((size_t)m + 255) / 256);
             // Registers stay where their value is until an operation needs them elsewhere: a
@@ -1876,19 +1922,21 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                     if (val[x].lin && (st = materialize(x)) != CS_OK) return st;
                 return CS_OK;
             };
+            auto padded = [&](int x, bool reverse) {
+                return val[x].sketch ? ModSrc::padded_sketch(val[x].sketch, m, reverse)
+                                     : ModSrc::padded_reg(val[x].reg, m, reverse);
+            };
             auto forward = [&](int x, bool reverse, uint32_t *out) {  // its transform, zero-padded for m no power of two
                 if (h.pow2) {
                     ModSrc src;  // in place: x is in its register
                     return ntt_forward(src, d, K, out, L, S, primes, roots, s);
                 }
-                return ntt_forward(val[x].sketch ? ModSrc::padded_sketch(val[x].sketch, m, reverse)
-                                                 : ModSrc::padded_reg(val[x].reg, m, reverse),
-                                   d, K, out, L, S, primes, roots, s);
+                return ntt_forward(padded(x, reverse), d, K, out, L, S, primes, roots, s);
             };
             const size_t n_ops = h.g.ops.size();
             ModVal sum_a, sum_b;
             int two = 0;
-            for (size_t oi = 0; oi < n_ops; ++oi) {
+            for (size_t oi = 0; oi + (parseval ? 1 : 0) < n_ops; ++oi) {
                 const Op &op = h.g.ops[oi];
                 switch (op.code) {
                     case OP_LOAD:
@@ -1919,6 +1967,34 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                         } else {
                             // src star dst = reverse(src) circularly convolved with dst
                             if ((st = spare_pads()) != CS_OK) return st;
+                            if (parseval && oi + 2 == n_ops) {
+                                // its product with the last register, summed: the linear
+                                // convolution times that register repeated twice
+                                const Op &last = h.g.ops[oi + 1];
+                                ModSrc rest = padded(last.dst == op.dst ? last.src : last.dst, false);
+                                rest.periodic = 1;
+                                const size_t pad = (size_t)K * d * Mlen;
+                                if ((st = ntt_columns(padded(op.src, true), d, K, padA, L, S, primes, roots, s)) != CS_OK ||
+                                    (st = ntt_columns(padded(op.dst, false), d, K, padA + pad, L, S, primes, roots, s)) != CS_OK ||
+                                    (st = ntt_columns(rest, d, K, padA + 2 * pad, L, S, primes, roots, s)) != CS_OK)
+                                    return st;
+                                ProductItem I{};
+                                I.r = 3;
+                                I.nb = I.stride = qd[q].nbm;
+                                I.out = qd[q].mod_off;
+                                for (int k = 0; k < 3; ++k) I.vec[k] = k * K * d;
+                                const int64_t pre[2] = {0, (int64_t)d * I.nb};
+                                std::memcpy(mod_host, &I, sizeof(I));
+                                std::memcpy(mod_host + align_up(sizeof(I)), pre, sizeof(pre));
+                                const size_t bytes = align_up(sizeof(I)) + align_up(sizeof(pre));
+                                CSK_HIP(hipMemcpyAsync(item_dev, mod_host, bytes, hipMemcpyHostToDevice, s));
+                                mod_host += bytes;
+                                if ((st = ntt_products(nullptr, padA, d, K, reinterpret_cast<const ProductItem *>(item_dev),
+                                                       reinterpret_cast<const int64_t *>(item_dev + align_up(sizeof(I))),
+                                                       1, pre[1], L, S, primes, roots, d_modp, mod_plane, true, s)) != CS_OK)
+                                    return st;
+                                break;
+                            }
                             if ((st = forward(op.src, true, padA)) != CS_OK) return st;
                             if ((st = forward(op.dst, false, padB)) != CS_OK) return st;
                             if ((st = ntt_inverse(ModSrc::times(padA), d, K, padB, L, S, primes, roots, s)) != CS_OK)
@@ -1934,6 +2010,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 }
                 CSK_HIP(hipGetLastError());
             }
+            if (parseval) continue;
             if (!two) sum_a = val[h.g.result_reg];
             hipLaunchKernelGGL(k_mod_sum, dim3(qd[q].nb, K * d), dim3(kThreads), 0, s, sum_a, sum_b, two, m, d, primes,
                                qd[q].nb, qd[q].mod_off, mod_plane, d_modp);

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "csk_internal.h"
@@ -105,6 +106,9 @@ struct ModSrc {
     const uint32_t *reg = nullptr;  // kPadReg, kMul
     uint32_t m = 0;
     int32_t reverse = 0;
+    // kPadSketch, kPadReg: element i is the value (2^log2m - i) mod 2^log2m of the vector
+    // repeated twice, zero beyond (its transform at f is the repetition's at -f)
+    int32_t periodic = 0;
     static ModSrc from_table(const int64_t *const *t)
     {
         ModSrc s;
@@ -140,6 +144,42 @@ struct ModSrc {
 };
 cs_status ntt_forward(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
                       const PrimeDev *primes, const ModTables &roots, hipStream_t s);
+// The column pass alone (lengths above 4096): ntt_products takes the rows.
+cs_status ntt_columns(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s);
+
+// d products of r factors, each summed over its frequencies: factor k of product t is vector
+// vec[k] + t, at -f where conj has bit k.  Partial sums of product t go to out + t stride of
+// each prime's plane: nb of them, the rest of the stride is set to zero.
+struct ProductItem {
+    int32_t r, nb, stride;
+    uint32_t conj;
+    int64_t out;
+    int32_t vec[kMaxRel];
+};
+// Partial sums of one product: a workgroup's rows, up to four per lane of the wavefront that
+// adds them (64 workgroups a product left a second round of them nearly empty).
+inline int product_blocks(int log2m, int S) { return log2m <= 12 ? 1 : std::min(256, 1 << (log2m - S)); }
+// Lengths up to 4096 are transformed from the sketches in `table`, longer ones from their
+// column pass in buf [primes][vec_per_prime][2^log2m].  prefix: workgroups before each item
+// (d nb of them an item), `blocks` in all.  scale: partial sums times 2^-log2m.
+cs_status ntt_products(const int64_t *const *table, const uint32_t *buf, int vec_per_prime, int n_primes,
+                       const ProductItem *items, const int64_t *prefix, int n_items, int64_t blocks, int log2m, int S,
+                       const PrimeDev *primes, const ModTables &roots, uint32_t *partials, int64_t plane, bool scale,
+                       hipStream_t s);
+
+// Flattened launches: block b belongs to item i with prefix[i] <= b < prefix[i + 1].
+__device__ __forceinline__ int find_item(const int64_t *__restrict__ prefix, int n, int64_t b)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (prefix[mid] <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 cs_status ntt_inverse(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
                       const PrimeDev *primes, const ModTables &roots, hipStream_t s);
 

@@ -57,9 +57,9 @@ constexpr int brev_bits(int x, int bits)
     return r;
 }
 
-// One round of the tile's transforms (see above).  src(n, c) supplies the first round's
-// inputs, dst(f, c, k, value) takes the last one's outputs (k counts a DFT's, whose
-// frequencies f are an arithmetic progression); s is the tile in LDS, root(e) the power
+// One round of the tile's transforms (see above).  src(n, c, e) supplies the first round's
+// inputs (e counts the thread's), dst(f, c, k, it, value) takes the last one's outputs (k counts a DFT's, whose
+// frequencies f are an arithmetic progression, it the thread's DFTs); s is the tile in LDS, root(e) the power
 // w_L^e, Dft the ring's register DFTs.
 template <int LG, int LC, int EB, int ROUND, class Dft, class T, class Root, class Src, class Dst>
 __device__ __forceinline__ void pass_round(T *s, const Dft &D, Root &&root, Src &&src, Dst &&dst)
@@ -90,14 +90,14 @@ __device__ __forceinline__ void pass_round(T *s, const Dft &D, Root &&root, Src 
         T x[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            if constexpr (first) x[k] = src(i + (k << LN), c);
+            if constexpr (first) x[k] = src(i + (k << LN), c, (g0 / NT) * N + k);
             else x[k] = s[lp(at + (k << (LN + LC)))];
         }
         D.template dft<RB, !last>(x);
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             const T v = x[brev_bits(k, RB)];  // frequency digit k
-            if constexpr (last) dst(h + (k << done), c, k, v);
+            if constexpr (last) dst(h + (k << done), c, k, g0 / NT, v);
             else s[lp(at + (k << (LN + LC)))] = k == 0 ? D.settle(v) : D.mul(v, root((i * k) << (LG - LJ)));
         }
     }
@@ -180,12 +180,12 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_fft_f64(F64Src src
     double2 *vec = buf + (size_t)v * m;
     const int64_t *re = src.re ? src.re[v] : nullptr;
     const int64_t *im = src.re ? src.im[v] : nullptr;
-    auto load = [&](int n, int c) {
+    auto load = [&](int n, int c, int) {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
         return re ? make_double2((double)re[pos], im ? (double)im[pos] : 0.0) : vec[pos];
     };
     DftC D{stage, log2S};
-    auto store = [&](int f, int c, int k, double2 val) {
+    auto store = [&](int f, int c, int k, int it, double2 val) {
         // w_m^(f column), from the table in tile order: looked up in the table of powers, a
         // tile's 2^11 twiddles lie in as many cache lines
         if (g.twiddle) val = D.R.mul(val, columns[((size_t)blk << (LG + LC)) + ((size_t)f << LC) + c]);
@@ -278,10 +278,16 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
     uint32_t *vec = buf + (size_t)v * m;
     const int64_t *in = src.mode == ModSrc::kTable ? src.table[j] : src.sketch + (size_t)j * src.m;
     const uint32_t *reg = src.reg + (size_t)v * (src.mode == ModSrc::kMul ? m : (int64_t)src.m);
-    auto load = [&](int n, int c) -> uint32_t {
+    auto load = [&](int n, int c, int) -> uint32_t {
         const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
         if constexpr (MODE == ModSrc::kInPlace) return vec[pos];
         if constexpr (MODE == ModSrc::kTable) return mont_from_i64(R, in[pos], P.r2, P.r3, P.neg2_64);
+        if (src.periodic) {
+            const int64_t q = (m - pos) & (m - 1);
+            if (q >= 2 * (int64_t)src.m - 1) return 0u;
+            const int64_t at = q < src.m ? q : q - src.m;
+            return src.mode == ModSrc::kPadReg ? reg[at] : mont_from_i64(R, in[at], P.r2, P.r3, P.neg2_64);
+        }
         const bool pad = src.mode == ModSrc::kPadSketch || src.mode == ModSrc::kPadReg;
         if (pad && pos >= src.m) return 0u;
         const int64_t at = pad && src.reverse && pos > 0 ? src.m - pos : pos;
@@ -298,7 +304,7 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
     // residues as one lookup per element.
     const int sh = log2T - g.log2m;
     uint32_t t_cur = 0, t_step = 0;
-    auto store = [&](int f, int c, int k, uint32_t val) {
+    auto store = [&](int f, int c, int k, int it, uint32_t val) {
         if (g.twiddle) {
             if (k == 0) {
                 constexpr int step = 1 << (LG - round_bits(LG, EB, NR - 1));
@@ -318,6 +324,97 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
         __syncthreads();
     }
     pass_rounds<LG, LC, EB>(s, D, [&](int e) { return stw[e]; }, load, store);
+}
+
+// The last pass of the factors' transforms and the sum over the frequencies of their product
+// (ProductItem): a workgroup transforms its rows of one factor after another and multiplies
+// in registers, so the spectra are never written.  Factor k conjugated is its spectrum at
+// -f: row r of it comes from row N1 - r read backwards, whose output N2 - 1 - f2 a factor
+// w_N2^n on input n moves to f2 (row 0: from itself, without it).  MODE kTable: lengths of
+// one pass, straight from the sketches.  Bound by memory (4 bytes read per element) and the
+// vector unit.
+template <int LG, int EB, int MODE>
+__global__ __launch_bounds__(pass_threads(LG, 0, EB)) void k_ntt_product(
+    const int64_t *const *__restrict__ table, const uint32_t *__restrict__ buf, int log2m, int vec_per_prime,
+    const ProductItem *__restrict__ items, const int64_t *__restrict__ prefix, int n_items,
+    const PrimeDev *__restrict__ primes, const uint32_t *__restrict__ stage, int log2S, uint32_t *partials,
+    int64_t plane, int scale)
+{
+    constexpr int L = 1 << LG, NT = pass_threads(LG, 0, EB), NR = n_rounds(LG, EB);
+    constexpr int N = 1 << round_bits(LG, EB, NR - 1);  // outputs of a DFT of the last round
+    __shared__ uint32_t s[NR > 1 ? lds_len<L>() : 1];
+    __shared__ uint32_t stw[L];  // w_L^e
+    __shared__ uint32_t s_sum[NT / 64];
+    const int pi = blockIdx.y;
+    const int item = find_item(prefix, n_items, blockIdx.x);
+    const ProductItem &I = items[item];
+    const int within = (int)(blockIdx.x - prefix[item]), t = within / I.nb, blk = within - t * I.nb;
+    const PrimeDev &P = primes[pi];
+    const RingM R{P.p, P.pinv_neg};
+    DftM D{R, stage + ((size_t)(2 * pi) << log2S), log2S};
+    for (int e = threadIdx.x; e < L; e += NT) stw[e] = D.stage[(size_t)e << (log2S - LG)];
+    __syncthreads();
+    auto root = [&](int e) { return stw[e]; };
+    const int rows = 1 << (log2m - LG), per = rows / I.nb;
+    // this thread's first-round inputs of factor k of a row; the next factor's are on their
+    // way while one is transformed
+    using In = std::conditional_t<MODE == ModSrc::kTable, int64_t, uint32_t>;
+    auto fetch = [&](int row, int k, In (&x)[1 << EB]) {
+        constexpr int RB0 = round_bits(LG, EB, 0), LN = LG - RB0;
+        const int back = (int)((I.conj >> k) & 1u), flip = -back;
+        const int64_t v = I.vec[k] + t;
+        const In *in;
+        if constexpr (MODE == ModSrc::kTable) in = table[v];
+        else in = buf + (((size_t)pi * vec_per_prime + v) << log2m) + ((size_t)(back && row ? rows - row : row) << LG);
+#pragma unroll
+        for (int g0 = 0; g0 < (1 << LN); g0 += NT) {
+            const int h = g0 + (int)threadIdx.x;
+            if ((1 << LN) < NT && h >= (1 << LN)) break;
+#pragma unroll
+            for (int e = 0; e < (1 << RB0); ++e)
+                x[(g0 / NT) * (1 << RB0) + e] = in[(((h + (e << LN)) ^ flip) + back) & (L - 1)];
+        }
+    };
+    uint32_t acc = 0;
+    In cur[1 << EB];
+    fetch(blk * per, 0, cur);
+    for (int row = blk * per; row < (blk + 1) * per; ++row) {
+        uint32_t prod[1 << EB];
+#pragma unroll
+        for (int e = 0; e < (1 << EB); ++e) prod[e] = 0u;  // a lane without outputs adds nothing
+        for (int k = 0; k < I.r; ++k) {
+            In next[1 << EB];
+            const bool last = k + 1 == I.r && row + 1 == (blk + 1) * per;  // fetches itself again
+            fetch(k + 1 == I.r && !last ? row + 1 : row, last ? k : k + 1 == I.r ? 0 : k + 1, next);
+            if (k || row > blk * per) __syncthreads();  // the tile's readers are done
+            const bool twist = MODE != ModSrc::kTable && row && ((I.conj >> k) & 1u);
+            auto value = [&](int e) -> uint32_t {
+                if constexpr (MODE == ModSrc::kTable) return mont_from_i64(R, cur[e], P.r2, P.r3, P.neg2_64);
+                else return cur[e];
+            };
+            auto store = [&](int, int, int kk, int it, uint32_t val) {
+                uint32_t &x = prod[it * N + kk];
+                x = k ? R.mul(x, val) : val;
+            };
+            if (twist) pass_rounds<LG, 0, EB>(s, D, root, [&](int n, int, int e) { return R.mul(value(e), stw[n]); }, store);
+            else pass_rounds<LG, 0, EB>(s, D, root, [&](int, int, int e) { return value(e); }, store);
+#pragma unroll
+            for (int e = 0; e < (1 << EB); ++e) cur[e] = next[e];
+        }
+#pragma unroll
+        for (int e = 0; e < (1 << EB); ++e) acc = R.add(acc, prod[e]);
+    }
+    for (int o = 32; o > 0; o >>= 1) acc = R.add(acc, __shfl_down(acc, o, 64));
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < NT / 64; ++w) acc = R.add(acc, s_sum[w]);
+        if (scale) acc = R.mul(acc, P.minv[log2m]);
+        uint32_t *o = partials + (size_t)pi * plane + I.out + (int64_t)t * I.stride;
+        o[blk] = acc;
+        if (blk == 0)
+            for (int b = I.nb; b < I.stride; ++b) o[b] = 0u;
+    }
 }
 
 // Two-pass lengths: tiles of N2 = 2^S elements, columns of N1 = 2^(log2m - S) <= N2.
@@ -519,6 +616,33 @@ cs_status ntt_forward(const ModSrc &src, int vec_per_prime, int n_primes, uint32
     CSK_HIP(ntt_pass(with_columns(column_pass(log2m, S, true), ntt_log2c(log2m - S)), src, n_vec, buf, vec_per_prime,
                      primes, roots, 0, s));
     CSK_HIP(ntt_pass(row_pass(log2m, S, false), ModSrc{}, n_vec, buf, vec_per_prime, primes, roots, 0, s));
+    return CS_OK;
+}
+
+cs_status ntt_columns(const ModSrc &src, int vec_per_prime, int n_primes, uint32_t *buf, int log2m, int S,
+                      const PrimeDev *primes, const ModTables &roots, hipStream_t s)
+{
+    CSK_HIP(ntt_pass(with_columns(column_pass(log2m, S, true), ntt_log2c(log2m - S)), src, vec_per_prime * n_primes, buf,
+                     vec_per_prime, primes, roots, 0, s));
+    return CS_OK;
+}
+
+cs_status ntt_products(const int64_t *const *table, const uint32_t *buf, int vec_per_prime, int n_primes,
+                       const ProductItem *items, const int64_t *prefix, int n_items, int64_t blocks, int log2m, int S,
+                       const PrimeDev *primes, const ModTables &roots, uint32_t *partials, int64_t plane, bool scale,
+                       hipStream_t s)
+{
+    const bool single = log2m <= 12;
+    CSK_HIP(with_length(single ? single_pass(log2m) : row_pass(log2m, S, false), [&](auto lg, auto row, auto sgl) {
+        constexpr int LG = decltype(lg)::value;
+        constexpr bool kSingle = decltype(sgl)::value;
+        if constexpr (decltype(row)::value) {
+            constexpr int EB = ntt_elems(LG, 0, kSingle), MODE = kSingle ? ModSrc::kTable : ModSrc::kInPlace;
+            hipLaunchKernelGGL((k_ntt_product<LG, EB, MODE>), dim3((unsigned)blocks, n_primes),
+                               dim3(pass_threads(LG, 0, EB)), 0, s, table, buf, log2m, vec_per_prime, items, prefix,
+                               n_items, primes, roots.stage, roots.log2S, partials, plane, scale ? 1 : 0);
+        }
+    }));
     return CS_OK;
 }
 
