@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -70,12 +71,7 @@ __device__ __forceinline__ double warp_sum(double v)
     return v;
 }
 
-// Butterfly reductions: every lane ends with the same value (fixed order).
-__device__ __forceinline__ double wave_allsum(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
+// Butterfly reduction: every lane ends with the same value.
 __device__ __forceinline__ double wave_allmax(double v)
 {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
@@ -94,19 +90,6 @@ __device__ double block_sum(double v, double *sh)
     if (threadIdx.x == 0)
         for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += sh[i];
     return r;  // valid in thread 0
-}
-
-__device__ double block_max(double v, double *sh)
-{
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_down(v, o, 64));
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    __syncthreads();
-    if (l == 0) sh[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r = fmax(r, sh[i]);
-    return r;
 }
 
 // Correctly rounded conversion of a signed 128-bit integer to double.
@@ -223,6 +206,8 @@ struct QDesc {
     int32_t plan, r, d, log2m, rep_base;
     int32_t nb;              // blocks of a repetition's reductions
     int32_t nbm;             // modular partials of a repetition
+    int32_t nbn;             // norm partials of a sketch
+    int32_t adds;            // SPECTRAL: most additions on a term's path to a norm or sum
     int32_t S;               // row length 2^S of the two-pass transforms of this length
     uint32_t m;              // buckets (log2m is exact only for powers of two)
     uint32_t conj;           // SPECTRAL: relations taken conjugated
@@ -317,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
                                                        const int64_t *__restrict__ prefix, int n_items,
                                                        double *partials)
 {
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[2 + kMaxRel][kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
     const QDesc &D = qs[idx[item]];
     const int within = (int)(blockIdx.x - prefix[item]), t = within / D.nb, blk = within - t * D.nb;
@@ -357,14 +342,26 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
         acc += pr;
         acc_abs += fabs(pr) + fabs(pi);
     }
-    double *o = partials + (D.spec_off + (int64_t)within * (2 + r));
-    const double s0 = block_sum(acc, sh);
-    if (threadIdx.x == 0) o[0] = s0;
-    const double s1 = block_sum(acc_abs, sh);
-    if (threadIdx.x == 0) o[1] = s1;
-    for (int k = 0; k < r; ++k) {
-        const double mk = block_max(mx[k], sh);
-        if (threadIdx.x == 0) o[2 + k] = mk;
+    // every value's wavefront results first, one barrier, then a thread per value
+    acc = warp_sum(acc);
+    acc_abs = warp_sum(acc_abs);
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][wv] = acc;
+        sh[1][wv] = acc_abs;
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxRel; ++k)
+        if (k < r) {
+            const double mk = wave_allmax(mx[k]);
+            if ((threadIdx.x & 63) == 0) sh[2 + k][wv] = mk;
+        }
+    __syncthreads();
+    if ((int)threadIdx.x < 2 + r) {
+        const double *v = sh[threadIdx.x];
+        double x = v[0];
+        for (int w = 1; w < kThreads / 64; ++w) x = threadIdx.x < 2 ? x + v[w] : fmax(x, v[w]);
+        partials[D.spec_off + (int64_t)within * (2 + r) + threadIdx.x] = x;
     }
 }
 
@@ -542,6 +539,7 @@ constexpr int kSpecPrimes = 5;                       // speculative modular step
 // the results of up to kDirectReps repetitions are written to it by the finalize.
 constexpr size_t kDirectTables = (size_t)1 << 15;
 constexpr int kDirectReps = 512;
+constexpr int kBriefProduct = 3 << 11;  // largest r m of a one-pass product
 constexpr size_t kSpecBudget = (size_t)1 << 30;      // and its largest workspace
 constexpr int kOverlapPrimes = 3;                    // at most this many: beside the fp64 chain
 constexpr size_t kOverlapMinResidues = (size_t)1 << 24;  // and at least this many residues
@@ -569,48 +567,81 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
     const int wv = t >> 6, lane = t & 63;
     constexpr int kWaves = NT / 64;
     if (STAGE != 2 && plan != CS_PLAN_DOT) {
-        // The nb <= 64 block partials of each owner (a sketch for the norms, a repetition
-        // for the spectral sums) are reduced by one wavefront: lane b loads partial b and
-        // a shuffle tree of depth 6 adds them, in a fixed order.
-        const int nb = Q.nb;
+        // The block partials of each owner (a sketch for the norms, a repetition for the
+        // spectral sums) are reduced by one wavefront, several owners' loads at a time: lane b
+        // adds partials b, b + 64, ... and a shuffle tree of depth 6 the lanes, in a fixed
+        // order.  One partial each (lengths of one pass) needs no sum.
+        const int nbn = Q.nbn, nbs = Q.nb;
         const int n_sk = Q.r * Q.d;
-        for (int o = wv; o < n_sk; o += kWaves) {
-            double q2 = 0.0, l1 = 0.0;
-            if (lane < nb) {
+        if (nbn == 1) {
+            for (int o = t; o < n_sk; o += NT) {
                 const int k = o / Q.d;
-                const double *p = a.norms + (Q.norm_off[k] + (int64_t)(o - k * Q.d) * nb + lane) * 2;
-                q2 = p[0];
-                l1 = p[1];
+                const double *p = a.norms + (Q.norm_off[k] + (o - k * Q.d)) * 2;
+                s_q2[o] = p[0];
+                s_l1[o] = p[1];
             }
-            q2 = warp_sum(q2);
-            l1 = warp_sum(l1);
-            if (lane == 0) {
-                s_q2[o] = q2;
-                s_l1[o] = l1;
-            }
+        } else {
+            auto norms = [&](auto owners) {
+                constexpr int U = decltype(owners)::value;
+                for (int o0 = wv; o0 < n_sk; o0 += U * kWaves) {
+                    double q2[U], l1[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int o = min(o0 + u * kWaves, n_sk - 1), k = o / Q.d;
+                        const double *p = a.norms + (Q.norm_off[k] + (int64_t)(o - k * Q.d) * nbn) * 2;
+                        q2[u] = l1[u] = 0.0;
+                        for (int b = lane; b < nbn; b += 64) {
+                            q2[u] += p[2 * b];
+                            l1[u] += p[2 * b + 1];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        q2[u] = warp_sum(q2[u]);
+                        l1[u] = warp_sum(l1[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (lane == 0 && o0 + u * kWaves < n_sk) {
+                            s_q2[o0 + u * kWaves] = q2[u];
+                            s_l1[o0 + u * kWaves] = l1[u];
+                        }
+                }
+            };
+            if (n_sk <= kWaves) norms(std::integral_constant<int, 1>{});
+            else norms(std::integral_constant<int, 4>{});
         }
         if (plan == CS_PLAN_SPECTRAL && (Q.d & 1)) {
             for (int k = wv; k < Q.r; k += kWaves) {
                 const int64_t po = Q.pair_off[k];
-                const double q2 = warp_sum(po >= 0 && lane < nb ? a.norms[(po + lane) * 2] : 0.0);
+                double q2 = 0.0;
+                for (int b = lane; b < nbn && po >= 0; b += 64) q2 += a.norms[(po + b) * 2];
+                q2 = warp_sum(q2);
                 if (lane == 0) s_p2[k] = q2;
             }
         }
         if (plan == CS_PLAN_SPECTRAL) {
             const int w = 2 + Q.r;
             const double *spc = a.spec + Q.spec_off;
-            for (int o = wv; o < Q.d; o += kWaves) {
-                const double *p = spc + ((int64_t)o * nb + lane) * w;
-                double sm = lane < nb ? p[0] : 0.0, sa = lane < nb ? p[1] : 0.0;
-                sm = warp_sum(sm);
-                sa = warp_sum(sa);
-                if (lane == 0) {
-                    s_sum[o] = sm;
-                    s_sabs[o] = sa;
+            if (nbs == 1) {
+                for (int e = t; e < Q.d * w; e += NT) {
+                    const int o = e / w, i = e - o * w;
+                    (i == 0 ? s_sum[o] : i == 1 ? s_sabs[o] : s_mx[o * kMaxRel + i - 2]) = spc[e];
                 }
-                for (int k = 0; k < Q.r; ++k) {
-                    const double mk = wave_allmax(lane < nb ? p[2 + k] : 0.0);
-                    if (lane == 0) s_mx[o * kMaxRel + k] = mk;
+            } else {
+                for (int o = wv; o < Q.d; o += kWaves) {
+                    const double *p = spc + ((int64_t)o * nbs + lane) * w;
+                    double sm = lane < nbs ? p[0] : 0.0, sa = lane < nbs ? p[1] : 0.0;
+                    sm = warp_sum(sm);
+                    sa = warp_sum(sa);
+                    if (lane == 0) {
+                        s_sum[o] = sm;
+                        s_sabs[o] = sa;
+                    }
+                    for (int k = 0; k < Q.r; ++k) {
+                        const double mk = wave_allmax(lane < nbs ? p[2 + k] : 0.0);
+                        if (lane == 0) s_mx[o * kMaxRel + k] = mk;
+                    }
                 }
             }
         }
@@ -640,9 +671,10 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
         if constexpr (STAGE == 2) rp = a.rs[Q.rep_base + t];
         // additions on any term's path to a sum: its thread's serial sum (per_thread - 1),
         // block_sum (6 shuffle levels, then the kThreads / 64 wavefront sums one after
-        // another) and the tree of depth 6 over the nb <= 64 block partials above
+        // another) and the tree of depth 6 over the nb <= 64 block partials above; for the
+        // transforms' own norms and sums the host counts them
         const double per_thread = ceil(m / ((double)Q.nb * kThreads));
-        const double n_eff = per_thread + 6.0 + kThreads / 64 + 6.0;
+        const double n_eff = plan == CS_PLAN_SPECTRAL ? (double)Q.adds : per_thread + 6.0 + kThreads / 64 + 6.0;
         if constexpr (STAGE != 2) {
             rp.kprimes = 0;
             rp.status = 0;
@@ -1334,8 +1366,10 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         int log2m, S;
         std::vector<int32_t> queries;
         std::vector<const int64_t *> re, im;
+        std::vector<int64_t> re_norm, im_norm;  // their sketches' norm partials
         std::vector<const int64_t *> mod_ptrs;  // every sketch once
         size_t z_off = 0;
+        bool fused = false;  // its modular products are summed by k_ntt_product
     };
     // The d sketches of one relation, normed and transformed once however many queries of
     // the call read them (with `shared`: the sub-queries of one base query do, 30 relation
@@ -1376,13 +1410,13 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         Q.nb = nb;
         Q.spec_off = spec_off;
         Q.dot_off = dot_off;
-        Q.mod_off = mod_off;
-        // products of transforms that nothing else reads are summed as their rows are transformed
-        Q.nbm = Q.plan == CS_PLAN_SPECTRAL && !shared   ? product_blocks(L, Q.S)
-                : Q.plan == CS_PLAN_GENERAL && parseval_end(h) ? product_blocks(conv_log2(h), split_of(conv_log2(h)))
-                                                               : nb;
-        mod_off += (int64_t)d * Q.nbm;
-        if (Q.plan == CS_PLAN_SPECTRAL) spec_off += (int64_t)d * nb * (2 + r);
+        Q.nbn = nb;
+        if (Q.plan == CS_PLAN_SPECTRAL) {
+            Q.nbn = fft_norm_blocks(L, Q.S);
+            Q.adds = std::max((int)((h.m + nb * kThreads - 1) / (nb * kThreads)) + 6 + kThreads / 64 + 6,
+                              fft_norm_adds(L, Q.S));
+            spec_off += (int64_t)d * nb * (2 + r);
+        }
         if (Q.plan == CS_PLAN_DOT) {
             dot_off += (int64_t)d * nb;
             dot_idx.push_back(q);
@@ -1414,28 +1448,34 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 B.group = G;
                 B.pair_off = -1;
                 B.norm_off = norm_off;
-                nd.push_back(NormDesc{base, norm_off, h.m, d, nb, 0});
-                norm_off += (int64_t)d * nb;
+                if (!G) nd.push_back(NormDesc{base, norm_off, h.m, d, nb, 0});
+                norm_off += (int64_t)d * Q.nbn;
                 if (G) {
+                    auto norm_of = [&](int t) { return B.norm_off + (int64_t)t * Q.nbn; };
                     B.mod0 = (int32_t)G->mod_ptrs.size();
                     B.vec0 = (int32_t)G->re.size();
                     for (int t = 0; t < d; ++t) G->mod_ptrs.push_back(base + (size_t)t * m);
                     for (int t = 0; t + 1 < d; t += 2) {
                         G->re.push_back(base + (size_t)t * m);
                         G->im.push_back(base + (size_t)(t + 1) * m);
+                        G->re_norm.push_back(norm_of(t));
+                        G->im_norm.push_back(norm_of(t + 1));
                     }
                     if (d & 1) {
                         if (open < 0) {
                             B.last = 2 * (int32_t)G->re.size();
                             G->re.push_back(base + (size_t)(d - 1) * m);
                             G->im.push_back(nullptr);
+                            G->re_norm.push_back(norm_of(d - 1));
+                            G->im_norm.push_back(0);
                             open = b;
                         } else {
                             RelBlock &O = blocks[open];
                             B.last = O.last + 1;
                             G->im[O.last >> 1] = base + (size_t)(d - 1) * m;
-                            B.pair_off = O.norm_off + (int64_t)(d - 1) * nb;
-                            O.pair_off = B.norm_off + (int64_t)(d - 1) * nb;
+                            G->im_norm[O.last >> 1] = norm_of(d - 1);
+                            B.pair_off = O.norm_off + (int64_t)(d - 1) * Q.nbn;
+                            O.pair_off = norm_of(d - 1);
                             open = -1;
                         }
                     }
@@ -1452,6 +1492,27 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             Q.mod0[k] = B.mod0;
         }
         if (Q.plan == CS_PLAN_GENERAL) general_q.push_back(q);
+    }
+    // Products of a group's modular spectra that nothing else reads are summed as their rows
+    // are transformed (k_ntt_product): always for lengths of two passes (estimates 3% faster
+    // at 2^13, d = 5, 8% at 2^18, d = 15, r = 5), and for one pass up to kBriefProduct, where
+    // the launch saved counts as much as its chain of r transforms in one workgroup (r = 3,
+    // 2^11: 72.6 us apart, 72.3 together; r = 5, 2^11: 87.9 and 91.9; r = 5, 2^12: 91 and 100).
+    for (auto &kv : groups) {
+        Group &G = kv.second;
+        G.fused = !shared;
+        for (int32_t q : G.queries)
+            if (G.log2m <= 12 && (qd[q].r << G.log2m) > kBriefProduct) G.fused = false;
+    }
+    for (int q = 0; q < nq; ++q) {
+        QDesc &Q = qd[q];
+        const Handle &h = *hs[q];
+        Q.nbm = Q.nb;
+        if (Q.plan == CS_PLAN_SPECTRAL && groups[Q.log2m].fused) Q.nbm = product_blocks(Q.log2m, Q.S);
+        if (Q.plan == CS_PLAN_GENERAL && parseval_end(h))
+            Q.nbm = product_blocks(conv_log2(h), split_of(conv_log2(h)));
+        Q.mod_off = mod_off;
+        mod_off += (int64_t)Q.d * Q.nbm;
     }
     const int64_t mod_plane = mod_off;
     if (async_out && !general_q.empty())
@@ -1473,7 +1534,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const std::vector<int64_t> dot_pre = prefix_of(dot_idx.size(), [&](size_t i) { return q_blocks_of(dot_idx[i]); });
     const size_t o_ndpre = c.take(nd_pre.size() * sizeof(int64_t));
     const size_t o_dotpre = c.take(dot_pre.size() * sizeof(int64_t));
-    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_gitem, o_gipre;
+    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_gitem, o_gipre, o_gren, o_gimn;
     std::vector<std::vector<int64_t>> g_pre, g_ipre;
     std::vector<std::vector<ProductItem>> g_items;
     // workgroups of a spectral query's product: powers of two, within its partials (a shared
@@ -1496,12 +1557,14 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
         g_pre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_blocks_of(G.queries[i]); }));
         o_gpre.push_back(c.take(g_pre.back().size() * sizeof(int64_t)));
         g_items.emplace_back();
-        for (size_t i = 0; i < G.queries.size() && !shared; ++i) {
+        for (size_t i = 0; i < G.queries.size() && G.fused; ++i) {
             const int32_t q = G.queries[i];
             g_items.back().push_back(product_item(q));
             for (int k = 0; k < qd[q].r; ++k) g_items.back().back().vec[k] = qd[q].mod0[k];
         }
         g_ipre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_products_of(G.queries[i]); }));
+        o_gren.push_back(c.take(G.re_norm.size() * sizeof(int64_t)));
+        o_gimn.push_back(c.take(G.im_norm.size() * sizeof(int64_t)));
         o_gitem.push_back(c.take(g_items.back().size() * sizeof(ProductItem)));
         o_gipre.push_back(c.take(g_ipre.back().size() * sizeof(int64_t)));
         o_gre.push_back(c.take(G.re.size() * sizeof(void *)));
@@ -1581,6 +1644,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             Group &G = kv.second;
             put(o_gidx[gi], G.queries);
             put(o_gpre[gi], g_pre[gi]);
+            put(o_gren[gi], G.re_norm);
+            put(o_gimn[gi], G.im_norm);
             put(o_gitem[gi], g_items[gi]);
             put(o_gipre[gi], g_ipre[gi]);
             put(o_gre[gi], G.re);
@@ -1683,7 +1748,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                 mod_cur += align_up((size_t)ks * vpp * ((size_t)1 << G.log2m) * sizeof(uint32_t));
                 const auto *table = reinterpret_cast<const int64_t *const *>(wb + o_gptr[gi]);
                 const ModSrc src = ModSrc::from_table(table);
-                if (shared) {
+                if (!G.fused) {
                     st = ntt_forward(src, vpp, ks, N, G.log2m, G.S, primes, groots[gi], ms);
                     if (st != CS_OK) return st;
                     hipLaunchKernelGGL(k_spec_mod, dim3((unsigned)g_pre[gi].back(), ks), dim3(kThreads), 0, ms, N, vpp,
@@ -1721,9 +1786,11 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             const TwiddleTables tw = twiddle_tables(device, G.log2m, G.S, s, &st);
             if (!tw.full) return st;
             double2 *Z = reinterpret_cast<double2 *>(wb + o_Z + G.z_off);
-            st = fft_f64_forward(reinterpret_cast<const int64_t *const *>(wb + o_gre[gi]),
-                                 reinterpret_cast<const int64_t *const *>(wb + o_gim[gi]), (int)G.re.size(), Z,
-                                 G.log2m, G.S, tw, s);
+            const SketchVectors sv{reinterpret_cast<const int64_t *const *>(wb + o_gre[gi]),
+                                   reinterpret_cast<const int64_t *const *>(wb + o_gim[gi]),
+                                   reinterpret_cast<const int64_t *>(wb + o_gren[gi]),
+                                   reinterpret_cast<const int64_t *>(wb + o_gimn[gi]), d_norms};
+            st = fft_f64_forward(sv, (int)G.re.size(), Z, G.log2m, G.S, tw, s);
             if (st != CS_OK) return st;
             hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_pre[gi].back()), dim3(kThreads), 0, s, Z, d_q,
                                reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
@@ -2129,6 +2196,10 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
     void **ptrs = nullptr;
     unsigned int *flag = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    double *norms = nullptr;
+    size_t norm_blocks = 1;
+    for (int S = 10; S <= 12; ++S)
+        if (split_ok(log2m, S)) norm_blocks = std::max(norm_blocks, (size_t)fft_norm_blocks(log2m, S));
     auto cleanup = [&]() {
         (void)hipStreamSynchronize(s);
         if (src) (void)hipFree(src);
@@ -2136,6 +2207,7 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         if (N) (void)hipFree(N);
         if (Nref) (void)hipFree(Nref);
         if (ptrs) (void)hipFree(ptrs);
+        if (norms) (void)hipFree(norms);
         if (flag) (void)hipFree(flag);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
@@ -2143,7 +2215,8 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
     // packed pairs: vector v's real part is vector 2v of src, its imaginary part 2v + 1
     if (hipMalloc(&src, 2 * elems * sizeof(int64_t)) != hipSuccess || hipMalloc(&Z, elems * sizeof(double2)) != hipSuccess ||
         hipMalloc(&N, elems * sizeof(uint32_t)) != hipSuccess || hipMalloc(&Nref, elems * sizeof(uint32_t)) != hipSuccess ||
-        hipMalloc(&ptrs, 3 * (size_t)n_vec * sizeof(void *)) != hipSuccess ||
+        hipMalloc(&ptrs, 5 * (size_t)n_vec * sizeof(void *)) != hipSuccess ||
+        hipMalloc(&norms, 4 * (size_t)n_vec * norm_blocks * sizeof(double)) != hipSuccess ||
         hipMalloc(&flag, sizeof(unsigned int)) != hipSuccess) {
         cleanup();
         return fail(CS_ENOMEM, "transform tuning buffers");
@@ -2152,11 +2225,14 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         cleanup();
         return fail(CS_EDEVICE, "transform tuning events");
     }
-    std::vector<const int64_t *> tab(3 * (size_t)n_vec);
+    std::vector<const int64_t *> tab(5 * (size_t)n_vec);
     for (int v = 0; v < n_vec; ++v) {
         tab[v] = src + (size_t)(2 * v) * m;               // fp64: real parts
         tab[n_vec + v] = src + (size_t)(2 * v + 1) * m;   // fp64: imaginary parts
         tab[2 * n_vec + v] = src + (size_t)v * m;         // NTT: one sketch per vector
+        // norm partials of either part: indices, in the pointer-sized words of the same table
+        tab[3 * n_vec + v] = reinterpret_cast<const int64_t *>((uintptr_t)(2 * v) * norm_blocks);
+        tab[4 * n_vec + v] = reinterpret_cast<const int64_t *>((uintptr_t)(2 * v + 1) * norm_blocks);
     }
     hipLaunchKernelGGL(k_tune_fill, dim3(4096), dim3(256), 0, s, src, 2 * elems);
     if (hipMemcpyAsync(ptrs, tab.data(), tab.size() * sizeof(void *), hipMemcpyHostToDevice, s) != hipSuccess ||
@@ -2167,6 +2243,8 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
     const int64_t *const *re = reinterpret_cast<const int64_t *const *>(ptrs);
     const int64_t *const *im = re + n_vec;
     const int64_t *const *nt = re + 2 * n_vec;
+    const SketchVectors sv{re, im, reinterpret_cast<const int64_t *>(re + 3 * n_vec),
+                           reinterpret_cast<const int64_t *>(re + 4 * n_vec), norms};
     const int S0 = default_split_bits(log2m);
     std::memset(out, 0, sizeof(*out));
     out->best = -1;
@@ -2205,7 +2283,7 @@ extern "C" cs_status cs_tune_transform(int32_t log2m, int32_t n_vec, void *strea
         bool ok = true;
         for (int r = 0; r < 3 && ok; ++r)
             ok = hipEventRecord(e0, s) == hipSuccess &&
-                 fft_f64_forward(re, im, n_vec, Z, log2m, S, tw, s) == CS_OK &&
+                 fft_f64_forward(sv, n_vec, Z, log2m, S, tw, s) == CS_OK &&
                  ntt_forward(ModSrc::from_table(nt), n_vec, 1, N, log2m, S, primes, roots, s) == CS_OK &&
                  hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
                  hipEventElapsedTime(&t[r], e0, e1) == hipSuccess;

@@ -85,10 +85,22 @@ ModTables mod_tables(int device, int log2m, hipStream_t s, cs_status *st);
 // outputs in tile order, blocks one after another.
 cs_status column_twiddles(double2 *out, const double2 *tw, int log2m, int S, hipStream_t s);
 
-// Forward fp64 FFTs of n_vec complex vectors re[v] + i im[v] (device pointer tables of
-// int64 sketches; im[v] may be null) into buf [n_vec][m].
-cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
-                          int S, const TwiddleTables &tw, hipStream_t s);
+// Complex vectors re[v] + i im[v] (device pointer tables of int64 sketches; im[v] may be
+// null).  Their first pass leaves the sketches' norm partials (sum of squares, sum of
+// absolute values), fft_norm_blocks() pairs a sketch from pair re_norm[v] and im_norm[v] of
+// `norms` on.
+struct SketchVectors {
+    const int64_t *const *re, *const *im;
+    const int64_t *re_norm, *im_norm;
+    double *norms;
+};
+int fft_norm_blocks(int log2m, int S);
+// Most additions on a term's path to a norm, a wavefront's sum of the partials included.
+int fft_norm_adds(int log2m, int S);
+
+// Their forward fp64 FFTs into buf [n_vec][m].
+cs_status fft_f64_forward(const SketchVectors &v, int n_vec, double2 *buf, int log2m, int S, const TwiddleTables &tw,
+                          hipStream_t s);
 
 // Where the first pass of a modular transform takes element `pos` of vector v = (prime, j)
 // from: the sketch's int64 value or a residue, converted, padded or multiplied on the way

@@ -60,7 +60,7 @@ constexpr int brev_bits(int x, int bits)
 // One round of the tile's transforms (see above).  src(n, c, e) supplies the first round's
 // inputs (e counts the thread's), dst(f, c, k, it, value) takes the last one's outputs (k counts a DFT's, whose
 // frequencies f are an arithmetic progression, it the thread's DFTs); s is the tile in LDS, root(e) the power
-// w_L^e, Dft the ring's register DFTs.
+// w_L^e, Dft the ring's register DFTs and the thread's index.
 template <int LG, int LC, int EB, int ROUND, class Dft, class T, class Root, class Src, class Dst>
 __device__ __forceinline__ void pass_round(T *s, const Dft &D, Root &&root, Src &&src, Dst &&dst)
 {
@@ -72,7 +72,7 @@ __device__ __forceinline__ void pass_round(T *s, const Dft &D, Root &&root, Src 
     constexpr int groups = 1 << (LG + LC - RB);
 #pragma unroll
     for (int g0 = 0; g0 < groups; g0 += NT) {
-        const int g = g0 + threadIdx.x;
+        const int g = g0 + D.tid;
         if (groups < NT && g >= groups) break;
         const int c = g & ((1 << LC) - 1), h = g >> LC;
         // middle rounds: h = block * 2^LN + index; last round: h counts the blocks by their
@@ -120,7 +120,43 @@ __device__ __forceinline__ void pass_rounds(T *s, Dft &D, Root &&root, Src &&src
 struct F64Src {
     const int64_t *const *re;  // [n_vec] sketch loaded as the real part (null: in place)
     const int64_t *const *im;  // [n_vec] sketch loaded as the imaginary part (entry null: 0)
+    // first pass: where the norm partials (sum of squares, of absolute values) of either
+    // sketch go, one pair per block of the pass
+    const int64_t *re_norm, *im_norm;
+    double *norms;
 };
+
+// v[0..N) summed over the wavefront (lane 0 holds them).
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N])
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] += __shfl_down(v[i], o, 64);
+}
+
+// Sums of squares and absolute values of the real and the imaginary parts.
+template <int E>
+__device__ __forceinline__ void add_norms(const double2 (&x)[E], double (&n)[4])
+{
+    double q[E][4];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        q[e][0] = x[e].x * x[e].x;
+        q[e][1] = fabs(x[e].x);
+        q[e][2] = x[e].y * x[e].y;
+        q[e][3] = fabs(x[e].y);
+    }
+#pragma unroll
+    for (int h = E / 2; h > 0; h >>= 1)  // a tree: log2 E additions deep
+#pragma unroll
+        for (int e = 0; e < h; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[e][i] += q[e + h][i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n[i] = q[0][i];
+}
 
 // Register DFTs of complex doubles, decimation in frequency: x[k] in, frequency
 // brev_bits(k) in x[k] out.  Along any path of a round of RB stages there are at most RB
@@ -129,6 +165,7 @@ struct F64Src {
 struct DftC {
     const double2 *stage;  // w_(2^log2S) powers
     int log2S;
+    int tid;
     double2 w[8];
     RingC R;
     template <int RB>
@@ -165,9 +202,10 @@ struct DftC {
 // One pass: a block transforms 2^LC interleaved columns of length 2^LG.  Bound by memory
 // (16 bytes read and written per element: the row pass at 5 TB/s, the column pass, whose
 // sources are runs of 128 bytes, at 3.6; 38 vectors of 2^18 take 64 and 88 us, 106 each
-// with two stages per trip through LDS).  The stage roots are read through the cache: in LDS
+// with two stages per trip through LDS).  FIRST: from the sketches, whose norms are summed on
+// the way (a pass of their own over the int64 counters took 81 us of that estimate).  The stage roots are read through the cache: in LDS
 // they would take as much of it as the tile and halve the blocks per CU.
-template <int LG, int LC, int EB>
+template <int LG, int LC, int EB, bool FIRST>
 __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_fft_f64(F64Src src, double2 *buf, PassGeom g,
                                                                   const double2 *__restrict__ columns,
                                                                   const double2 *__restrict__ stage, int log2S)
@@ -178,13 +216,45 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_fft_f64(F64Src src
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     double2 *vec = buf + (size_t)v * m;
-    const int64_t *re = src.re ? src.re[v] : nullptr;
-    const int64_t *im = src.re ? src.im[v] : nullptr;
-    auto load = [&](int n, int c, int) {
-        const int64_t pos = base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride;
-        return re ? make_double2((double)re[pos], im ? (double)im[pos] : 0.0) : vec[pos];
+    constexpr int E = 1 << EB;
+    double2 x[FIRST ? E : 1];
+    if constexpr (FIRST) {
+        // this thread's inputs, and their norms
+        constexpr int RB = round_bits(LG, EB, 0), NT = pass_threads(LG, LC, EB), groups = 1 << (LG + LC - RB);
+        const int64_t *re = src.re[v], *im = src.im[v];
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int g0 = 0; g0 < groups; g0 += NT) {
+            const int h = g0 + (int)threadIdx.x;
+            if (groups < NT && h >= groups) break;
+            const int64_t at = base + (int64_t)(h & ((1 << LC) - 1)) * g.col_stride + (int64_t)(h >> LC) * g.elem_stride;
+#pragma unroll
+            for (int k = 0; k < (1 << RB); ++k) {
+                const int64_t pos = at + ((int64_t)k << (LG - RB)) * g.elem_stride;
+                x[(g0 / NT) * (1 << RB) + k] = make_double2((double)re[pos], im ? (double)im[pos] : 0.0);
+            }
+        }
+        double nr[4];
+        add_norms<E>(x, nr);
+        wave_sums(nr);
+        __shared__ double s_nr[NT / 64][4];
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s_nr[threadIdx.x >> 6][i] = nr[i];
+        }
+        __syncthreads();
+        if (threadIdx.x < 4 && (threadIdx.x < 2 || im)) {
+            double a = 0.0;
+            for (int w = 0; w < NT / 64; ++w) a += s_nr[w][threadIdx.x];
+            src.norms[((threadIdx.x < 2 ? src.re_norm : src.im_norm)[v] + blk) * 2 + (threadIdx.x & 1)] = a;
+        }
+    }
+    auto load = [&](int n, int c, int e) {
+        if constexpr (FIRST) return x[e];
+        else return vec[base + (int64_t)c * g.col_stride + (int64_t)n * g.elem_stride];
     };
-    DftC D{stage, log2S};
+    DftC D{stage, log2S, (int)threadIdx.x};
     auto store = [&](int f, int c, int k, int it, double2 val) {
         // w_m^(f column), from the table in tile order: looked up in the table of powers, a
         // tile's 2^11 twiddles lie in as many cache lines
@@ -203,6 +273,7 @@ struct DftM {
     RingM R;
     const uint32_t *stage;  // w_(2^log2S) powers
     int log2S;
+    int tid;
     uint32_t w[8];
     template <int RB>
     __device__ __forceinline__ void load_roots()
@@ -272,7 +343,7 @@ __global__ __launch_bounds__(pass_threads(LG, LC, EB)) void k_ntt(ModSrc src, ui
     const PrimeDev &P = primes[pi];  // by reference: a copy with minv[] indexed would live in scratch
     const RingM R{P.p, P.pinv_neg};
     const uint32_t *tw = roots + ((size_t)(2 * pi + inverse) << log2T);
-    DftM D{R, stage + ((size_t)(2 * pi + inverse) << log2S), log2S};
+    DftM D{R, stage + ((size_t)(2 * pi + inverse) << log2S), log2S, (int)threadIdx.x};
     const int64_t m = (int64_t)1 << g.log2m;
     const int64_t base = (int64_t)blk * g.block_stride;
     uint32_t *vec = buf + (size_t)v * m;
@@ -351,7 +422,7 @@ __global__ __launch_bounds__(pass_threads(LG, 0, EB)) void k_ntt_product(
     const int within = (int)(blockIdx.x - prefix[item]), t = within / I.nb, blk = within - t * I.nb;
     const PrimeDev &P = primes[pi];
     const RingM R{P.p, P.pinv_neg};
-    DftM D{R, stage + ((size_t)(2 * pi) << log2S), log2S};
+    DftM D{R, stage + ((size_t)(2 * pi) << log2S), log2S, (int)threadIdx.x};
     for (int e = threadIdx.x; e < L; e += NT) stw[e] = D.stage[(size_t)e << (log2S - LG)];
     __syncthreads();
     auto root = [&](int e) { return stw[e]; };
@@ -388,6 +459,11 @@ __global__ __launch_bounds__(pass_threads(LG, 0, EB)) void k_ntt_product(
             fetch(k + 1 == I.r && !last ? row + 1 : row, last ? k : k + 1 == I.r ? 0 : k + 1, next);
             if (k || row > blk * per) __syncthreads();  // the tile's readers are done
             const bool twist = MODE != ModSrc::kTable && row && ((I.conj >> k) & 1u);
+            {
+                int id = threadIdx.x;  // opaque: addresses are not kept in registers between factors
+                asm volatile("" : "+v"(id));
+                D.tid = id;
+            }
             auto value = [&](int e) -> uint32_t {
                 if constexpr (MODE == ModSrc::kTable) return mont_from_i64(R, cur[e], P.r2, P.r3, P.neg2_64);
                 else return cur[e];
@@ -549,8 +625,13 @@ hipError_t fft_pass(const PassGeom &g, const F64Src &src, int n_vec, double2 *bu
     return with_length(g, [&](auto lg, auto row, auto single) {
         constexpr int LG = decltype(lg)::value, LC = decltype(row)::value ? 0 : fft_log2c(LG);
         constexpr int EB = fft_elems(LG, LC, decltype(single)::value);
-        hipLaunchKernelGGL((k_fft_f64<LG, LC, EB>), dim3(n_vec, g.blocks), dim3(pass_threads(LG, LC, EB)), 0, s, src, buf, g,
-                           tw.columns, tw.stage, tw.log2S);
+        auto go = [&](auto first) {
+            hipLaunchKernelGGL((k_fft_f64<LG, LC, EB, decltype(first)::value>), dim3(n_vec, g.blocks),
+                               dim3(pass_threads(LG, LC, EB)), 0, s, src, buf, g, tw.columns, tw.stage, tw.log2S);
+        };
+        // the first pass is the column one, or the only one
+        if constexpr (LC > 0 || decltype(single)::value) go(std::true_type{});
+        else go(std::false_type{});
     });
 }
 
@@ -589,18 +670,29 @@ cs_status column_twiddles(double2 *out, const double2 *tw, int log2m, int S, hip
     return CS_OK;
 }
 
-cs_status fft_f64_forward(const int64_t *const *re, const int64_t *const *im, int n_vec, double2 *buf, int log2m,
-                          int S, const TwiddleTables &tw, hipStream_t s)
+int fft_norm_blocks(int log2m, int S) { return log2m <= 12 ? 1 : (1 << S) >> fft_log2c(log2m - S); }
+
+int fft_norm_adds(int log2m, int S)
+{
+    if (log2m <= 12) {  // k_fft_f64 or k_fft_product
+        const int EB = fft_elems(log2m, 0, true);
+        return EB + 6 + pass_threads(log2m, 0, EB) / 64;
+    }
+    const int lg = log2m - S, lc = fft_log2c(lg), EB = fft_elems(lg, lc, false);
+    return EB + 6 + pass_threads(lg, lc, EB) / 64 + (fft_norm_blocks(log2m, S) + 63) / 64 + 6;
+}
+
+cs_status fft_f64_forward(const SketchVectors &v, int n_vec, double2 *buf, int log2m, int S, const TwiddleTables &tw,
+                          hipStream_t s)
 {
     if (n_vec == 0) return CS_OK;
-    F64Src first{re, im};
-    F64Src self{nullptr, nullptr};
+    const F64Src first{v.re, v.im, v.re_norm, v.im_norm, v.norms};
     if (log2m <= 12) {
         CSK_HIP(fft_pass(single_pass(log2m), first, n_vec, buf, tw, s));
         return CS_OK;
     }
     CSK_HIP(fft_pass(with_columns(column_pass(log2m, S, true), fft_log2c(log2m - S)), first, n_vec, buf, tw, s));
-    CSK_HIP(fft_pass(row_pass(log2m, S, false), self, n_vec, buf, tw, s));
+    CSK_HIP(fft_pass(row_pass(log2m, S, false), F64Src{}, n_vec, buf, tw, s));
     return CS_OK;
 }
 
