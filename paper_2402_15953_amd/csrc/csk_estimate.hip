@@ -58,7 +58,7 @@ struct OutDev {
 
 struct CrtTables {
     uint32_t p[kMaxPrimes];
-    uint32_t inv[kMaxPrimes][kMaxPrimes];     // inv[j][i] = p_j^-1 mod p_i
+    uint32_t inv[kMaxPrimes][kMaxPrimes];     // inv[j][i]: Montgomery form of p_j^-1 mod p_i
     uint32_t half[kMaxPrimes][kMaxPrimes];    // half[K-1]: digits of (P_K - 1) / 2
     double log2p[kMaxPrimes];
 };
@@ -124,34 +124,27 @@ __device__ __int128 double_to_i128(double x)
     return neg ? -(__int128)u : (__int128)u;
 }
 
-__device__ uint32_t mod_u128(unsigned __int128 u, uint32_t p)
+// x mod p: 32-bit limbs times their powers of 2^32 (Montgomery products; a 64-bit remainder
+// costs the vector unit a hundred instructions).
+__device__ uint32_t mod_i128(__int128 x, const PrimeDev &P, const RingM &R)
 {
-    uint64_t r = 0;
-    for (int i = 3; i >= 0; --i) {
-        const uint32_t limb = (uint32_t)(u >> (32 * i));
-        r = ((r << 32) | limb) % p;
-    }
-    return (uint32_t)r;
+    const bool neg = x < 0;
+    const unsigned __int128 u = neg ? (unsigned __int128)0 - (unsigned __int128)x : (unsigned __int128)x;
+    uint32_t r = R.mul((uint32_t)u, P.one);
+    r = R.add(r, R.mul((uint32_t)(u >> 32), P.r2));
+    r = R.add(r, R.mul((uint32_t)(u >> 64), P.r3));
+    r = R.add(r, R.mul(R.mul((uint32_t)(u >> 96), P.r3), P.r2));
+    return neg && r ? P.p - r : r;
 }
 
-__device__ uint32_t mod_i128(__int128 x, uint32_t p)
-{
-    if (x >= 0) return mod_u128((unsigned __int128)x, p);
-    const uint32_t r = mod_u128((unsigned __int128)0 - (unsigned __int128)x, p);
-    return r ? p - r : 0;
-}
-
-__device__ void garner(const uint32_t *res, int K, const CrtTables &T, uint32_t *dig)
+__device__ void garner(const uint32_t *res, int K, const CrtTables &T, const PrimeDev *__restrict__ primes, uint32_t *dig)
 {
     for (int i = 0; i < K; ++i) {
-        const uint64_t pi = T.p[i];
-        uint64_t x = res[i] % pi;
-        for (int j = 0; j < i; ++j) {
-            const uint64_t dj = dig[j] % pi;
-            x = (x + pi - dj) % pi;
-            x = (x * T.inv[j][i]) % pi;
-        }
-        dig[i] = (uint32_t)x;
+        const RingM R{primes[i].p, primes[i].pinv_neg};
+        const uint32_t one = primes[i].one;
+        uint32_t x = res[i];
+        for (int j = 0; j < i; ++j) x = R.mul(R.sub(x, R.mul(dig[j], one)), T.inv[j][i]);  // (x - d_j) / p_j
+        dig[i] = x;
     }
 }
 
@@ -222,8 +215,6 @@ struct QDesc {
     // twice the vector of its last sketch plus the half it is (odd d), and its first vector
     // of the modular pass, in its group's buffers
     int32_t vec0[kMaxRel], last[kMaxRel], mod0[kMaxRel];
-    // packed vector of relation k's repetition t times 2, plus the half it is
-    __device__ __forceinline__ int packed(int k, int t) const { return (t ^ 1) < d ? 2 * vec0[k] + t : last[k]; }
 };
 
 // ---------------------------------------------------------------- kernels
@@ -294,7 +285,10 @@ __global__ __launch_bounds__(kThreads) void k_dot(const QDesc *__restrict__ qs, 
     }
 }
 
-// fp64 spectral product-reduce for the queries idx of one m-group.
+// fp64 spectral product-reduce for the queries idx of one m-group: both repetitions of a
+// packed vector, and of each pair +-f, whose terms are conjugate, one frequency that counts
+// twice, so a value of Z is read once per query (and not four times: 15 repetitions of ten
+// sub-chains of 2^18 took 228 us).
 // partials: sum Re(term), sum |Re|+|Im| of terms, max |C_k| per relation.
 __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict__ Z,
                                                        const QDesc *__restrict__ qs,
@@ -302,66 +296,87 @@ __global__ __launch_bounds__(kThreads) void k_spec_f64(const double2 *__restrict
                                                        const int64_t *__restrict__ prefix, int n_items,
                                                        double *partials)
 {
-    __shared__ double sh[2 + kMaxRel][kThreads / 64];
+    __shared__ double sh[2][2 + kMaxRel][kThreads / 64];
     const int item = find_item(prefix, n_items, blockIdx.x);
     const QDesc &D = qs[idx[item]];
-    const int within = (int)(blockIdx.x - prefix[item]), t = within / D.nb, blk = within - t * D.nb;
-    const int log2m = D.log2m, S = D.S;
-    const uint32_t m = 1u << log2m;
+    const int within = (int)(blockIdx.x - prefix[item]), slot = within / D.nb, blk = within - slot * D.nb;
+    const int t0 = 2 * slot;
+    const bool two = t0 + 1 < D.d;  // else the last repetition, packed with another relation's
+    const int log2m = D.log2m, S = log2m > 12 ? D.S : log2m;
+    const uint32_t m = 1u << log2m, row = 1u << S, n1 = m >> S;
     const int r = D.r;
-    double acc = 0.0, acc_abs = 0.0;
-    double mx[kMaxRel];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};  // sum and absolute sum of either repetition
+    double mxa[kMaxRel], mxb[kMaxRel];
 #pragma unroll
-    for (int k = 0; k < kMaxRel; ++k) mx[k] = 0.0;
-    for (uint32_t pos = blk * kThreads + threadIdx.x; pos < m; pos += (uint32_t)D.nb * kThreads) {
-        const uint32_t f = pos_freq(pos, log2m, S);
-        const uint32_t npos = freq_pos((m - f) & (m - 1), log2m, S);
-        double pr = 1.0, pi = 0.0;
+    for (int k = 0; k < kMaxRel; ++k) mxa[k] = mxb[k] = 0.0;
+    for (uint32_t e = blk * kThreads + threadIdx.x; e <= m / 2; e += (uint32_t)D.nb * kThreads) {
+        // Place e of rows 0 .. N1 / 2 - 1 and its mirror (row N1 - r, places reversed).  Row 0
+        // is its own mirror: its second half stands for row N1 / 2, which is too.
+        uint32_t pos = e, npos;
+        if (e < row && (n1 == 1 || e <= row / 2)) {
+            npos = (row - e) & (row - 1);
+        } else if (e < row || e == m / 2) {  // places 0 .. row / 2 - 1 of row N1 / 2
+            const uint32_t c = e < row ? e - row / 2 - 1 : row / 2 - 1;
+            pos = m / 2 + c;
+            npos = m / 2 + row - 1 - c;
+        } else {
+            npos = ((n1 - (e >> S)) << S) + row - 1 - (e & (row - 1));
+        }
+        const double weight = pos == npos ? 1.0 : 2.0;
+        double2 pa = make_double2(1.0, 0.0), pb = pa;
 #pragma unroll
         for (int k = 0; k < kMaxRel; ++k) {
             if (k < r) {
-                const int sidx = D.packed(k, t);
-                const double2 *zv = Z + (size_t)(sidx >> 1) * m;
+                const int v = two ? D.vec0[k] + slot : D.last[k] >> 1;
+                const double2 *zv = Z + (size_t)v * m;
                 const double2 a = zv[pos], b = zv[npos];
-                double cr, ci;
-                if ((sidx & 1) == 0) {
-                    cr = 0.5 * (a.x + b.x);
-                    ci = 0.5 * (a.y - b.y);
-                } else {
-                    cr = 0.5 * (a.y + b.y);
-                    ci = 0.5 * (b.x - a.x);
-                }
-                if ((D.conj >> k) & 1u) ci = -ci;
-                mx[k] = fmax(mx[k], fabs(cr) + fabs(ci));
-                const double nr = pr * cr - pi * ci;
-                const double ni = pr * ci + pi * cr;
-                pr = nr;
-                pi = ni;
+                const double sg = (D.conj >> k) & 1u ? -0.5 : 0.5;
+                double2 x = make_double2(0.5 * (a.x + b.x), sg * (a.y - b.y));
+                const double2 y = make_double2(0.5 * (a.y + b.y), sg * (b.x - a.x));
+                if (!two && (D.last[k] & 1)) x = y;
+                mxa[k] = fmax(mxa[k], fabs(x.x) + fabs(x.y));
+                mxb[k] = fmax(mxb[k], fabs(y.x) + fabs(y.y));
+                pa = make_double2(pa.x * x.x - pa.y * x.y, pa.x * x.y + pa.y * x.x);
+                pb = make_double2(pb.x * y.x - pb.y * y.y, pb.x * y.y + pb.y * y.x);
             }
         }
-        acc += pr;
-        acc_abs += fabs(pr) + fabs(pi);
+        acc[0] += weight * pa.x;
+        acc[1] += weight * (fabs(pa.x) + fabs(pa.y));
+        acc[2] += weight * pb.x;
+        acc[3] += weight * (fabs(pb.x) + fabs(pb.y));
     }
     // every value's wavefront results first, one barrier, then a thread per value
-    acc = warp_sum(acc);
-    acc_abs = warp_sum(acc_abs);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += __shfl_down(acc[i], o, 64);
     const int wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        sh[0][wv] = acc;
-        sh[1][wv] = acc_abs;
+    const bool first = (threadIdx.x & 63) == 0;
+    if (first) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sh[i >> 1][i & 1][wv] = acc[i];
     }
 #pragma unroll
     for (int k = 0; k < kMaxRel; ++k)
         if (k < r) {
-            const double mk = wave_allmax(mx[k]);
-            if ((threadIdx.x & 63) == 0) sh[2 + k][wv] = mk;
+            double a = mxa[k], b = mxb[k];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                a = fmax(a, __shfl_down(a, o, 64));
+                b = fmax(b, __shfl_down(b, o, 64));
+            }
+            if (first) {
+                sh[0][2 + k][wv] = a;
+                sh[1][2 + k][wv] = b;
+            }
         }
     __syncthreads();
-    if ((int)threadIdx.x < 2 + r) {
-        const double *v = sh[threadIdx.x];
+    const int half = threadIdx.x >> 6, i = threadIdx.x & 63;  // a wavefront for either repetition
+    if (half < (two ? 2 : 1) && i < 2 + r) {
+        const double *v = sh[half][i];
         double x = v[0];
-        for (int w = 1; w < kThreads / 64; ++w) x = threadIdx.x < 2 ? x + v[w] : fmax(x, v[w]);
-        partials[D.spec_off + (int64_t)within * (2 + r) + threadIdx.x] = x;
+        for (int w = 1; w < kThreads / 64; ++w) x = i < 2 ? x + v[w] : fmax(x, v[w]);
+        partials[D.spec_off + ((int64_t)(t0 + half) * D.nb + blk) * (2 + r) + i] = x;
     }
 }
 
@@ -559,6 +574,11 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
     __shared__ double s_sum[kMaxD], s_sabs[kMaxD], s_mx[kMaxD * kMaxRel];
     __shared__ double s_stage[kStage];  // scratch of the bound computation
     __shared__ uint32_t s_res[kMaxD * kMaxPrimes], s_dig[kMaxD * kMaxPrimes];
+    // the CRT tables, read by the serial part below an entry at a time
+    __shared__ CrtTables s_crt;
+    static_assert(sizeof(CrtTables) % 4 == 0, "copied by words");
+    for (int e = threadIdx.x; e < (int)(sizeof(CrtTables) / 4); e += NT)
+        reinterpret_cast<uint32_t *>(&s_crt)[e] = reinterpret_cast<const uint32_t *>(&a.crt)[e];
     const QDesc &Q = a.qs[blockIdx.x];
     const int t = threadIdx.x;
     const double u = 0x1p-53;
@@ -580,20 +600,39 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                 s_q2[o] = p[0];
                 s_l1[o] = p[1];
             }
+            for (int k = t; k < Q.r && plan == CS_PLAN_SPECTRAL && (Q.d & 1); k += NT)
+                s_p2[k] = Q.pair_off[k] >= 0 ? a.norms[Q.pair_off[k] * 2] : 0.0;
         } else {
+            // odd d: also the norms of the last sketches' packed partners
+            const int n_own = n_sk + (plan == CS_PLAN_SPECTRAL && (Q.d & 1) ? Q.r : 0);
             auto norms = [&](auto owners) {
                 constexpr int U = decltype(owners)::value;
-                for (int o0 = wv; o0 < n_sk; o0 += U * kWaves) {
+                for (int o0 = wv; o0 < n_own; o0 += U * kWaves) {
                     double q2[U], l1[U];
+                    const double2 *p[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int o = min(o0 + u * kWaves, n_sk - 1), k = o / Q.d;
-                        const double *p = a.norms + (Q.norm_off[k] + (int64_t)(o - k * Q.d) * nbn) * 2;
+                        const int o = o0 + u * kWaves, k = o / Q.d;
+                        const int64_t at = o < n_sk    ? Q.norm_off[k] + (int64_t)(o - k * Q.d) * nbn
+                                           : o < n_own ? Q.pair_off[o - n_sk]
+                                                       : -1;
+                        p[u] = at < 0 ? nullptr : reinterpret_cast<const double2 *>(a.norms) + at;
                         q2[u] = l1[u] = 0.0;
-                        for (int b = lane; b < nbn; b += 64) {
-                            q2[u] += p[2 * b];
-                            l1[u] += p[2 * b + 1];
-                        }
+                    }
+                    for (int b0 = lane; b0 < nbn; b0 += 128) {
+                        double2 v[U][2];
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+                                v[u][j] = p[u] && b0 + 64 * j < nbn ? p[u][b0 + 64 * j] : make_double2(0.0, 0.0);
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) {
+                                q2[u] += v[u][j].x;
+                                l1[u] += v[u][j].y;
+                            }
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -601,24 +640,19 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                         l1[u] = warp_sum(l1[u]);
                     }
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (lane == 0 && o0 + u * kWaves < n_sk) {
-                            s_q2[o0 + u * kWaves] = q2[u];
-                            s_l1[o0 + u * kWaves] = l1[u];
+                    for (int u = 0; u < U; ++u) {
+                        const int o = o0 + u * kWaves;
+                        if (lane == 0 && o < n_sk) {
+                            s_q2[o] = q2[u];
+                            s_l1[o] = l1[u];
+                        } else if (lane == 0 && o < n_own) {
+                            s_p2[o - n_sk] = q2[u];
                         }
+                    }
                 }
             };
-            if (n_sk <= kWaves) norms(std::integral_constant<int, 1>{});
+            if (n_own <= kWaves) norms(std::integral_constant<int, 1>{});
             else norms(std::integral_constant<int, 4>{});
-        }
-        if (plan == CS_PLAN_SPECTRAL && (Q.d & 1)) {
-            for (int k = wv; k < Q.r; k += kWaves) {
-                const int64_t po = Q.pair_off[k];
-                double q2 = 0.0;
-                for (int b = lane; b < nbn && po >= 0; b += 64) q2 += a.norms[(po + b) * 2];
-                q2 = warp_sum(q2);
-                if (lane == 0) s_p2[k] = q2;
-            }
         }
         if (plan == CS_PLAN_SPECTRAL) {
             const int w = 2 + Q.r;
@@ -629,18 +663,26 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                     (i == 0 ? s_sum[o] : i == 1 ? s_sabs[o] : s_mx[o * kMaxRel + i - 2]) = spc[e];
                 }
             } else {
+                // a repetition's values four at a time
                 for (int o = wv; o < Q.d; o += kWaves) {
                     const double *p = spc + ((int64_t)o * nbs + lane) * w;
-                    double sm = lane < nbs ? p[0] : 0.0, sa = lane < nbs ? p[1] : 0.0;
-                    sm = warp_sum(sm);
-                    sa = warp_sum(sa);
-                    if (lane == 0) {
-                        s_sum[o] = sm;
-                        s_sabs[o] = sa;
-                    }
-                    for (int k = 0; k < Q.r; ++k) {
-                        const double mk = wave_allmax(lane < nbs ? p[2 + k] : 0.0);
-                        if (lane == 0) s_mx[o * kMaxRel + k] = mk;
+                    for (int i0 = 0; i0 < w; i0 += 4) {
+                        double v[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = lane < nbs && i0 + i < w ? p[i0 + i] : 0.0;
+#pragma unroll
+                        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const double x = __shfl_down(v[i], off, 64);
+                                v[i] = i0 + i < 2 ? v[i] + x : fmax(v[i], x);
+                            }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (lane == 0 && i0 + i < w)
+                                (i0 + i == 0   ? s_sum[o]
+                                 : i0 + i == 1 ? s_sabs[o]
+                                               : s_mx[o * kMaxRel + i0 + i - 2]) = v[i];
                     }
                 }
             }
@@ -654,20 +696,41 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
             const int K = STAGE == 3 ? a.kcap : a.rs[Q.rep_base + o].kprimes;
             if (K <= 0 || K > a.kcap) continue;
             const int64_t mod_off = Q.mod_off + (int64_t)o * Q.nbm;  // repetitions' residues follow each other
-            for (int i = 0; i < K; ++i) {
-                const PrimeDev &P = a.primes[i];
-                const RingM R{P.p, P.pinv_neg};
-                uint32_t v = 0u;
-                for (int b = lane; b < Q.nbm; b += 64) v = R.add(v, a.modp[(size_t)i * a.mod_plane + mod_off + b]);
-                for (int off = 32; off > 0; off >>= 1) v = R.add(v, __shfl_down(v, off, 64));
-                if (lane == 0) s_res[o * kMaxPrimes + i] = v;
+            constexpr int U = 4;  // primes at a time
+            for (int i0 = 0; i0 < K; i0 += U) {
+                uint32_t v[U], p[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = 0u;
+                    p[u] = a.primes[min(i0 + u, K - 1)].p;
+                }
+                for (int b0 = lane; b0 < Q.nbm; b0 += 128) {
+                    uint32_t x[U][2];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            x[u][j] = i0 + u < K && b0 + 64 * j < Q.nbm
+                                          ? a.modp[(size_t)(i0 + u) * a.mod_plane + mod_off + b0 + 64 * j]
+                                          : 0u;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) v[u] = RingM{p[u], 0u}.add(v[u], x[u][j]);
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = RingM{p[u], 0u}.add(v[u], __shfl_down(v[u], off, 64));
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (lane == 0 && i0 + u < K) s_res[o * kMaxPrimes + i0 + u] = v[u];
             }
         }
     }
     __syncthreads();
+    RepDev rp{};  // this repetition's record lives in registers; written back once at the end
     if (t < Q.d) {
-        // this repetition's record lives in registers; written back once at the end
-        RepDev rp{};
         if constexpr (STAGE == 2) rp = a.rs[Q.rep_base + t];
         // additions on any term's path to a sum: its thread's serial sum (per_thread - 1),
         // block_sum (6 shuffle levels, then the kThreads / 64 wavefront sums one after
@@ -769,7 +832,7 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                                                           : log2(2.0 * (fabs(xf) + bound) + 4.0) + 1.0;
                             double have = 0.0;
                             int K = 0;
-                            while (K < kMaxPrimes && have <= need) have += a.crt.log2p[K++];
+                            while (K < kMaxPrimes && have <= need) have += s_crt.log2p[K++];
                             if (have > need) rp.kprimes = K;
                             else rp.status = 1;
                         } else {
@@ -806,34 +869,44 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                         const double need = fmax(lb, 0.0) + 2.0 + 1e-6;
                         double have = 0.0;
                         int K = 0;
-                        while (K < kMaxPrimes && have <= need) have += a.crt.log2p[K++];
+                        while (K < kMaxPrimes && have <= need) have += s_crt.log2p[K++];
                         if (have > need) rp.kprimes = K;
                         else rp.status = 1;
                     }
                 }
             }
         }
+        s_kp[t] = rp.kprimes;
+        s_val[t] = rp.xf;
+        s_ex[t] = plan == CS_PLAN_SPECTRAL && rp.window;
+    }
+    if constexpr (STAGE != 1) {
+        // a thread per (repetition, prime): the residue out of Montgomery form, less the
+        // window's centre
+        __syncthreads();
+        for (int e = t; e < Q.d * kMaxPrimes; e += NT) {
+            const int o = e / kMaxPrimes, i = e - o * kMaxPrimes;
+            if (i >= s_kp[o] || s_kp[o] > a.kcap) continue;
+            const PrimeDev &P = a.primes[i];
+            const RingM R{P.p, P.pinv_neg};
+            uint32_t x = s_res[e];  // the sum of the block partials, from above
+            if (plan == CS_PLAN_SPECTRAL) x = R.mul(x, P.minv[Q.log2m]);
+            x = R.mul(x, 1u);
+            if (s_ex[o]) x = R.sub(x, mod_i128(double_to_i128(rint(s_val[o])), P, R));
+            s_res[e] = x;
+        }
+        __syncthreads();
+    }
+    if (t < Q.d) {
         if (STAGE != 1 && rp.kprimes > 0 && rp.kprimes <= a.kcap) {  // stage 2: residues -> exact value
             const int K = rp.kprimes;
             uint32_t *res = s_res + t * kMaxPrimes, *dig = s_dig + t * kMaxPrimes;
-            for (int i = 0; i < K; ++i) {
-                const PrimeDev &P = a.primes[i];
-                const RingM R{P.p, P.pinv_neg};
-                uint32_t s = res[i];  // the sum of the block partials, from above
-                if (plan == CS_PLAN_SPECTRAL) s = R.mul(s, P.minv[Q.log2m]);
-                res[i] = R.mul(s, 1u);  // out of Montgomery form
-            }
             if (plan == CS_PLAN_SPECTRAL && rp.window) {
                 const __int128 x0 = double_to_i128(rint(rp.xf));
-                for (int i = 0; i < K; ++i) {
-                    const uint32_t p = a.crt.p[i];
-                    const uint32_t x0m = mod_i128(x0, p);
-                    res[i] = (uint32_t)(((uint64_t)res[i] + p - x0m) % p);
-                }
-                garner(res, K, a.crt, dig);
+                garner(res, K, s_crt, a.primes, dig);
                 __int128 delta;
                 double dd;
-                if (digits_to_i128(dig, K, a.crt, &delta, &dd)) {
+                if (digits_to_i128(dig, K, s_crt, &delta, &dd)) {
                     const __int128 x = x0 + delta;
                     rp.lo = (int64_t)(uint64_t)(unsigned __int128)x;
                     rp.hi = (int64_t)(uint64_t)((unsigned __int128)x >> 64);
@@ -843,10 +916,10 @@ __global__ __launch_bounds__(NT) void k_finalize(FinalizeArgs a)
                     rp.status = 1;
                 }
             } else {
-                garner(res, K, a.crt, dig);
+                garner(res, K, s_crt, a.primes, dig);
                 __int128 x;
                 double dv;
-                if (digits_to_i128(dig, K, a.crt, &x, &dv)) {
+                if (digits_to_i128(dig, K, s_crt, &x, &dv)) {
                     rp.lo = (int64_t)(uint64_t)(unsigned __int128)x;
                     rp.hi = (int64_t)(uint64_t)((unsigned __int128)x >> 64);
                     rp.exact = 1;
@@ -1053,6 +1126,9 @@ void build_crt_tables()
             g_crt.half[K - 1][i] = (uint32_t)x;
         }
     }
+    for (int j = 0; j < kMaxPrimes; ++j)
+        for (int i = 0; i < kMaxPrimes; ++i)
+            g_crt.inv[j][i] = (uint32_t)(((uint64_t)g_crt.inv[j][i] << 32) % P[i].p);
     g_crt_ready = true;
 }
 
@@ -1534,8 +1610,8 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     const std::vector<int64_t> dot_pre = prefix_of(dot_idx.size(), [&](size_t i) { return q_blocks_of(dot_idx[i]); });
     const size_t o_ndpre = c.take(nd_pre.size() * sizeof(int64_t));
     const size_t o_dotpre = c.take(dot_pre.size() * sizeof(int64_t));
-    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_gitem, o_gipre, o_gren, o_gimn;
-    std::vector<std::vector<int64_t>> g_pre, g_ipre;
+    std::vector<size_t> o_gidx, o_gre, o_gim, o_gpre, o_gptr, o_gitem, o_gipre, o_gspre, o_gren, o_gimn;
+    std::vector<std::vector<int64_t>> g_pre, g_ipre, g_spre;
     std::vector<std::vector<ProductItem>> g_items;
     // workgroups of a spectral query's product: powers of two, within its partials (a shared
     // call's are those of k_spec_mod)
@@ -1563,6 +1639,10 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             for (int k = 0; k < qd[q].r; ++k) g_items.back().back().vec[k] = qd[q].mod0[k];
         }
         g_ipre.push_back(prefix_of(G.queries.size(), [&](size_t i) { return q_products_of(G.queries[i]); }));
+        g_spre.push_back(prefix_of(G.queries.size(), [&](size_t i) {
+            return (int64_t)((qd[G.queries[i]].d + 1) / 2) * qd[G.queries[i]].nb;  // two repetitions at a time
+        }));
+        o_gspre.push_back(c.take(g_spre.back().size() * sizeof(int64_t)));
         o_gren.push_back(c.take(G.re_norm.size() * sizeof(int64_t)));
         o_gimn.push_back(c.take(G.im_norm.size() * sizeof(int64_t)));
         o_gitem.push_back(c.take(g_items.back().size() * sizeof(ProductItem)));
@@ -1644,6 +1724,7 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
             Group &G = kv.second;
             put(o_gidx[gi], G.queries);
             put(o_gpre[gi], g_pre[gi]);
+            put(o_gspre[gi], g_spre[gi]);
             put(o_gren[gi], G.re_norm);
             put(o_gimn[gi], G.im_norm);
             put(o_gitem[gi], g_items[gi]);
@@ -1792,9 +1873,9 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
                                    reinterpret_cast<const int64_t *>(wb + o_gimn[gi]), d_norms};
             st = fft_f64_forward(sv, (int)G.re.size(), Z, G.log2m, G.S, tw, s);
             if (st != CS_OK) return st;
-            hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_pre[gi].back()), dim3(kThreads), 0, s, Z, d_q,
+            hipLaunchKernelGGL(k_spec_f64, dim3((unsigned)g_spre[gi].back()), dim3(kThreads), 0, s, Z, d_q,
                                reinterpret_cast<const int32_t *>(wb + o_gidx[gi]),
-                               reinterpret_cast<const int64_t *>(wb + o_gpre[gi]), (int)G.queries.size(), d_spec);
+                               reinterpret_cast<const int64_t *>(wb + o_gspre[gi]), (int)G.queries.size(), d_spec);
             CSK_HIP(hipGetLastError());
             ++gi;
         }
