@@ -249,24 +249,27 @@ __global__ __launch_bounds__(kSqB) void k_subq_hash(const uint32_t *__restrict__
     }
 }
 
-// Pass 2.  Block (range r, slab = target * d + repetition): two copies of 2^14 int32
-// LDS counters (even and odd lanes), every block's run of this range added, the sums
-// added into the counters this workgroup alone owns.
+// Pass 2.  Block (range r, slab = target * d + repetition): 2^14 int32 LDS counters, every
+// block's run of this range added, the sums added into the counters this workgroup alone
+// owns.  COPIES: 2 where a workgroup per CU covers the grid (even and odd lanes add to
+// different ones), else 1 (two workgroups share a CU).  log2w: lanes that read a run together.
+template <int COPIES>
 __global__ __launch_bounds__(kSqAB) void k_subq_accum(const uint16_t *__restrict__ rec,
                                                       const uint16_t *__restrict__ tab, uint64_t nblk,
-                                                      int32_t ranges, uint32_t m, int32_t d, SqTargets T)
+                                                      int32_t ranges, uint32_t m, int32_t d, SqTargets T,
+                                                      int32_t log2w)
 {
     extern __shared__ __align__(16) uint32_t s_dyn[];
-    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_dyn);  // [2][kSqR]
-    uint32_t *s_run = s_dyn + 2 * kSqR;                    // [nblk]: start / 4 | words << 16
+    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_dyn);  // [COPIES][kSqR]
+    uint32_t *s_run = s_dyn + COPIES * kSqR;                   // [nblk]: start / 4 | words << 16
     const int r = blockIdx.x;
     const uint64_t slab = blockIdx.y;
     const int i = (int)(slab / d), t = (int)(slab % d);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t *my_cnt = s_cnt + (lane & 1) * kSqR;
+    int32_t *my_cnt = s_cnt + (lane & (COPIES - 1)) * kSqR;
     constexpr int kWaves = kSqAB / 64;
     constexpr int kInFlight = 4;
-    for (uint32_t e = threadIdx.x; e < 2 * kSqR / 4; e += kSqAB) reinterpret_cast<int4 *>(s_cnt)[e] = make_int4(0, 0, 0, 0);
+    for (uint32_t e = threadIdx.x; e < COPIES * kSqR / 4; e += kSqAB) reinterpret_cast<int4 *>(s_cnt)[e] = make_int4(0, 0, 0, 0);
     for (uint64_t b = threadIdx.x; b < nblk; b += kSqAB) {
         const uint16_t *tb = tab + (slab * nblk + b) * (uint64_t)(ranges + 1);
         const uint32_t beg = tb[r], end = tb[r + 1];
@@ -280,31 +283,55 @@ __global__ __launch_bounds__(kSqAB) void k_subq_accum(const uint16_t *__restrict
             if (v[k] != kSqPad) atomicAdd(&my_cnt[v[k] & (kSqR - 1)], (v[k] >> kSqLog2R) & 1u ? -1 : 1);
     };
     const uint2 *rt = reinterpret_cast<const uint2 *>(rec + slab * nblk * kSqCap);
-    for (uint64_t b0 = wave; b0 < nblk; b0 += (uint64_t)kWaves * kInFlight) {
-        uint32_t run[kInFlight];
+    const uint32_t width = 1u << log2w, sub = (uint32_t)lane & (width - 1u);
+    const uint32_t groups = 64u >> log2w;  // per wavefront
+    for (uint64_t b0 = (uint64_t)wave * groups + ((uint32_t)lane >> log2w); b0 < nblk;
+         b0 += (uint64_t)kWaves * groups * kInFlight) {
+        uint32_t len[kInFlight];
         const uint2 *p[kInFlight];
+        uint2 w[kInFlight];
         uint32_t lmax = 0;
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-            const uint64_t b = b0 + (uint64_t)u * kWaves;
-            run[u] = b < nblk ? s_run[b] : 0u;
-            p[u] = rt + (b < nblk ? b : 0) * (kSqCap / 4) + (run[u] & 0xFFFFu);
-            lmax = max(lmax, run[u] >> 16);
+            const uint64_t b = b0 + (uint64_t)u * kWaves * groups;
+            const uint32_t run = b < nblk ? s_run[b] : 0u;
+            len[u] = run >> 16;
+            p[u] = rt + (b < nblk ? b : 0) * (kSqCap / 4) + (run & 0xFFFFu);
+            lmax = max(lmax, len[u]);
+            w[u] = sub < len[u] ? p[u][sub] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
         }
-        for (uint32_t k = lane; k < lmax; k += 64) {
-            uint2 w[kInFlight];
+        for (uint32_t k = sub; k < lmax; k += width) {
+            uint2 next[kInFlight];
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) w[u] = k < (run[u] >> 16) ? p[u][k] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
+            for (int u = 0; u < kInFlight; ++u)
+                next[u] = k + width < len[u] ? p[u][k + width] : make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) add4(w[u]);
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) w[u] = next[u];
         }
     }
     __syncthreads();
     uint64_t *out = T.p[i] + (uint64_t)t * m + ((uint64_t)r << kSqLog2R);
     const uint32_t span = min(kSqR, m - ((uint32_t)r << kSqLog2R));  // the last range may be partial
-    for (uint32_t e = threadIdx.x; e < span; e += kSqAB) {
-        const int64_t v = (int64_t)s_cnt[e] + (int64_t)s_cnt[kSqR + e];
-        if (v) out[e] += (uint64_t)v;
+    constexpr int U = 8;  // counters per thread whose loads are issued together
+    for (uint32_t e0 = threadIdx.x; e0 < span; e0 += kSqAB * U) {
+        int64_t v[U];
+        uint64_t o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = e0 + u * kSqAB;
+            v[u] = 0;
+            if (e < span) {
+                v[u] = s_cnt[e];
+                if constexpr (COPIES == 2) v[u] += s_cnt[kSqR + e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = v[u] ? out[e0 + u * kSqAB] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v[u]) out[e0 + u * kSqAB] = o[u] + (uint64_t)v[u];
     }
 }
 
@@ -375,9 +402,12 @@ cs_status sq_launch(SubqHandle &h, int rel, const uint32_t *keys, const int64_t 
         return CS_OK;
     }
     if (!sq_accum_ready) {
-        CSK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_subq_accum),
+        CSK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_subq_accum<2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)((2 * kSqR + 1024) * sizeof(uint32_t))));
+        CSK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_subq_accum<1>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)((kSqR + 1024) * sizeof(uint32_t))));
         sq_accum_ready = true;
     }
     int n_cu = 256;
@@ -401,9 +431,15 @@ cs_status sq_launch(SubqHandle &h, int rel, const uint32_t *keys, const int64_t 
             hipLaunchKernelGGL((k_subq_hash<NC, false>), dim3((unsigned)nblk, groups), dim3(kSqB), 0, s, kp, wp, len,
                                R.coef_dev, R.cpr, D, bm, d, ranges, rpg, nblk, rec, tab);
         CSK_HIP(hipGetLastError());
-        const size_t lds = (2 * kSqR + nblk) * sizeof(uint32_t);
-        hipLaunchKernelGGL(k_subq_accum, dim3(ranges, D.nt * d), dim3(kSqAB), lds, s, rec, tab, nblk, ranges, h.m,
-                           d, T);
+        // as in the partition update's second pass: one counter copy beyond a workgroup per CU
+        // (2^18, d = 15, ten sub-chains: 68 us a call on average with two copies, 61 by this rule),
+        // and lanes for a run of about 512 / ranges words
+        const bool one_copy = (uint64_t)ranges * D.nt * d > (uint64_t)n_cu;
+        int log2w = 6;
+        while (log2w > 3 && (512 / ranges) < (3 << (log2w - 1))) --log2w;
+        const size_t lds = ((one_copy ? 1 : 2) * kSqR + nblk) * sizeof(uint32_t);
+        hipLaunchKernelGGL(one_copy ? &k_subq_accum<1> : &k_subq_accum<2>, dim3(ranges, D.nt * d), dim3(kSqAB), lds, s,
+                           rec, tab, nblk, ranges, h.m, d, T, log2w);
         CSK_HIP(hipGetLastError());
     }
     return CS_OK;
