@@ -69,6 +69,8 @@ struct Handle {
     bool own_scratch = false;          // the handle keeps its own update scratch (grown on demand)
     void *scratch = nullptr;           // partial sums of the LDS-segmented update, partition records
     size_t scratch_bytes = 0;
+    uint64_t scratch_n = 0;            // tuples of the last call it was found to hold (0: none)
+    bool scratch_unit = false;         //   and whether its Deltas were +-1
     void *filter_scratch = nullptr;    // filtered 16-bit path: partial sums and a round of kept keys
     size_t filter_scratch_bytes = 0;   //   (allocated by the first filtered update that needs it)
     void *result_host = nullptr;       // pinned host staging for results

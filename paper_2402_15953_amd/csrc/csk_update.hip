@@ -2018,8 +2018,12 @@ static SegGeom balanced_geometry(uint32_t m, int32_t d, uint32_t max_r, int elem
         consider(c0);
         for (double i : {it, it + 1.0, it - 1.0})
             if (i > 0.0) consider(std::floor(kilo / i) + 1.0);
-        for (int k = 1; k < 8 && one < 8; ++k) consider(k);
-        for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(256 * k / g.segments);
+        // (neither beyond twice c0: there more chunks only cost)
+        for (int k = 1; k < 8 && one < 8 && k <= 2.0 * c0 + 1.0; ++k) consider(k);
+        for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            if (256 * k / g.segments > 2.0 * c0 + 1.0) break;
+            consider(256 * k / g.segments);
+        }
     }
     return best;
 }
