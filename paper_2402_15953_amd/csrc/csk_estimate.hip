@@ -17,8 +17,9 @@
 //             within B_t of the fp64 value.
 //   GENERAL   some component joins three or more attributes: Alg. 3's register program
 //             (Hadamard products, cross-correlations through NTT / inverse NTT) in
-//             modular arithmetic for enough primes to cover |X_t| <= prod_k ||c_k||_1,
-//             then the Chinese remainder theorem.
+//             modular arithmetic for enough primes to cover |X_t| <= prod_k ||c_k||_1 (two
+//             factors by ||c_k||_2 where every component joins two attributes and m is no
+//             power of two), then the Chinese remainder theorem.
 // The median (lower middle element for even d) is taken on the device.
 #include <hip/hip_runtime.h>
 
@@ -1778,11 +1779,13 @@ cs_status estimate_batch(Handle *const *hs, int nq, hipStream_t s, cs_estimate_t
     // chains share nothing until the finalize: with at most kOverlapPrimes primes and at
     // least kOverlapMinResidues residues the modular one runs on the workspace's side
     // stream (forked behind the table upload, joined before the finalize), so that the
-    // launches of either overlap the other's.  Measured: overlapping five primes at
-    // m = 2^18 with 75 sketch vectors made the estimate 10% slower (the modular chain
-    // fills the chip alone), two or three primes 1-13% faster; for small estimates
-    // (thousands of handles with m <= 2^16, one estimate each) the fork and join cost
-    // more than they save and halved the estimates per second.
+    // launches of either overlap the other's.  Measured when the transforms were slower:
+    // overlapping five primes at m = 2^18 with 75 sketch vectors made the estimate 10%
+    // slower (the modular chain fills the chip alone), two or three primes 1-13% faster; for
+    // thousands of handles with m <= 2^16, one estimate each, the fork and join halved the
+    // estimates per second.  With the present ones, limits of 2^22 residues or of five
+    // primes change a single estimate (m = 2^14 to 2^18, d = 5 to 15) by less than the runs
+    // differ.
     int kdone = 0;
     const int ks = ws.spec_k >= 0 ? std::min(ws.spec_k, kSpecPrimes) : kSpecPrimes;
     bool spec = false, overlap = false;

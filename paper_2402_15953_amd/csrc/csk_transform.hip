@@ -677,7 +677,7 @@ int fft_norm_blocks(int log2m, int S) { return log2m <= 12 ? 1 : (1 << S) >> fft
 
 int fft_norm_adds(int log2m, int S)
 {
-    if (log2m <= 12) {  // k_fft_f64 or k_fft_product
+    if (log2m <= 12) {
         const int EB = fft_elems(log2m, 0, true);
         return EB + 6 + pass_threads(log2m, 0, EB) / 64;
     }

@@ -945,7 +945,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(const CT *__restrict__ pa
 // halves the lanes of one add that meet on a skewed bucket's word), adds +-1 for every
 // record of its group from every block (8-byte loads of four records, four runs in flight
 // per group of lanes), adds the hot tuples whose bucket falls in its range, and adds the non-zero
-// sums of the two copies into the sketch (it owns those counters: plain
+// sums into the sketch (it owns those counters: plain
 // read-modify-write, no atomics).  One extra workgroup writes the relation's hints: the
 // distinct hot tuples of the first eight blocks, ranked by their |Delta sum| over all
 // blocks.
